@@ -60,7 +60,8 @@ struct Job {
     int32_t *diag_cnt;            // optional [n_est][3][n] (n_xz, n_yz, n_z)
     // neighbour-list path only (see ListSet): list set index, and the
     // permuted X columns transposed so that the estimates of one row are
-    // adjacent: xt[c][i][e] = X_c[pi_e(i)] ([dx][n][n_est]) for the scan (xp
+    // adjacent, in scan groups (scan_groups): xt[c][g][i][l] = X_c[pi_e(i)],
+    // e the l-th estimate of group g ([dx][groups][n][64]) for the scan (xp
     // holds the same values estimate-major for the fallback).  The per-row
     // counts go to pk; eps and cnt are the caller's diagnostics ([n_est][n],
     // [n_est][3][n]) or null.
@@ -97,19 +98,11 @@ constexpr int kNoZSortMax = 16384;
 // the (Y,Z) max-norm distance d_yz(i,j) in the smallest key buckets that fit
 // m1 entries, list 2 the same for the Z distance d_z(i,j) and m2.  A key is
 // the top 12 bits of the distance's float encoding (8 exponent and 4
-// mantissa bits), so a list is ordered by bucket, not fully sorted.  List 2 entries
-// also carry d_yz (d_yz >= d_z, so every row with d_yz below a radius is in
-// the part of list 2 below that radius).  bound[i][w] is a
+// mantissa bits), so a list is ordered by bucket, not fully sorted.  bound[i][w] is a
 // lower bound of every unlisted distance (+inf when nothing is left out), so
 // a radius r <= bound[i][w] is decided by the list alone.
 struct LEnt {
-    float d;                      // d_yz
-    int32_t j;                    // row
-};
-
-struct LEnt2 {
-    float dz;                     // d_z (the list key)
-    float dyz;                    // d_yz, so that n_yz is counted from this list too
+    float d;                      // d_yz in list 1, d_z in list 2 (the list key)
     int32_t j;                    // row
 };
 
@@ -125,19 +118,18 @@ struct ListSet {
     int m1, m2;                   // list capacities per row
     int s1, s2;                   // row strides: capacity + kListPad sentinels
     LEnt *l1;                     // [n][s1]  (Y,Z) list
-    LEnt2 *l2;                    // [n][s2]  Z list
+    LEnt *l2;                     // [n][s2]  Z list
     int32_t *len;                 // [n][2]
     float *bound;                 // [n][2]
     // One Z column and n <= kRankMaxN: the rows sorted by z, so that the rows
     // within a radius of a row's z are one range of ranks (float subtraction
     // is monotone in its first operand).  zs[r] the r-th smallest z, zord[r]
-    // its row, zrank the inverse, yr[c][r] = Y_c[zord[r]].  The counts of
-    // such a set's jobs come from these ranges, not from the Z list (whose
-    // capacity is then kRankListCap).  Null otherwise.
+    // its row, zrank the inverse.  n_z and n_xz of such a set's jobs come
+    // from these ranges, not from the Z list (whose capacity is then
+    // kRankListCap).  Null otherwise.
     float *zs;
     int32_t *zord;
     int32_t *zrank;
-    float *yr;
 };
 
 constexpr int kCoopLanes = 4;                 // default cooperative-finish threshold of the scan
@@ -156,6 +148,27 @@ constexpr int kListStatStride = 16;           // words (64 bytes) per slot
 constexpr int kListCounterWords = kListStatWord + kListStatSlots * kListStatStride;
 constexpr int kKeyShift = 19;                 // 4096 key buckets
 constexpr int kKeyBins = 1 << (32 - kKeyShift - 1);
+
+// Scan groups of a job: its E estimates in ceil(E / 64) groups of nearly
+// equal size, group g holding the estimates g*E/G .. (g+1)*E/G - 1, one lane
+// each.
+constexpr int kScanLanes = 64;
+#ifdef __HIP__
+#define MTE_HD __host__ __device__
+#else
+#define MTE_HD
+#endif
+MTE_HD inline int scan_groups(int n_est) { return (n_est + kScanLanes - 1) / kScanLanes; }
+MTE_HD inline int scan_group_first(int g, int n_est) { return (int)((int64_t)g * n_est / scan_groups(n_est)); }
+MTE_HD inline int scan_group_of(int e, int n_est) {
+    return (int)((((int64_t)e + 1) * scan_groups(n_est) - 1) / n_est);
+}
+
+// A range of rows (positions in the set's row order) of one scan group.
+struct ScanUnit {
+    int32_t job, group, row0, nrows;
+};
+constexpr int kScanRows = kWaves;             // rows per scan block, one wave each
 
 // One launch of the list path over `n_jobs` jobs (all with dz > 0).
 struct ListLaunch {
@@ -186,17 +199,15 @@ struct ListLaunch {
     int max_chunks;               // largest ceil(n / kChunk) of the jobs (reduction grid)
     int sortx;                    // some job has no Z: sort the X columns (Job::xs)
     int coop_lanes;               // the scan finishes cooperatively once this many lanes remain
-    int grouped;                  // 1 (one job): lanes over 64-estimate groups, XCD-contiguous
-                                  // blocks; 2 (several jobs): XCD-dealt units, below
-    // grouped == 2: unit u = (job, 64-estimate group of the job, the last one
-    // taking the remainder), its lanes row-major in the set's row order and
-    // padded to whole blocks, runs on XCD u % kXcds.  xcd_off[x * (unit_t + 1)
-    // + t] is the first block, counting XCD x's blocks alone, of x's t-th unit
+    int grouped;                  // 1: a scan group's rows on as few XCDs as fill them evenly; 0: on all
+    // Scan units, dealt to the XCDs in turn (unit u on XCD u % kXcds, each XCD
+    // taking its units one after another): xcd_off[x * (unit_t + 1) + t] is
+    // the first block, counting XCD x's blocks alone, of x's t-th unit
     // (unit x + t * kXcds; the entry at t = unit_t, and past x's last unit,
-    // is x's block count); unit_info[u] = job << 32 | group.
+    // is x's block count).
     const int64_t *xcd_off;
-    const int64_t *unit_info;
-    int unit_t, n_units;
+    const ScanUnit *units;
+    int unit_t;
     int64_t scan_blocks;          // grid of the scan
     int scan_step;                // list entries per step of the scan's lane-by-lane loops (4, 8)
     int rank_sets;                // sets counted by ranks (ListSet::zs)

@@ -32,7 +32,7 @@ __device__ __forceinline__ int n_rounds_dev(int64_t n) {
 }
 
 // ------------------------------------------------------------------ permute
-// xp[e][c][i] = X_c[src_e(i)] (and, for the list path, also xt[c][i][e]) for
+// xp[e][c][i] = X_c[src_e(i)] (and, for the list path, also the scan's copy xt) for
 // every job, estimate and row.  Rows are R = J.reps replications of nr = n/R rows
 // (R = 1: one block of all rows).  One thread block per (job, estimate,
 // replication, 1024-row chunk of the replication), keyed by the estimate's
@@ -153,10 +153,13 @@ __global__ __launch_bounds__(kPermThreads) void permute_kernel(const Job *__rest
             if (t >= nr) break;
             const int64_t i = base + t;
             const int64_t x = xbase + (int64_t)src[q];
+            // the scan's copy: group g's estimates of one row in 64 adjacent words
+            const int gE = J.n_est, gG = scan_groups(gE), gg = scan_group_of(e, gE);
+            const int gl = e - scan_group_first(gg, gE);
             const int64_t ri = J.xr ? (int64_t)min(max(J.zrank[i], 0), J.n - 1) : 0;
             for (int c = 0; c < J.dx; ++c) {
                 const float v = J.cols[c][x];
-                if (J.xt) J.xt[((int64_t)c * J.n + i) * J.n_est + e] = v;
+                if (J.xt) J.xt[(((int64_t)c * gG + gg) * J.n + i) * kScanLanes + gl] = v;
                 J.xp[((int64_t)e * J.dx + c) * J.n + i] = v;
                 if (J.xr) J.xr[((int64_t)e * J.dx + c) * J.n + ri] = v;
             }

@@ -17,11 +17,11 @@
 //            estimate's permuted X; it stops at the first bucket whose floor
 //            reaches the current k-th distance (nothing later can enter).  The
 //            radius is exact when it stopped that way or when the k-th
-//            distance is at most the list's bound.  n_z, n_yz and n_xz scan
-//            list 2 (whose entries also carry d_yz) until its bucket floor
+//            distance is at most the list's bound.  n_yz counts the entries of
+//            list 1 below eps, n_z and n_xz scan list 2 until its bucket floor
 //            reaches eps, exact when it stopped that way or eps <= its bound.
-//            Without Z (one X column) there is no list 2: n_y comes from list
-//            1 and n_x from range counts on the sorted X column;
+//            Without Z (one X column) there is no list 2: n_x comes from range
+//            counts on the sorted X column;
 //   fallback the pairs the lists cannot decide (rare) are queued and redone
 //            over all rows (a block per pair, or a wave when they are many);
 //   reduce   the digamma sum per estimate in the same fixed order as the
@@ -72,13 +72,6 @@ __device__ __forceinline__ void gstore(LEnt *p, uint32_t idx, const LEnt &v) {
     auto *q = (__attribute__((address_space(1))) uint32_t *)(p + idx);
     q[0] = __float_as_uint(v.d);
     q[1] = (uint32_t)v.j;
-}
-
-__device__ __forceinline__ void gstore(LEnt2 *p, uint32_t idx, const LEnt2 &v) {
-    auto *q = (__attribute__((address_space(1))) uint32_t *)(p + idx);
-    q[0] = __float_as_uint(v.dz);
-    q[1] = __float_as_uint(v.dyz);
-    q[2] = (uint32_t)v.j;
 }
 
 // The same with a byte offset: the address is then a uniform base plus one
@@ -372,7 +365,7 @@ __global__ __launch_bounds__(kBT) void list_build_kernel(const ListSet *__restri
     // pass 2 with the kept prefixes and the rows' list bases in registers
     uint32_t keep[QB][2];
     LEnt *out1[QB];
-    LEnt2 *out2[QB];
+    LEnt *out2[QB];
 #pragma unroll
     for (int r = 0; r < QB; ++r) {
         keep[r][0] = sm.kept_bins[r][0];
@@ -392,7 +385,7 @@ __global__ __launch_bounds__(kBT) void list_build_kernel(const ListSet *__restri
         if (k2 < keep[r][1]) {
             const uint32_t pos =
                 bin_get<PACK>(atomicAdd(bin_word<PACK>(sm.h[r][copy], 1, k2), bin_inc<PACK>(1)), 1);
-            if (pos < m2) gstore(out2[r], pos, LEnt2{a, c, j});
+            if (pos < m2) gstore(out2[r], pos, LEnt{a, j});
         }
     });
     // lengths, bounds and the sentinels after each list.  A list is whole
@@ -413,7 +406,7 @@ __global__ __launch_bounds__(kBT) void list_build_kernel(const ListSet *__restri
         const float bound = whole ? inf_f() : __uint_as_float(kb << kKeyShift);
         const float sent = whole ? inf_f() : __uint_as_float((kb << kKeyShift) + 1u);
         if (w == 0) S.l1[i * S.s1 + kr + u] = LEnt{sent, (int32_t)i};
-        else S.l2[i * S.s2 + kr + u] = LEnt2{sent, inf_f(), (int32_t)i};
+        else S.l2[i * S.s2 + kr + u] = LEnt{sent, (int32_t)i};
         if (u == 0) {
             S.len[2 * i + w] = (int32_t)kr;
             S.bound[2 * i + w] = bound;
@@ -610,7 +603,7 @@ __global__ __launch_bounds__(kBT) void list_build_dz_kernel(const ListSet *__res
     // taken below it)
     uint32_t keep1[QB], keep2[QB];
     LEnt *out1[QB];
-    LEnt2 *out2[QB];
+    LEnt *out2[QB];
 #pragma unroll
     for (int r = 0; r < QB; ++r) {
         keep1[r] = min(kb[r][0], kSink);
@@ -643,7 +636,7 @@ __global__ __launch_bounds__(kBT) void list_build_dz_kernel(const ListSet *__res
                 }
                 if (ok && k2 < keep2[r]) {
                     const uint32_t pos = atomicAdd(&sm.h[r][k2], kInc2) >> 16;
-                    if (pos < m2) gstore(out2[r], pos, LEnt2{az[r][u], ayz[r][u], j});
+                    if (pos < m2) gstore(out2[r], pos, LEnt{az[r][u], j});
                 }
             }
     };
@@ -670,7 +663,7 @@ __global__ __launch_bounds__(kBT) void list_build_dz_kernel(const ListSet *__res
         const float bound = whole ? inf_f() : __uint_as_float(kbw << kKeyShift);
         const float sent = whole ? inf_f() : __uint_as_float((kbw << kKeyShift) + 1u);
         if (w == 0) S.l1[i * S.s1 + krw + u] = LEnt{sent, (int32_t)i};
-        else S.l2[i * S.s2 + krw + u] = LEnt2{sent, inf_f(), (int32_t)i};
+        else S.l2[i * S.s2 + krw + u] = LEnt{sent, (int32_t)i};
         if (u == 0) {
             S.len[2 * i + w] = (int32_t)krw;
             S.bound[2 * i + w] = bound;
@@ -843,451 +836,358 @@ __global__ __launch_bounds__(kSortThreads) void list_order_kernel(const ListLaun
 }
 
 // ------------------------------------------------------------------ scan
-// Each list row is followed by kListPad sentinel entries (row = self, d_yz =
-// +inf) whose key distance lies in the bucket that starts at the row's bound:
-// the bound plus one unit in the last place (+inf for a whole list: nothing
-// left out, or only rows at +inf).
+// Each list row is followed by kListPad sentinel entries (row = self) whose
+// key distance lies in the bucket that starts at the row's bound: the bound
+// plus one unit in the last place (+inf for a whole list: nothing left out,
+// or only rows at +inf).
 // A step of kU <= kListPad entries that starts at or before the list's end
 // then needs no bounds checks, and the last step of a list always ends on a
 // sentinel, whose bucket-floor test (floor = bound >= radius) is exactly the
 // condition under which the list decides the pair.  A sentinel that enters
 // the k-NN list (bound + 1 ulp < k-th distance) leaves a radius above the
 // bound, i.e. an undecided pair, as it should.
-// Entries per step (KU, the next step's loaded ahead): 8 or 4, a launch
-// parameter.  One-job launches take 8 (C2's scan: 0.33 ms against 0.38-0.40
-// with 4); launches of several jobs take 4, whose scan kernel holds 55
-// instead of 79 registers and runs 8 waves per SIMD instead of 6 (network
-// inference 1.08-1.09 s against 1.13-1.14 s with 8).
 constexpr int kU = 8;   // the largest step
 static_assert(kU <= kListPad, "a step must stay within the sentinels");
 
-template <int KMAX, int DXM>
-struct Lane {
-    const float *xt;
-    uint32_t cs;    // xt column stride n * n_est (xt has fewer than 2^31 elements)
-    uint32_t E, e;
-    int dx;
-    float xq[DXM];
+// Read-only memory addressed through the constant address space: a load from
+// a wave-uniform address is then a scalar load.
+template <class T>
+using Const = const __attribute__((address_space(4))) T;
+template <class T>
+__device__ __forceinline__ Const<T> *as_const(const T *p) { return (Const<T> *)p; }
 
-    __device__ Lane(const Job &J, int i, int e_) : e((uint32_t)e_) {
-        xt = J.xt;
-        E = (uint32_t)J.n_est;
-        cs = (uint32_t)J.n * E;
-        dx = J.dx;
-        Unroll<0, DXM>::upto(dx, [&](auto cc) {
-            constexpr int c = decltype(cc)::value;
-            xq[c] = xt[c * cs + (uint32_t)i * E + e];
-        });
-    }
-
-    // max-norm over the X columns between this lane's row and the rows of a
-    // step (under the estimate's permutation); all loads issued before use
-    template <class Ent, int NU>
-    __device__ __forceinline__ void xdist(const Ent (&en)[NU], float (&d)[NU]) const {
-        uint32_t o[NU];
-        float v[NU];
-#pragma unroll
-        for (int u = 0; u < NU; ++u) {
-            o[u] = (uint32_t)en[u].j * E + e;
-            v[u] = gload(xt, o[u]);
-        }
-#pragma unroll
-        for (int u = 0; u < NU; ++u) d[u] = absdiff(xq[0], v[u]);
-        Unroll<1, DXM>::upto(dx, [&](auto cc) {
-            constexpr int c = decltype(cc)::value;
-#pragma unroll
-            for (int u = 0; u < NU; ++u) v[u] = gload(xt, c * cs + o[u]);
-#pragma unroll
-            for (int u = 0; u < NU; ++u) d[u] = fmax_(d[u], absdiff(xq[c], v[u]));
-        });
-    }
+// A step's entries (distance, row) in scalar registers.
+template <int NU>
+struct Step {
+    float d[NU];
+    uint32_t j[NU];
 };
 
-template <class Ent, int NU>
-__device__ __forceinline__ void load_step(const Ent *l, Ent (&en)[NU]) {
+template <int NU>
+__device__ __forceinline__ void load_step(Const<uint32_t> *l, Step<NU> &s) {
 #pragma unroll
-    for (int u = 0; u < NU; ++u) en[u] = l[u];
+    for (int u = 0; u < NU; ++u) {
+        s.d[u] = __uint_as_float(l[2 * u]);
+        s.j[u] = l[2 * u + 1];
+    }
 }
 
-// Wave-uniform helpers of the cooperative finish.
+// Wave-uniform helpers.
 __device__ __forceinline__ uint64_t ballot(bool p) { return __ballot(p); }
 // The lane mask of one compare as the compare writes it (no round trip of the
 // predicate through a vector register); masks are combined by the scalar unit.
-// (The scan keeps ballot(): with this form its one-job launch at N = 10^4 took
-// 0.343 ms instead of 0.329.)
 __device__ __forceinline__ uint64_t cmp_mask(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 __device__ __forceinline__ int lowest(uint64_t m) { return __builtin_amdgcn_readfirstlane(__builtin_ctzll(m)); }
 __device__ __forceinline__ float bcast(float v, int o) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), o));
 }
 __device__ __forceinline__ int bcast(int v, int o) { return __builtin_amdgcn_readlane(v, o); }
-__device__ __forceinline__ uint32_t bcast(uint32_t v, int o) { return (uint32_t)__builtin_amdgcn_readlane((int)v, o); }
-template <class T>
-__device__ __forceinline__ T *bcast(T *v, int o) {
-    const uint64_t a = reinterpret_cast<uint64_t>(v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)a, o);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(a >> 32), o);
-    return reinterpret_cast<T *>(((uint64_t)hi << 32) | lo);
-}
 
-// The scans' divergence: the 64 lanes of a wave stop at very different list
-// positions (a few estimates of a row have radii far above the others), and
-// a wave runs until its slowest lane is done.  So each phase runs lane by lane
-// only while more than kCoopLanes lanes are still scanning; the wave then
-// finishes the remaining lanes one after the other with all 64 lanes, 64
-// list entries per step (a ballot per test, the top-k kept wave-uniform).
-// Entries, distances and tests are the same, so the results are too: a scan
-// may stop at any position whose bucket floor reaches the current radius.
-// A cooperative step gathers X for 64 different rows (64 cache lines instead
-// of the 2-4 of a lane-by-lane step, whose lanes are adjacent estimates), so
-// it only pays for the last few lanes: on C2 (N = 10^4, 201 estimates), in the
-// hardware block order, the scan took 0.62 ms without it, 0.48 ms with
-// kCoopLanes = 2, 0.50 ms with 4, 0.54 ms with 8, 0.67 ms with 16; with the
-// XCD-aware order (below), whose gathers mostly hit L2, 0.343 ms with 2,
-// 0.335 ms with 4, 0.350 ms with 6, 0.372 ms with 8.  2 or 4 entries per lane
-// per cooperative step were slower still (more scattered gathers past the
-// stop position).
-// The threshold (kCoopLanes by default) and the grouped lane order are launch
-// parameters, chosen by the tuner; neither changes a result.
-constexpr int kCoopU = 1;      // list entries per lane per cooperative step
-
-// UNITS: the lane order of launches of several jobs below (a separate
-// instance, so that the other orders' kernels keep their registers: with both
-// mappings in one kernel the one-job scan took 81 registers instead of 79, 5
-// waves per SIMD instead of 6, and 0.342 ms instead of 0.328 at N = 10^4).
-template <int KMAX, int DXM, int KU, bool UNITS>
+// A wave takes one row and one scan group of a job, a lane per estimate, so
+// that a step's list entries are the same for all lanes: they come through
+// the scalar cache into scalar registers, and the only vector loads are the
+// X gathers, 256 aligned bytes per entry (xt holds a group's estimates of one
+// row in adjacent words) at a uniform base.  With the entries loaded per lane
+// the broadcast loads (64 or 96 bytes a lane and step) took two thirds of the
+// vector memory path's cycles; the kernel held 79 registers (20 now).  Whole
+// tests, before and after: N = 10^4, dz = 5, 201 estimates 662 -> 560 us;
+// N = 30011, dz = 4, 101 estimates 3.00 -> 2.75 ms; 32 served requests
+// 11.4 -> 9.8 ms; network of 8 targets, T = 3000 101 -> 86 ms; without Z
+// (n_y was counted entry by entry in each lane) 3.07 -> 1.50 ms.
+//
+// The 64 lanes stop at very different list positions (a few estimates of a
+// row have radii far above the others).  Each phase runs with all lanes while
+// more than `coop` of them still need entries (a lane past its own stop reads
+// on without effect: no later entry is below its radius), then finishes the
+// remaining lanes one after the other with all 64 lanes, 64 list entries per
+// step.  Entries, distances and tests are the same, so the results are too.
+//
+// Phases: the k-NN radius over list 1; n_yz, the entries of list 1 below the
+// radius (every such entry precedes the stop, so no X is gathered); n_z and
+// n_xz over list 2.  Jobs counted by ranks leave after n_yz, jobs without Z
+// take n_x from the sorted X column.
+template <int KMAX, int DXM, int KU>
 __global__ __launch_bounds__(kBlock) void list_scan_kernel(const ListLaunch L) {
     static_assert(KU <= kU, "a step must stay within the sentinels");
     const int lane = tid_x() & 63;
-    // Lane order.  A launch of one job runs its lanes over estimate groups:
-    // group c holds rows x estimates 64c .. 64c + E_c - 1, row-major, with
-    // E_c = 64 but for the last group, which takes the remainder too (64 to
-    // 127 estimates; all E when E < 64), so that a wave takes one row and 64
-    // consecutive estimates, or two rows.  The hardware deals blocks to the
-    // XCDs in turn; block b is renumbered so that each XCD takes a contiguous
-    // range of lanes, i.e. one or two groups, and its L2 holds those groups'
-    // columns of xt (n * 256 bytes each) instead of all of them.  A launch of
-    // several jobs runs its lanes over units of (job, estimate group), each
-    // row-major over the group's estimates with the rows in the set's Morton
-    // order (rows that run together are near in (Y,Z), so their list entries
-    // and the X values they gather overlap), and deals the units to the XCDs
-    // in turn (unit u to XCD u mod 8, each XCD taking its units one after
-    // another): an XCD's L2 then holds the xt columns of the group it is on
-    // (n * 256 bytes) instead of gathering over whole jobs' xt (n * E * 4
-    // bytes each), and unequal jobs still spread over all XCDs.
-    const bool grouped = L.grouped == 1;          // set by the host for launches of one job only
+    const int wave = __builtin_amdgcn_readfirstlane(tid_x() >> 6);
+    // XCD x's k-th block: the last of x's units whose first block is <= k
+    const int64_t b = bid_x();
+    const int x = (int)(b % kXcds);
+    const int64_t k = b / kXcds;
+    Const<int64_t> *xo = as_const(L.xcd_off) + (int64_t)x * (L.unit_t + 1);
+    if (k >= xo[L.unit_t]) return;            // past x's blocks (no barrier in this kernel)
+    int lo = 0, hi = L.unit_t - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (xo[mid] <= k) lo = mid; else hi = mid - 1;
+    }
+    Const<ScanUnit> *U = as_const(L.units) + (x + lo * kXcds);
+    const int at = (int)(k - xo[lo]) * kScanRows + wave;
+    if (at >= U->nrows) return;
+    const int jb = U->job, grp = U->group, il = U->row0 + at;
+    Const<Job> *J = as_const(L.jobs) + jb;
+    Const<ListSet> *S = as_const(L.sets) + J->set;
+    const int n = J->n, E = J->n_est, dx = J->dx;
+    const int i = S->order ? as_const(S->order)[il] : il;
+    const int e0 = scan_group_first(grp, E), ne = scan_group_first(grp + 1, E) - e0;
+    const bool live = lane < ne;
+    const int e = e0 + min(lane, ne - 1);
+    const uint64_t livem = ballot(live);
     const int coop = L.coop_lanes;
-    int64_t b = bid_x();
-    if (grouped) {
-        const int64_t nb = (int64_t)__builtin_amdgcn_grid_size_x() / kBlock, hb = b;
-        const int64_t q = nb / kXcds, rem = nb % kXcds, x = hb % kXcds;
-        b = x * q + min(x, rem) + hb / kXcds;
-    }
-    bool live;
-    int64_t g;
-    int jb, i, e;
-    if constexpr (UNITS) {
-        // XCD x's k-th block: the last of x's units whose first block is <= k
-        const int x = (int)(b % kXcds);
-        const int64_t k = b / kXcds;
-        const int64_t *xo = L.xcd_off + (int64_t)x * (L.unit_t + 1);
-        if (k >= xo[L.unit_t]) return;            // past x's blocks (no barrier in this kernel)
-        int lo = 0, hi = L.unit_t - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (xo[mid] <= k) lo = mid; else hi = mid - 1;
-        }
-        const int u = x + lo * kXcds;
-        const int64_t info = L.unit_info[u];
-        jb = (int)(info >> 32);
-        const int grp = (int)(info & 0xffffffff);
-        const Job &Ju = L.jobs[jb];
-        const int ng = max(1, Ju.n_est / 64);
-        const int eg = grp == ng - 1 ? Ju.n_est - 64 * grp : 64;
-        const int64_t ul = (int64_t)Ju.n * eg;
-        const int64_t l0 = (k - xo[lo]) * kBlock + tid_x();
-        // lanes past the unit's last pair mirror it and store nothing
-        live = l0 < ul;
-        const int64_t lu = live ? l0 : ul - 1;
-        const int il = (int)(lu / eg);
-        e = 64 * grp + (int)(lu - (int64_t)il * eg);
-        const ListSet &Su = L.sets[Ju.set];
-        i = Su.order ? Su.order[il] : il;
-        g = L.lane_off[jb] + (int64_t)il * Ju.n_est + e;
-    } else {
-    const int64_t g0 = b * kBlock + tid_x();
-    // every lane of a wave takes part in the cooperative steps: lanes past
-    // the last pair mirror it and store nothing
-    live = g0 < L.lanes;
-    g = live ? g0 : L.lanes - 1;
-    jb = find_job(L.lane_off, L.n_jobs, g);
-    {
-        const Job &J = L.jobs[jb];
-        const ListSet &S = L.sets[J.set];
-        const int64_t r = g - L.lane_off[jb];
-        if (grouped) {
-            const int64_t gsz = (int64_t)J.n * 64;
-            const int ng = max(1, J.n_est / 64);
-            const int grp = (int)min(r / gsz, (int64_t)(ng - 1));
-            const int64_t rr = r - grp * gsz;
-            const int eg = grp == ng - 1 ? J.n_est - 64 * grp : 64;
-            i = (int)(rr / eg);
-            e = 64 * grp + (int)(rr - (int64_t)i * eg);
-        } else {
-            const int il = (int)(r / J.n_est);
-            e = (int)(r - (int64_t)il * J.n_est);
-            i = S.order ? S.order[il] : il;
-        }
-    }
-    }
-    const Job &J = L.jobs[jb];
-    const ListSet &S = L.sets[J.set];
-    const int n = J.n;
-    Lane<KMAX, DXM> ln(J, i, e);
 
-    // X distance of one entry under lane o's estimate (cooperative steps)
-    auto coop_xdist = [&](const float *xt, uint32_t cs, uint32_t E, uint32_t eo, int dxo, const float (&xq)[DXM],
-                          int32_t j) {
-        const uint32_t oo = (uint32_t)j * E + eo;
-        float d = absdiff(xq[0], gload(xt, oo));
-        Unroll<1, DXM>::upto(dxo, [&](auto cc) {
+    // X of row j under this lane's estimate: group column + 64 j + lane
+    const int64_t cs = (int64_t)scan_groups(E) * n * kScanLanes;
+    const float *xg = J->xt + (int64_t)grp * n * kScanLanes;
+    const uint32_t loff = (uint32_t)min(lane, ne - 1) * 4u;
+    auto xval = [&](int c, uint32_t j, uint32_t off) {
+        return gload_b(xg + c * cs, j * (kScanLanes * 4u) + off);
+    };
+    float xq[DXM];
+    Unroll<0, DXM>::upto(dx, [&](auto cc) {
+        constexpr int c = decltype(cc)::value;
+        xq[c] = xval(c, (uint32_t)i, loff);
+    });
+    // max-norm over the X columns between the lane's row and a step's rows
+    auto xdist = [&](const Step<KU> &s, float (&d)[KU]) {
+        float v[KU];
+#pragma unroll
+        for (int u = 0; u < KU; ++u) v[u] = xval(0, s.j[u], loff);
+#pragma unroll
+        for (int u = 0; u < KU; ++u) d[u] = absdiff(xq[0], v[u]);
+        Unroll<1, DXM>::upto(dx, [&](auto cc) {
             constexpr int c = decltype(cc)::value;
-            d = fmax_(d, absdiff(xq[c], gload(xt, c * cs + oo)));
+#pragma unroll
+            for (int u = 0; u < KU; ++u) v[u] = xval(c, s.j[u], loff);
+#pragma unroll
+            for (int u = 0; u < KU; ++u) d[u] = fmax_(d[u], absdiff(xq[c], v[u]));
+        });
+    };
+    // the same for one entry per lane under lane o's estimate
+    auto coop_xdist = [&](int o, const float (&q)[DXM], int32_t j) {
+        const uint32_t oo = (uint32_t)o * 4u;
+        float d = absdiff(q[0], xval(0, (uint32_t)j, oo));
+        Unroll<1, DXM>::upto(dx, [&](auto cc) {
+            constexpr int c = decltype(cc)::value;
+            d = fmax_(d, absdiff(q[c], xval(c, (uint32_t)j, oo)));
         });
         return d;
     };
 
     // k-NN radius over list 1
     float top[KMAX];
-    const int pad_front = KMAX - J.k;
+    const int pad_front = KMAX - J->k;
 #pragma unroll
     for (int m = 0; m < KMAX; ++m) top[m] = m < pad_front ? -inf_f() : inf_f();
-    const LEnt *l1 = S.l1 + (int64_t)i * S.s1;
-    const int len1 = S.len[2 * (int64_t)i];
-    bool decided = false, act = live;
-    int seen1 = 0, seen2 = 0;     // list entries read (statistics)
+    const LEnt *l1 = S->l1 + (int64_t)i * S->s1;
+    const int len1 = as_const(S->len)[2 * (int64_t)i];
+    uint64_t open = livem;        // lanes whose radius needs later entries
+    int64_t seen1 = 0, seen2 = 0; // list entries read by the pairs (statistics)
     int m1 = 0;
     {
-        LEnt cur[KU];
-        load_step(l1, cur);
-        while (__builtin_popcountll(ballot(act)) > coop) {
-            if (!act) continue;
-            if (m1 > len1) {          // list exhausted: undecided
-                act = false;
-                continue;
-            }
-            seen1 = m1 + KU;
-            LEnt nxt[KU];
-            load_step(l1 + m1 + KU, nxt);
+        Const<uint32_t> *p = as_const(reinterpret_cast<const uint32_t *>(l1));
+        Step<KU> cur;
+        load_step(p, cur);
+        for (;;) {
+            Step<KU> nxt;
+            load_step(p + 2 * (m1 + KU), nxt);
             float d[KU];
-            ln.xdist(cur, d);
-            float lo = inf_f();
+            xdist(cur, d);
+            float dmin = inf_f();
 #pragma unroll
             for (int u = 0; u < KU; ++u) {
-                d[u] = fmax_(d[u], cur[u].d);
-                lo = __builtin_fminf(lo, d[u]);
+                d[u] = fmax_(d[u], cur.d[u]);
+                dmin = __builtin_fminf(dmin, d[u]);
             }
-            if (lo < top[KMAX - 1]) {
+            // a distance not below the k-th leaves a lane's list as it is
+            if (cmp_mask(dmin < top[KMAX - 1])) {
 #pragma unroll
                 for (int u = 0; u < KU; ++u) topk_insert<KMAX>(top, d[u]);
             }
-            if (bucket_floor(cur[KU - 1].d) >= top[KMAX - 1]) {
-                decided = true;
-                act = false;
-                continue;
-            }
-#pragma unroll
-            for (int u = 0; u < KU; ++u) cur[u] = nxt[u];
+            seen1 += (int64_t)__builtin_popcountll(open) * KU;
+            open = livem & ~cmp_mask(bucket_floor(cur.d[KU - 1]) >= top[KMAX - 1]);
             m1 += KU;
+            if (__builtin_popcountll(open) <= coop || m1 > len1) break;
+            cur = nxt;
         }
     }
-    for (uint64_t rest = ballot(act); rest; rest &= rest - 1) {
-        const int o = lowest(rest);
-        const LEnt *pl = bcast(l1, o);
-        const int end = bcast(len1, o) + kListPad;
-        const float *xt = bcast(ln.xt, o);
-        const uint32_t cs = bcast(ln.cs, o), E = bcast(ln.E, o), eo = bcast(ln.e, o);
-        const int dxo = bcast(ln.dx, o);
-        float xq[DXM], pt[KMAX];
+    uint64_t dec = livem & ~open; // decided lanes
+    if (m1 <= len1) {             // (else the list is exhausted: the open lanes are undecided)
+        for (uint64_t rest = open; rest; rest &= rest - 1) {
+            const int o = lowest(rest);
+            const int end = len1 + kListPad;
+            float q[DXM], pt[KMAX];
 #pragma unroll
-        for (int c = 0; c < DXM; ++c) xq[c] = bcast(ln.xq[c], o);
+            for (int c = 0; c < DXM; ++c) q[c] = bcast(xq[c], o);
 #pragma unroll
-        for (int q = 0; q < KMAX; ++q) pt[q] = bcast(top[q], o);
-        bool dec = false;
-        int p = bcast(m1, o);
-        for (; p < end; p += 64 * kCoopU) {
-            // kCoopU entries per lane, all loads issued first
-            const int last = min(p + 64 * kCoopU - 1, end - 1);
-            const float stop = bucket_floor(pl[last].d);
-            LEnt en[kCoopU];
-#pragma unroll
-            for (int u = 0; u < kCoopU; ++u) {
-                const int idx = p + lane + 64 * u;
-                en[u] = pl[min(idx, end - 1)];
+            for (int t = 0; t < KMAX; ++t) pt[t] = bcast(top[t], o);
+            bool done = false;
+            int p = m1;
+            for (; p < end; p += 64) {
+                const int last = min(p + 63, end - 1);
+                const float stop = bucket_floor(l1[last].d);
+                const LEnt en = l1[min(p + lane, end - 1)];
+                float d = fmax_(coop_xdist(o, q, en.j), en.d);
+                if (p + lane >= end) d = inf_f();
+                for (uint64_t cand = ballot(d < pt[KMAX - 1]); cand; cand &= cand - 1)
+                    topk_insert<KMAX>(pt, bcast(d, lowest(cand)));
+                if (stop >= pt[KMAX - 1]) {
+                    done = true;
+                    p = last + 1;
+                    break;
+                }
             }
-            float d[kCoopU];
+            if (lane == o) {
 #pragma unroll
-            for (int u = 0; u < kCoopU; ++u) {
-                d[u] = fmax_(coop_xdist(xt, cs, E, eo, dxo, xq, en[u].j), en[u].d);
-                if (p + lane + 64 * u >= end) d[u] = inf_f();
+                for (int t = 0; t < KMAX; ++t) top[t] = pt[t];
             }
-#pragma unroll
-            for (int u = 0; u < kCoopU; ++u)
-                for (uint64_t cand = ballot(d[u] < pt[KMAX - 1]); cand; cand &= cand - 1)
-                    topk_insert<KMAX>(pt, bcast(d[u], lowest(cand)));
-            if (stop >= pt[KMAX - 1]) {
-                dec = true;
-                p = last + 1;
-                break;
-            }
-        }
-        if (lane == o) {
-#pragma unroll
-            for (int q = 0; q < KMAX; ++q) top[q] = pt[q];
-            decided = dec;
-            seen1 = min(p, end);
+            if (done) dec |= uint64_t(1) << o;
+            seen1 += min(p, end) - m1;
         }
     }
     const float eps = top[KMAX - 1];
 
-    // n_z, n_yz and n_xz from list 2 below eps (every row with d_z < eps, and
-    // so every row with d_yz < eps, is listed when eps <= its bound)
+    // n_yz: list 1 below eps
     int cxz = 0, cyz = 0, cz = 0;
-    const LEnt2 *l2 = S.l2 + (int64_t)i * S.s2;
-    const int len2 = S.len[2 * (int64_t)i + 1];
-    const bool noz = J.dz == 0;
-    const bool knn_decided = decided;
-    // a job of a set counted by ranks takes its counts from the rank-count
-    // kernel: this kernel hands it the radius (or the pair to the redo)
-    const bool ranked = J.er != nullptr;
-    act = live && decided && !noz && !ranked;
-    decided = ranked && knn_decided;
-    int m2 = 0;
     {
-        LEnt2 cur[KU];
-        load_step(l2, cur);
-        while (__builtin_popcountll(ballot(act)) > coop) {
-            if (!act) continue;
-            if (m2 > len2) {
-                act = false;
-                continue;
+        Const<uint32_t> *p = as_const(reinterpret_cast<const uint32_t *>(l1));
+        open = dec;
+        int m = 0;
+        Step<KU> cur;
+        load_step(p, cur);
+        while (__builtin_popcountll(open) > coop && m <= len1) {
+            Step<KU> nxt;
+            load_step(p + 2 * (m + KU), nxt);
+#pragma unroll
+            for (int u = 0; u < KU; ++u) cyz += cur.d[u] < eps;
+            open = dec & ~cmp_mask(bucket_floor(cur.d[KU - 1]) >= eps);
+            m += KU;
+            cur = nxt;
+        }
+        if (m <= len1)
+            for (uint64_t rest = open; rest; rest &= rest - 1) {
+                const int o = lowest(rest);
+                const int end = len1 + kListPad;
+                const float pe = bcast(eps, o);
+                int q = 0;
+                for (int c = m; c < end; c += 64) {
+                    const float stop = bucket_floor(l1[min(c + 63, end - 1)].d);
+                    const float d = l1[min(c + lane, end - 1)].d;
+                    q += __builtin_popcountll(ballot(c + lane < end && d < pe));
+                    if (stop >= pe) break;
+                }
+                if (lane == o) cyz += q;
             }
-            seen2 = m2 + KU;
-            LEnt2 nxt[KU];
-            load_step(l2 + m2 + KU, nxt);
-            float dx[KU];
-            ln.xdist(cur, dx);
+    }
+
+    // n_z and n_xz from list 2 below eps (every row with d_z < eps is listed
+    // when eps <= its bound); a job of a set counted by ranks takes them from
+    // the rank-count kernel
+    const bool noz = J->dz == 0, ranked = J->er != nullptr;
+    if (!noz && !ranked) {
+        const LEnt *l2 = S->l2 + (int64_t)i * S->s2;
+        const int len2 = as_const(S->len)[2 * (int64_t)i + 1];
+        Const<uint32_t> *p = as_const(reinterpret_cast<const uint32_t *>(l2));
+        const uint64_t want = dec;
+        open = want;
+        int m2 = 0;
+        Step<KU> cur;
+        load_step(p, cur);
+        while (__builtin_popcountll(open) > coop && m2 <= len2) {
+            Step<KU> nxt;
+            load_step(p + 2 * (m2 + KU), nxt);
+            float d[KU];
+            xdist(cur, d);
 #pragma unroll
             for (int u = 0; u < KU; ++u) {
-                cz += cur[u].dz < eps;
-                cyz += cur[u].dyz < eps;
-                cxz += fmax_(dx[u], cur[u].dz) < eps;
+                cz += cur.d[u] < eps;
+                cxz += fmax_(d[u], cur.d[u]) < eps;
             }
-            if (bucket_floor(cur[KU - 1].dz) >= eps) {
-                decided = true;
-                act = false;
-                continue;
-            }
-#pragma unroll
-            for (int u = 0; u < KU; ++u) cur[u] = nxt[u];
+            seen2 += (int64_t)__builtin_popcountll(open) * KU;
+            open = want & ~cmp_mask(bucket_floor(cur.d[KU - 1]) >= eps);
             m2 += KU;
+            cur = nxt;
         }
-    }
-    for (uint64_t rest = ballot(act); rest; rest &= rest - 1) {
-        const int o = lowest(rest);
-        const LEnt2 *pl = bcast(l2, o);
-        const int end = bcast(len2, o) + kListPad;
-        const float *xt = bcast(ln.xt, o);
-        const uint32_t cs = bcast(ln.cs, o), E = bcast(ln.E, o), eo = bcast(ln.e, o);
-        const int dxo = bcast(ln.dx, o);
-        const float pe = bcast(eps, o);
-        float xq[DXM];
+        dec = want & ~open;
+        if (m2 <= len2) {
+            for (uint64_t rest = open; rest; rest &= rest - 1) {
+                const int o = lowest(rest);
+                const int end = len2 + kListPad;
+                const float pe = bcast(eps, o);
+                float q[DXM];
 #pragma unroll
-        for (int c = 0; c < DXM; ++c) xq[c] = bcast(ln.xq[c], o);
-        int qz = 0, qyz = 0, qxz = 0;
-        bool dec = false;
-        int p = bcast(m2, o);
-        for (; p < end; p += 64 * kCoopU) {
-            const int last = min(p + 64 * kCoopU - 1, end - 1);
-            const float stop = bucket_floor(pl[last].dz);
-            LEnt2 en[kCoopU];
-#pragma unroll
-            for (int u = 0; u < kCoopU; ++u) en[u] = pl[min(p + lane + 64 * u, end - 1)];
-            float dxv[kCoopU];
-#pragma unroll
-            for (int u = 0; u < kCoopU; ++u) dxv[u] = coop_xdist(xt, cs, E, eo, dxo, xq, en[u].j);
-#pragma unroll
-            for (int u = 0; u < kCoopU; ++u) {
-                const bool in = p + lane + 64 * u < end;
-                qz += __builtin_popcountll(ballot(in && en[u].dz < pe));
-                qyz += __builtin_popcountll(ballot(in && en[u].dyz < pe));
-                qxz += __builtin_popcountll(ballot(in && fmax_(dxv[u], en[u].dz) < pe));
-            }
-            if (stop >= pe) {
-                dec = true;
-                p = last + 1;
-                break;
+                for (int c = 0; c < DXM; ++c) q[c] = bcast(xq[c], o);
+                int qz = 0, qxz = 0;
+                bool done = false;
+                int c = m2;
+                for (; c < end; c += 64) {
+                    const int last = min(c + 63, end - 1);
+                    const float stop = bucket_floor(l2[last].d);
+                    const LEnt en = l2[min(c + lane, end - 1)];
+                    const float dv = coop_xdist(o, q, en.j);
+                    const bool in = c + lane < end;
+                    qz += __builtin_popcountll(ballot(in && en.d < pe));
+                    qxz += __builtin_popcountll(ballot(in && fmax_(dv, en.d) < pe));
+                    if (stop >= pe) {
+                        done = true;
+                        c = last + 1;
+                        break;
+                    }
+                }
+                if (lane == o) {
+                    cz += qz;
+                    cxz += qxz;
+                }
+                if (done) dec |= uint64_t(1) << o;
+                seen2 += min(c, end) - m2;
             }
         }
-        if (lane == o) {
-            cz += qz;
-            cyz += qyz;
-            cxz += qxz;
-            decided = dec;
-            seen2 = min(p, end);
-        }
     }
-    if (noz && live && knn_decided) {
-        // Without Z: n_z is the number of rows outside the window; n_y comes
-        // from list 1 (its d is d_y, and every row with d_y < eps precedes the
-        // k-NN stop); n_x counts the rows j != i with |x_j - x_i| < eps.  The
-        // permuted values x_j run over the job's X column, so that count is
-        // the range of the sorted column around x_i: the s with
-        // -eps < fl(xs[s] - x_i) < eps (fl(. - x_i) is monotone), less row i
-        // itself and the rows of its Theiler window.
-        const int w = J.theiler;
+    const bool decided = (dec >> lane) & 1u;
+    if (noz && decided) {
+        // Without Z: n_z is the number of rows outside the window; n_x counts
+        // the rows j != i with |x_j - x_i| < eps.  The permuted values x_j run
+        // over the job's X column, so that count is the range of the sorted
+        // column around x_i: the s with -eps < fl(xs[s] - x_i) < eps
+        // (fl(. - x_i) is monotone), less row i itself and the rows of its
+        // Theiler window.
+        const int w = J->theiler;
         cz = n - 1 - min(i, w) - min(n - 1 - i, w);
-        for (int m = 0;; ++m) {
-            const float d = l1[m].d;
-            if (bucket_floor(d) >= eps) break;
-            cyz += d < eps;
+        const float xv = xq[0];
+        const float *xs = J->xs;
+        int lo2 = 0, hi2 = n;
+        while (lo2 < hi2) {
+            const int mid = (lo2 + hi2) >> 1;
+            if (gload(xs, mid) - xv > -eps) hi2 = mid; else lo2 = mid + 1;
         }
-        const float x = ln.xq[0];
-        const float *xs = J.xs;
-        int lo = 0, hi = n;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (gload(xs, mid) - x > -eps) hi = mid; else lo = mid + 1;
+        const int first = lo2;
+        hi2 = n;
+        while (lo2 < hi2) {
+            const int mid = (lo2 + hi2) >> 1;
+            if (gload(xs, mid) - xv >= eps) hi2 = mid; else lo2 = mid + 1;
         }
-        const int first = lo;
-        hi = n;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (gload(xs, mid) - x >= eps) hi = mid; else lo = mid + 1;
-        }
-        cxz = lo - first - (0.f < eps ? 1 : 0);
+        cxz = lo2 - first - (0.f < eps ? 1 : 0);
         for (int j = max(0, i - w); j <= min(n - 1, i + w); ++j)
-            if (j != i && absdiff(x, gload(ln.xt, (uint32_t)j * ln.E + ln.e)) < eps) --cxz;
-        decided = true;
+            if (j != i && absdiff(xv, xval(0, (uint32_t)j, loff)) < eps) --cxz;
     }
     if (live) {
-        if (ranked) {
-            J.er[(int64_t)e * n + i] = decided ? eps : -1.0f;
-        }
+        const int64_t at_e = (int64_t)e * n + i;
+        if (ranked) J->er[at_e] = decided ? eps : -1.0f;
         if (!decided) {
             const uint32_t pos = atomicAdd(&L.counters[0], 1u);
-            L.failq[pos] = ((uint64_t)jb << 40) | ((uint64_t)i * J.n_est + e);
-        } else if (!ranked) {
-            J.pk[(int64_t)e * n + i] = pack_counts(cxz, cyz, cz);
-            if (J.eps) J.eps[(int64_t)e * n + i] = eps;
-            if (J.cnt) {
-                J.cnt[((int64_t)e * 3 + 0) * n + i] = cxz;
-                J.cnt[((int64_t)e * 3 + 1) * n + i] = cyz;
-                J.cnt[((int64_t)e * 3 + 2) * n + i] = cz;
+            L.failq[pos] = ((uint64_t)jb << 40) | ((uint64_t)i * E + e);
+        } else {
+            // (of a ranked pair: n_yz, completed by the rank-count kernel)
+            J->pk[at_e] = pack_counts(cxz, cyz, cz);
+            if (!ranked && J->eps) J->eps[at_e] = eps;
+            if (!ranked && J->cnt) {
+                J->cnt[((int64_t)e * 3 + 0) * n + i] = cxz;
+                J->cnt[((int64_t)e * 3 + 1) * n + i] = cyz;
+                J->cnt[((int64_t)e * 3 + 2) * n + i] = cz;
             }
         }
-        if (L.stats) {
-            const int slot = (int)((g >> 6) & (kListStatSlots - 1));
+        if (L.stats && lane == 0) {
+            const int slot = (int)((b * kScanRows + wave) & (kListStatSlots - 1));
             unsigned long long *st =
                 reinterpret_cast<unsigned long long *>(L.counters + kListStatWord + slot * kListStatStride);
             atomicAdd(&st[0], (unsigned long long)seen1);
@@ -1340,7 +1240,6 @@ __global__ __launch_bounds__(kRankThreads) void list_rank_sort_kernel(const List
         S.zrank[i] = rank;
         S.zord[rank] = i;
         S.zs[rank] = zi;
-        S.yr[rank] = S.cols[0][i];
     }
 }
 
@@ -1374,9 +1273,10 @@ __global__ __launch_bounds__(kRankThreads) void list_rank_count_kernel(const Lis
     const int i = min(max(S.zord[rr], 0), n - 1);
     const float eps = J.er[(int64_t)e * n + i];
     const bool ok = r < n && eps >= 0.f;      // -1: the pair is in the redo queue
-    const float *zs = S.zs, *yr = S.yr;
+    const float *zs = S.zs;
     const float *xr = J.xr + (int64_t)e * dx * n;
-    const float zq = zs[rr], yq = yr[rr];
+    const float zq = zs[rr];
+    const uint64_t pk = J.pk[(int64_t)e * n + i];   // n_yz, from the scan
     float xq[DXM];
 #pragma unroll
     for (int c = 0; c < DXM; ++c) xq[c] = c < dx ? xr[(int64_t)c * n + rr] : 0.f;
@@ -1395,16 +1295,16 @@ __global__ __launch_bounds__(kRankThreads) void list_rank_count_kernel(const Lis
         }
         hi = a;
     }
-    int mx = 0, my = 0, mz = 0;
+    int mx = 0, mz = 0;
     int64_t ent = 0;
     for (uint64_t todo = ballot(ok); todo; todo &= todo - 1) {
         const int o = lowest(todo);
         const int plo = bcast(lo, o), phi = bcast(hi, o), pi = bcast(i, o);
-        const float pe = bcast(eps, o), py = bcast(yq, o);
+        const float pe = bcast(eps, o);
         float px[DXM];
 #pragma unroll
         for (int c = 0; c < DXM; ++c) px[c] = bcast(xq[c], o);
-        int cx = 0, cy = 0;
+        int cx = 0;
         // kRankU steps per iteration, their loads issued together (a pair's
         // steps would otherwise wait for their loads one after another): the
         // network-inference workload ran 3% faster than with one step per
@@ -1414,7 +1314,7 @@ __global__ __launch_bounds__(kRankThreads) void list_rank_count_kernel(const Lis
         for (int q = plo; q < phi; q += 64 * kRankU) {
             bool in[kRankU];
             uint32_t bo[kRankU];
-            float y[kRankU], x0[kRankU];
+            float x0[kRankU];
 #pragma unroll
             for (int u = 0; u < kRankU; ++u) {
                 const int m = q + 64 * u + lane;
@@ -1422,7 +1322,6 @@ __global__ __launch_bounds__(kRankThreads) void list_rank_count_kernel(const Lis
                 // byte offsets from the wave-uniform bases: the loads take
                 // no 64-bit address arithmetic
                 bo[u] = (uint32_t)(in[u] ? m : phi - 1) * 4u;
-                y[u] = gload_b(yr, bo[u]);
                 x0[u] = gload_b(xr, bo[u]);
             }
 #pragma unroll
@@ -1434,7 +1333,6 @@ __global__ __launch_bounds__(kRankThreads) void list_rank_count_kernel(const Lis
                 });
                 // the masks of single compares, combined by the scalar unit
                 const uint64_t inm = cmp_mask(in[u]);
-                cy += __builtin_popcountll(inm & cmp_mask(absdiff(y[u], py) < pe));
                 cx += __builtin_popcountll(inm & cmp_mask(d < pe));
             }
         }
@@ -1446,7 +1344,6 @@ __global__ __launch_bounds__(kRankThreads) void list_rank_count_kernel(const Lis
         if (J.theiler == 0) {
             const int own = pe > 0.f ? 1 : 0;
             cz -= own;
-            cy -= own;
             cx -= own;
         } else
         for (int j = w0 + lane; j - lane <= w1; j += 64) {
@@ -1459,17 +1356,16 @@ __global__ __launch_bounds__(kRankThreads) void list_rank_count_kernel(const Lis
                 d = fmax_(d, absdiff(xr[(int64_t)c * n + rj], px[c]));
             });
             cz -= __builtin_popcountll(ballot(inr));
-            cy -= __builtin_popcountll(ballot(inr && absdiff(yr[rj], py) < pe));
             cx -= __builtin_popcountll(ballot(inr && d < pe));
         }
         ent += phi - plo;
         if (lane == o) {
             mx = cx;
-            my = cy;
             mz = cz;
         }
     }
     if (ok) {
+        const int my = (int)((pk >> kPackBits) & kPackMask);
         J.pk[(int64_t)e * n + i] = pack_counts(mx, my, mz);
         if (J.eps) J.eps[(int64_t)e * n + i] = eps;
         if (J.cnt) {
@@ -1741,12 +1637,9 @@ __global__ __launch_bounds__(kBlock) void list_reduce_kernel(const ListLaunch L,
 }
 
 template <int KMAX, int DXM>
-void *scan_fn(int step, bool units) {
-    if (units)
-        return step == 4 ? reinterpret_cast<void *>(&list_scan_kernel<KMAX, DXM, 4, true>)
-                         : reinterpret_cast<void *>(&list_scan_kernel<KMAX, DXM, 8, true>);
-    return step == 4 ? reinterpret_cast<void *>(&list_scan_kernel<KMAX, DXM, 4, false>)
-                     : reinterpret_cast<void *>(&list_scan_kernel<KMAX, DXM, 8, false>);
+void *scan_fn(int step) {
+    return step == 4 ? reinterpret_cast<void *>(&list_scan_kernel<KMAX, DXM, 4>)
+                     : reinterpret_cast<void *>(&list_scan_kernel<KMAX, DXM, 8>);
 }
 
 }  // namespace
@@ -1799,18 +1692,17 @@ int launch_list_build(const ListLaunch &L, void *stream) {
 
 int launch_list_scan(const ListLaunch &L, void *stream) {
     if (L.lanes <= 0) return 0;
-    const int64_t blocks = L.grouped == 2 ? L.scan_blocks : (L.lanes + kBlock - 1) / kBlock;
     void *fn = nullptr;
     const bool wide = L.dxm > 1;
     const int st = L.scan_step;
-    const bool un = L.grouped == 2;
-    if (L.kmax == 4) fn = wide ? scan_fn<4, kMaxDx>(st, un) : scan_fn<4, 1>(st, un);
-    else if (L.kmax == 8) fn = wide ? scan_fn<8, kMaxDx>(st, un) : scan_fn<8, 1>(st, un);
-    else if (L.kmax == 16) fn = wide ? scan_fn<16, kMaxDx>(st, un) : scan_fn<16, 1>(st, un);
+    if (L.kmax == 4) fn = wide ? scan_fn<4, kMaxDx>(st) : scan_fn<4, 1>(st);
+    else if (L.kmax == 8) fn = wide ? scan_fn<8, kMaxDx>(st) : scan_fn<8, 1>(st);
+    else if (L.kmax == 16) fn = wide ? scan_fn<16, kMaxDx>(st) : scan_fn<16, 1>(st);
     else return -1;
     ListLaunch arg = L;
     void *args[] = {(void *)&arg};
-    return hipLaunchKernel(fn, dim3((unsigned)blocks), dim3(kBlock), args, 0, (hipStream_t)stream) == hipSuccess
+    return hipLaunchKernel(fn, dim3((unsigned)L.scan_blocks), dim3(kBlock), args, 0, (hipStream_t)stream) ==
+                   hipSuccess
                ? 0
                : -1;
 }

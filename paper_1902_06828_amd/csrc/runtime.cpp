@@ -953,7 +953,7 @@ static void list_caps(int dx, int dy, int dz, int n, int *m1, int *m2) {
         const int e = dx + dy - dz;
         *m1 = e >= 2 ? 8192 : e == 1 ? 4096 : e == 0 ? 2048 : 1024;
         while (*m1 > 1024 && (double)n * (std::min(n - 1, *m1) * (double)sizeof(LEnt) +
-                                          std::min(n - 1, 2 * *m1) * (double)sizeof(LEnt2)) > cap_bytes)
+                                          std::min(n - 1, 2 * *m1) * 12.0) > cap_bytes)
             *m1 /= 2;
         *m2 = 2 * *m1;
     }
@@ -990,43 +990,42 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
         dxm = std::max(dxm, sp.dx);
         n_keys += sp.n_est();
     }
-    // a launch of several jobs: the scan's units of (job, 64-estimate group),
-    // dealt to the XCDs in turn, when there are at least kUnitsPerXcd per XCD
-    // (fewer leave XCDs idle and tie each unit to one XCD's CUs: a served
-    // batch of two or three requests has six to nine); MTE_GROUPED_MANY=0:
-    // job-major lanes in the hardware order always
-    int64_t n_units_all = 0;
-    for (int j = 0; j < n_ljobs_; ++j) n_units_all += std::max(1, specs[j].n_est() / 64);
-    const bool units = n_ljobs_ > 1 && n_units_all >= (int64_t)kUnitsPerXcd * kXcds &&
-                       env_int("MTE_GROUPED_MANY", 1) != 0;
-    std::vector<int64_t> unit_info, unit_blocks, xcd_off;
-    int unit_t = 0;
-    int64_t scan_blocks = 0;
-    if (units) {
-        for (int j = 0; j < n_ljobs_; ++j) {
-            const JobSpec &sp = specs[j];
-            const int ng = std::max(1, sp.n_est() / 64);
-            for (int grp = 0; grp < ng; ++grp) {
-                const int eg = grp == ng - 1 ? sp.n_est() - 64 * grp : 64;
-                unit_info.push_back((int64_t)j << 32 | grp);
-                unit_blocks.push_back(((int64_t)sp.n * eg + kBlock - 1) / kBlock);
+    // scan units: every job's groups, cut into row ranges and dealt to the
+    // XCDs in turn.  With few groups a group is cut so that the units divide
+    // evenly among the XCDs (C2's 4 groups: halves, so an XCD's L2 holds one
+    // group's columns); MTE_GROUPED=0 and MTE_GROUPED_MANY=0 cut every group
+    // into one range per XCD instead
+    int n_groups_all = 0;
+    for (int j = 0; j < n_ljobs_; ++j) n_groups_all += scan_groups(specs[j].n_est());
+    const bool dealt = n_ljobs_ == 1 ? env_int("MTE_GROUPED", tc.grouped != 0 ? 1 : 0) != 0
+                                     : env_int("MTE_GROUPED_MANY", 1) != 0;
+    int cuts = kXcds;
+    if (dealt && n_groups_all >= kUnitsPerXcd * kXcds) cuts = 1;
+    else if (dealt)
+        while (cuts > 1 && n_groups_all * (cuts / 2) % kXcds == 0) cuts /= 2;
+    std::vector<ScanUnit> units;
+    for (int j = 0; j < n_ljobs_; ++j) {
+        const JobSpec &sp = specs[j];
+        for (int g = 0; g < scan_groups(sp.n_est()); ++g)
+            for (int q = 0; q < cuts; ++q) {
+                const int r0 = (int)((int64_t)sp.n * q / cuts), r1 = (int)((int64_t)sp.n * (q + 1) / cuts);
+                units.push_back(ScanUnit{j, g, r0, r1 - r0});
             }
-        }
-        const int nu = (int)unit_info.size();
-        unit_t = (nu + kXcds - 1) / kXcds;
-        xcd_off.assign((size_t)kXcds * (unit_t + 1), 0);
-        for (int x = 0; x < kXcds; ++x) {
-            int64_t acc = 0;
-            for (int t = 0; t < unit_t; ++t) {
-                xcd_off[(size_t)x * (unit_t + 1) + t] = acc;
-                const int u = x + t * kXcds;
-                if (u < nu) acc += unit_blocks[u];
-            }
-            xcd_off[(size_t)x * (unit_t + 1) + unit_t] = acc;
-            scan_blocks = std::max(scan_blocks, acc);
-        }
-        scan_blocks *= kXcds;
     }
+    const int nu = (int)units.size(), unit_t = (nu + kXcds - 1) / kXcds;
+    std::vector<int64_t> xcd_off((size_t)kXcds * (unit_t + 1), 0);
+    int64_t scan_blocks = 0;
+    for (int x = 0; x < kXcds; ++x) {
+        int64_t acc = 0;
+        for (int t = 0; t < unit_t; ++t) {
+            xcd_off[(size_t)x * (unit_t + 1) + t] = acc;
+            const int u = x + t * kXcds;
+            if (u < nu) acc += (units[u].nrows + kScanRows - 1) / kScanRows;
+        }
+        xcd_off[(size_t)x * (unit_t + 1) + unit_t] = acc;
+        scan_blocks = std::max(scan_blocks, acc);
+    }
+    scan_blocks *= kXcds;
     // scratch layout: per set its lists and Y,Z copy; per job xt, xp, the
     // packed counts and the chunk sums; then the queue
     size_t bytes = 0;
@@ -1072,7 +1071,7 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
         o_l1[t] = bytes;
         bytes = align_up(bytes + sizeof(LEnt) * ((size_t)sp.n * S.s1 + kListPad), 256);
         o_l2[t] = bytes;
-        bytes = align_up(bytes + sizeof(LEnt2) * ((size_t)sp.n * S.s2 + kListPad), 256);
+        bytes = align_up(bytes + sizeof(LEnt) * ((size_t)sp.n * S.s2 + kListPad), 256);
         o_len[t] = bytes;
         bytes = align_up(bytes + sizeof(int32_t) * 2 * (size_t)sp.n, 256);
         o_bound[t] = bytes;
@@ -1086,10 +1085,10 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
             o_order[t] = bytes;
             bytes = align_up(bytes + sizeof(int32_t) * (size_t)sp.n, 256);
         }
-        // rank arrays: zs, zord, zrank, yr (n words each)
+        // rank arrays: zs, zord, zrank (n words each)
         if (ranked[t]) {
             o_rank[t] = bytes;
-            bytes = align_up(bytes + 4 * sizeof(float) * (size_t)sp.n, 256);
+            bytes = align_up(bytes + 3 * sizeof(float) * (size_t)sp.n, 256);
         }
     }
     struct Off { size_t xt, xp, pk, xs, chunk, xr, er; };
@@ -1099,7 +1098,7 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
         const JobSpec &sp = specs[j];
         const size_t pairs = (size_t)sp.n * sp.n_est();
         offs[j].xt = bytes;
-        bytes = align_up(bytes + sizeof(float) * pairs * sp.dx, 256);
+        bytes = align_up(bytes + sizeof(float) * (size_t)sp.n * kScanLanes * scan_groups(sp.n_est()) * sp.dx, 256);
         offs[j].xp = bytes;
         bytes = align_up(bytes + sizeof(float) * pairs * sp.dx, 256);
         rank_off[j + 1] = rank_off[j];
@@ -1123,10 +1122,10 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     const size_t t_jobs = align_up(sizeof(Job) * n_ljobs_, 256);
     const size_t t_sets = align_up(sizeof(ListSet) * n_sets, 256);
     const size_t t_keys = align_up(sizeof(EstKey) * (size_t)n_keys, 256);
-    const size_t t_offs = align_up(sizeof(int64_t) * (5 * (size_t)(n_ljobs_ + 1) + 2 * ((size_t)n_sets + 1) +
-                                                      xcd_off.size() + unit_info.size()),
-                                   256);
-    const size_t tbytes = t_jobs + t_sets + t_keys + t_offs;
+    const size_t t_offs = align_up(
+        sizeof(int64_t) * (5 * (size_t)(n_ljobs_ + 1) + 2 * ((size_t)n_sets + 1) + xcd_off.size()), 256);
+    const size_t t_units = align_up(sizeof(ScanUnit) * units.size(), 256);
+    const size_t tbytes = t_jobs + t_sets + t_keys + t_offs + t_units;
     if (measure) {
         *measure += bytes + sizeof(uint32_t) * kListCounterWords + tbytes;
         return MTE_OK;
@@ -1138,7 +1137,7 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     for (int t = 0; t < n_sets; ++t) {
         ListSet &S = sets[t];
         S.l1 = reinterpret_cast<LEnt *>(sb + o_l1[t]);
-        S.l2 = reinterpret_cast<LEnt2 *>(sb + o_l2[t]);
+        S.l2 = reinterpret_cast<LEnt *>(sb + o_l2[t]);
         S.len = reinterpret_cast<int32_t *>(sb + o_len[t]);
         S.bound = reinterpret_cast<float *>(sb + o_bound[t]);
         S.zy = reinterpret_cast<float *>(sb + o_zy[t]);
@@ -1148,7 +1147,6 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
             S.zs = reinterpret_cast<float *>(sb + o_rank[t]);
             S.zord = reinterpret_cast<int32_t *>(sb + o_rank[t] + nb);
             S.zrank = reinterpret_cast<int32_t *>(sb + o_rank[t] + 2 * nb);
-            S.yr = reinterpret_cast<float *>(sb + o_rank[t] + 3 * nb);
         }
     }
     // build blocks: kBuildRows rows each with packed 16-bit histograms when
@@ -1224,9 +1222,9 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     std::memcpy(oh + 3 * nj1 + (n_sets + 1), build_off.data(), sizeof(int64_t) * (n_sets + 1));
     std::memcpy(oh + 3 * nj1 + 2 * (n_sets + 1), rank_off.data(), sizeof(int64_t) * nj1);
     const size_t o_units = 4 * nj1 + 2 * ((size_t)n_sets + 1);
-    if (!xcd_off.empty()) std::memcpy(oh + o_units, xcd_off.data(), sizeof(int64_t) * xcd_off.size());
-    if (!unit_info.empty())
-        std::memcpy(oh + o_units + xcd_off.size(), unit_info.data(), sizeof(int64_t) * unit_info.size());
+    std::memcpy(oh + o_units, xcd_off.data(), sizeof(int64_t) * xcd_off.size());
+    const size_t units_at = t_jobs + t_sets + t_keys + t_offs;
+    std::memcpy(hs + units_at, units.data(), sizeof(ScanUnit) * units.size());
     ljobs_dev_ = reinterpret_cast<Job *>(tb);
     lblk_off_ = od + 2 * nj1;
     lpermute_blocks_ = blk_off[n_ljobs_];
@@ -1258,11 +1256,10 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     L.sortx = 0;
     for (const JobSpec &sp : specs) L.sortx |= sp.dz == 0;
     L.coop_lanes = env_int("MTE_COOP_LANES", tc.coop_lanes > 0 ? tc.coop_lanes : kCoopLanes);
-    L.grouped = units ? 2 : (n_ljobs_ == 1 && env_int("MTE_GROUPED", tc.grouped != 0 ? 1 : 0) != 0 ? 1 : 0);
-    L.xcd_off = units ? od + o_units : nullptr;
-    L.unit_info = units ? od + o_units + xcd_off.size() : nullptr;
+    L.grouped = dealt ? 1 : 0;
+    L.xcd_off = od + o_units;
+    L.units = reinterpret_cast<const ScanUnit *>(tb + units_at);
     L.unit_t = unit_t;
-    L.n_units = (int)unit_info.size();
     L.scan_blocks = scan_blocks;
     L.scan_step = env_int("MTE_SCAN_STEP", tc.scan_step > 0 ? tc.scan_step : (n_ljobs_ == 1 ? 8 : 4)) == 4 ? 4 : 8;
     perm_cu_ = std::max(0, env_int("MTE_PERMUTE_BLOCKS_PER_CU", tc.perm_cu > 0 ? tc.perm_cu : kPermuteBlocksPerCu));
