@@ -106,7 +106,7 @@ struct LEnt {
     int32_t j;                    // row
 };
 
-constexpr int kListPad = 8;                   // sentinel entries after each row's list
+constexpr int kListPad = 16;                  // sentinel entries after each row's list
 
 struct ListSet {
     const float *cols[kMaxDy + kMaxDz];   // Y columns, then Z columns
@@ -168,7 +168,6 @@ MTE_HD inline int scan_group_of(int e, int n_est) {
 struct ScanUnit {
     int32_t job, group, row0, nrows;
 };
-constexpr int kScanRows = kWaves;             // rows per scan block, one wave each
 
 // One launch of the list path over `n_jobs` jobs (all with dz > 0).
 struct ListLaunch {

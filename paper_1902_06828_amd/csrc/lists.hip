@@ -840,14 +840,14 @@ __global__ __launch_bounds__(kSortThreads) void list_order_kernel(const ListLaun
 // key distance lies in the bucket that starts at the row's bound: the bound
 // plus one unit in the last place (+inf for a whole list: nothing left out,
 // or only rows at +inf).
-// A step of kU <= kListPad entries that starts at or before the list's end
-// then needs no bounds checks, and the last step of a list always ends on a
-// sentinel, whose bucket-floor test (floor = bound >= radius) is exactly the
+// A step of kU entries that starts at or before the list's end, and the step
+// after it, whose X values are loaded ahead, then need no bounds checks, and
+// the last step of a list always ends on a sentinel, whose bucket-floor test (floor = bound >= radius) is exactly the
 // condition under which the list decides the pair.  A sentinel that enters
 // the k-NN list (bound + 1 ulp < k-th distance) leaves a radius above the
 // bound, i.e. an undecided pair, as it should.
 constexpr int kU = 8;   // the largest step
-static_assert(kU <= kListPad, "a step must stay within the sentinels");
+static_assert(2 * kU <= kListPad, "a step and the next must stay within the sentinels");
 
 // Read-only memory addressed through the constant address space: a load from
 // a wave-uniform address is then a scalar load.
@@ -870,6 +870,16 @@ __device__ __forceinline__ void load_step(Const<uint32_t> *l, Step<NU> &s) {
         s.d[u] = __uint_as_float(l[2 * u]);
         s.j[u] = l[2 * u + 1];
     }
+}
+
+// The step's values are needed here: keeps the compiler from sinking a step's
+// load to the end of the loop that loads it ahead.
+template <int NU>
+__device__ __forceinline__ void pin_step(const Step<NU> &s) {
+#pragma unroll
+    for (int u = 0; u < NU; u += 4)
+        asm volatile("" ::"s"(s.d[u]), "s"(s.j[u]), "s"(s.d[u + 1]), "s"(s.j[u + 1]), "s"(s.d[u + 2]), "s"(s.j[u + 2]),
+                     "s"(s.d[u + 3]), "s"(s.j[u + 3]));
 }
 
 // Wave-uniform helpers.
@@ -895,22 +905,29 @@ __device__ __forceinline__ int bcast(int v, int o) { return __builtin_amdgcn_rea
 // 11.4 -> 9.8 ms; network of 8 targets, T = 3000 101 -> 86 ms; without Z
 // (n_y was counted entry by entry in each lane) 3.07 -> 1.50 ms.
 //
+// A block is one wave: the waves of a block give their slots back together,
+// and the slowest of four kept 4.6 of the 7 waves a SIMD could hold (5.6 with
+// one).  The next step's X values and the entries of the step after it are
+// loaded while a step is worked on.  The scan alone at N = 10^4, 201
+// estimates: 299 -> 262 us, N = 30011 915 -> 783 us, the served mix 1.53 ->
+// 1.30 ms a launch; a third of the cycles are vector instructions, the rest
+// X gathers, and about 70 us at the end belong to the few longest waves.
+//
 // The 64 lanes stop at very different list positions (a few estimates of a
 // row have radii far above the others).  Each phase runs with all lanes while
 // more than `coop` of them still need entries (a lane past its own stop reads
 // on without effect: no later entry is below its radius), then finishes the
-// remaining lanes one after the other with all 64 lanes, 64 list entries per
-// step.  Entries, distances and tests are the same, so the results are too.
+// remaining lanes together, 64 list entries per step, one per lane, for each
+// of them in turn.  Entries, distances and tests are the same, so the results are too.
 //
 // Phases: the k-NN radius over list 1; n_yz, the entries of list 1 below the
 // radius (every such entry precedes the stop, so no X is gathered); n_z and
 // n_xz over list 2.  Jobs counted by ranks leave after n_yz, jobs without Z
 // take n_x from the sorted X column.
 template <int KMAX, int DXM, int KU>
-__global__ __launch_bounds__(kBlock) void list_scan_kernel(const ListLaunch L) {
-    static_assert(KU <= kU, "a step must stay within the sentinels");
-    const int lane = tid_x() & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid_x() >> 6);
+__global__ __launch_bounds__(kScanLanes) void list_scan_kernel(const ListLaunch L) {
+    static_assert(KU <= kU, "two steps must stay within the sentinels");
+    const int lane = tid_x();
     // XCD x's k-th block: the last of x's units whose first block is <= k
     const int64_t b = bid_x();
     const int x = (int)(b % kXcds);
@@ -923,8 +940,7 @@ __global__ __launch_bounds__(kBlock) void list_scan_kernel(const ListLaunch L) {
         if (xo[mid] <= k) lo = mid; else hi = mid - 1;
     }
     Const<ScanUnit> *U = as_const(L.units) + (x + lo * kXcds);
-    const int at = (int)(k - xo[lo]) * kScanRows + wave;
-    if (at >= U->nrows) return;
+    const int at = (int)(k - xo[lo]);
     const int jb = U->job, grp = U->group, il = U->row0 + at;
     Const<Job> *J = as_const(L.jobs) + jb;
     Const<ListSet> *S = as_const(L.sets) + J->set;
@@ -935,6 +951,7 @@ __global__ __launch_bounds__(kBlock) void list_scan_kernel(const ListLaunch L) {
     const int e = e0 + min(lane, ne - 1);
     const uint64_t livem = ballot(live);
     const int coop = L.coop_lanes;
+    const LEnt *l1 = S->l1 + (int64_t)i * S->s1, *l2 = S->l2 + (int64_t)i * S->s2;
 
     // X of row j under this lane's estimate: group column + 64 j + lane
     const int64_t cs = (int64_t)scan_groups(E) * n * kScanLanes;
@@ -948,28 +965,32 @@ __global__ __launch_bounds__(kBlock) void list_scan_kernel(const ListLaunch L) {
         constexpr int c = decltype(cc)::value;
         xq[c] = xval(c, (uint32_t)i, loff);
     });
-    // max-norm over the X columns between the lane's row and a step's rows
-    auto xdist = [&](const Step<KU> &s, float (&d)[KU]) {
-        float v[KU];
+    // the X values of a step's rows (all loads issued before any is used; the
+    // first column of the next step is loaded while this one is worked on)
+    auto gather = [&](const Step<KU> &s, float (&v)[KU]) {
 #pragma unroll
         for (int u = 0; u < KU; ++u) v[u] = xval(0, s.j[u], loff);
+    };
+    // max-norm over the X columns between the lane's row and a step's rows
+    auto xdist = [&](const Step<KU> &s, const float (&v0)[KU], float (&d)[KU]) {
 #pragma unroll
-        for (int u = 0; u < KU; ++u) d[u] = absdiff(xq[0], v[u]);
+        for (int u = 0; u < KU; ++u) d[u] = absdiff(xq[0], v0[u]);
         Unroll<1, DXM>::upto(dx, [&](auto cc) {
             constexpr int c = decltype(cc)::value;
+            float v[KU];
 #pragma unroll
             for (int u = 0; u < KU; ++u) v[u] = xval(c, s.j[u], loff);
 #pragma unroll
             for (int u = 0; u < KU; ++u) d[u] = fmax_(d[u], absdiff(xq[c], v[u]));
         });
     };
-    // the same for one entry per lane under lane o's estimate
-    auto coop_xdist = [&](int o, const float (&q)[DXM], int32_t j) {
+    // the same between row i and one row per lane under lane o's estimate
+    auto coop_xdist = [&](int o, uint32_t j) {
         const uint32_t oo = (uint32_t)o * 4u;
-        float d = absdiff(q[0], xval(0, (uint32_t)j, oo));
+        float d = absdiff(bcast(xq[0], o), xval(0, j, oo));
         Unroll<1, DXM>::upto(dx, [&](auto cc) {
             constexpr int c = decltype(cc)::value;
-            d = fmax_(d, absdiff(q[c], xval(c, (uint32_t)j, oo)));
+            d = fmax_(d, absdiff(bcast(xq[c], o), xval(c, j, oo)));
         });
         return d;
     };
@@ -979,20 +1000,25 @@ __global__ __launch_bounds__(kBlock) void list_scan_kernel(const ListLaunch L) {
     const int pad_front = KMAX - J->k;
 #pragma unroll
     for (int m = 0; m < KMAX; ++m) top[m] = m < pad_front ? -inf_f() : inf_f();
-    const LEnt *l1 = S->l1 + (int64_t)i * S->s1;
     const int len1 = as_const(S->len)[2 * (int64_t)i];
     uint64_t open = livem;        // lanes whose radius needs later entries
     int64_t seen1 = 0, seen2 = 0; // list entries read by the pairs (statistics)
     int m1 = 0;
     {
         Const<uint32_t> *p = as_const(reinterpret_cast<const uint32_t *>(l1));
-        Step<KU> cur;
+        Step<KU> cur, nxt;
+        float v[KU];
         load_step(p, cur);
+        load_step(p + 2 * KU, nxt);
+        gather(cur, v);
         for (;;) {
-            Step<KU> nxt;
-            load_step(p + 2 * (m1 + KU), nxt);
+            float vn[KU];
+            Step<KU> nxt2;
+            gather(nxt, vn);
+            load_step(p + 2 * (m1 + 2 * KU), nxt2);
+            __builtin_amdgcn_sched_barrier(0);
             float d[KU];
-            xdist(cur, d);
+            xdist(cur, v, d);
             float dmin = inf_f();
 #pragma unroll
             for (int u = 0; u < KU; ++u) {
@@ -1007,42 +1033,37 @@ __global__ __launch_bounds__(kBlock) void list_scan_kernel(const ListLaunch L) {
             seen1 += (int64_t)__builtin_popcountll(open) * KU;
             open = livem & ~cmp_mask(bucket_floor(cur.d[KU - 1]) >= top[KMAX - 1]);
             m1 += KU;
+            pin_step(nxt2);
             if (__builtin_popcountll(open) <= coop || m1 > len1) break;
             cur = nxt;
+            nxt = nxt2;
+#pragma unroll
+            for (int u = 0; u < KU; ++u) v[u] = vn[u];
         }
     }
     uint64_t dec = livem & ~open; // decided lanes
-    if (m1 <= len1) {             // (else the list is exhausted: the open lanes are undecided)
-        for (uint64_t rest = open; rest; rest &= rest - 1) {
-            const int o = lowest(rest);
-            const int end = len1 + kListPad;
-            float q[DXM], pt[KMAX];
-#pragma unroll
-            for (int c = 0; c < DXM; ++c) q[c] = bcast(xq[c], o);
-#pragma unroll
-            for (int t = 0; t < KMAX; ++t) pt[t] = bcast(top[t], o);
-            bool done = false;
-            int p = m1;
-            for (; p < end; p += 64) {
-                const int last = min(p + 63, end - 1);
-                const float stop = bucket_floor(l1[last].d);
-                const LEnt en = l1[min(p + lane, end - 1)];
-                float d = fmax_(coop_xdist(o, q, en.j), en.d);
+    if (open && m1 <= len1) {     // (else the list is exhausted: the open lanes are undecided)
+        const int end = len1 + kListPad;
+        // the lanes share each chunk's entries; the next chunk's are loaded ahead
+        LEnt nxt = l1[min(m1 + lane, end - 1)];
+        for (int p = m1; open && p < end; p += 64) {
+            const LEnt en = nxt;
+            nxt = l1[min(p + 64 + lane, end - 1)];
+            const float stop = bucket_floor(bcast(en.d, 63));
+            for (uint64_t rest = open; rest; rest &= rest - 1) {
+                const int o = lowest(rest);
+                float d = fmax_(coop_xdist(o, (uint32_t)en.j), en.d);
                 if (p + lane >= end) d = inf_f();
-                for (uint64_t cand = ballot(d < pt[KMAX - 1]); cand; cand &= cand - 1)
-                    topk_insert<KMAX>(pt, bcast(d, lowest(cand)));
-                if (stop >= pt[KMAX - 1]) {
-                    done = true;
-                    p = last + 1;
-                    break;
+                // +inf leaves the other lanes' lists as they are
+                for (uint64_t cand = cmp_mask(d < bcast(top[KMAX - 1], o)); cand; cand &= cand - 1) {
+                    const float dv = bcast(d, lowest(cand));
+                    topk_insert<KMAX>(top, lane == o ? dv : inf_f());
                 }
+                seen1 += min(64, end - p);
             }
-            if (lane == o) {
-#pragma unroll
-                for (int t = 0; t < KMAX; ++t) top[t] = pt[t];
-            }
-            if (done) dec |= uint64_t(1) << o;
-            seen1 += min(p, end) - m1;
+            const uint64_t done = open & cmp_mask(stop >= top[KMAX - 1]);
+            dec |= done;
+            open &= ~done;
         }
     }
     const float eps = top[KMAX - 1];
@@ -1058,26 +1079,28 @@ __global__ __launch_bounds__(kBlock) void list_scan_kernel(const ListLaunch L) {
         while (__builtin_popcountll(open) > coop && m <= len1) {
             Step<KU> nxt;
             load_step(p + 2 * (m + KU), nxt);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int u = 0; u < KU; ++u) cyz += cur.d[u] < eps;
             open = dec & ~cmp_mask(bucket_floor(cur.d[KU - 1]) >= eps);
             m += KU;
+            pin_step(nxt);
             cur = nxt;
         }
-        if (m <= len1)
+        const int end = len1 + kListPad;
+        float nd = open ? l1[min(m + lane, end - 1)].d : 0.f;
+        for (int c = m; open && c < end; c += 64) {
+            const float d = nd;
+            nd = l1[min(c + 64 + lane, end - 1)].d;
+            const float stop = bucket_floor(bcast(d, 63));
+            const uint64_t in = cmp_mask(c + lane < end);
             for (uint64_t rest = open; rest; rest &= rest - 1) {
                 const int o = lowest(rest);
-                const int end = len1 + kListPad;
-                const float pe = bcast(eps, o);
-                int q = 0;
-                for (int c = m; c < end; c += 64) {
-                    const float stop = bucket_floor(l1[min(c + 63, end - 1)].d);
-                    const float d = l1[min(c + lane, end - 1)].d;
-                    q += __builtin_popcountll(ballot(c + lane < end && d < pe));
-                    if (stop >= pe) break;
-                }
-                if (lane == o) cyz += q;
+                const int q = __builtin_popcountll(in & cmp_mask(d < bcast(eps, o)));
+                cyz += lane == o ? q : 0;
             }
+            open &= ~cmp_mask(stop >= eps);
+        }
     }
 
     // n_z and n_xz from list 2 below eps (every row with d_z < eps is listed
@@ -1085,19 +1108,24 @@ __global__ __launch_bounds__(kBlock) void list_scan_kernel(const ListLaunch L) {
     // the rank-count kernel
     const bool noz = J->dz == 0, ranked = J->er != nullptr;
     if (!noz && !ranked) {
-        const LEnt *l2 = S->l2 + (int64_t)i * S->s2;
         const int len2 = as_const(S->len)[2 * (int64_t)i + 1];
         Const<uint32_t> *p = as_const(reinterpret_cast<const uint32_t *>(l2));
         const uint64_t want = dec;
         open = want;
         int m2 = 0;
-        Step<KU> cur;
+        Step<KU> cur, nxt;
+        float v[KU];
         load_step(p, cur);
+        load_step(p + 2 * KU, nxt);
+        gather(cur, v);
         while (__builtin_popcountll(open) > coop && m2 <= len2) {
-            Step<KU> nxt;
-            load_step(p + 2 * (m2 + KU), nxt);
+            float vn[KU];
+            Step<KU> nxt2;
+            gather(nxt, vn);
+            load_step(p + 2 * (m2 + 2 * KU), nxt2);
+            __builtin_amdgcn_sched_barrier(0);
             float d[KU];
-            xdist(cur, d);
+            xdist(cur, v, d);
 #pragma unroll
             for (int u = 0; u < KU; ++u) {
                 cz += cur.d[u] < eps;
@@ -1106,40 +1134,34 @@ __global__ __launch_bounds__(kBlock) void list_scan_kernel(const ListLaunch L) {
             seen2 += (int64_t)__builtin_popcountll(open) * KU;
             open = want & ~cmp_mask(bucket_floor(cur.d[KU - 1]) >= eps);
             m2 += KU;
+            pin_step(nxt2);
             cur = nxt;
+            nxt = nxt2;
+#pragma unroll
+            for (int u = 0; u < KU; ++u) v[u] = vn[u];
         }
         dec = want & ~open;
-        if (m2 <= len2) {
-            for (uint64_t rest = open; rest; rest &= rest - 1) {
-                const int o = lowest(rest);
-                const int end = len2 + kListPad;
-                const float pe = bcast(eps, o);
-                float q[DXM];
-#pragma unroll
-                for (int c = 0; c < DXM; ++c) q[c] = bcast(xq[c], o);
-                int qz = 0, qxz = 0;
-                bool done = false;
-                int c = m2;
-                for (; c < end; c += 64) {
-                    const int last = min(c + 63, end - 1);
-                    const float stop = bucket_floor(l2[last].d);
-                    const LEnt en = l2[min(c + lane, end - 1)];
-                    const float dv = coop_xdist(o, q, en.j);
-                    const bool in = c + lane < end;
-                    qz += __builtin_popcountll(ballot(in && en.d < pe));
-                    qxz += __builtin_popcountll(ballot(in && fmax_(dv, en.d) < pe));
-                    if (stop >= pe) {
-                        done = true;
-                        c = last + 1;
-                        break;
-                    }
+        if (open && m2 <= len2) {
+            const int end = len2 + kListPad;
+            LEnt nx = l2[min(m2 + lane, end - 1)];
+            for (int c = m2; open && c < end; c += 64) {
+                const LEnt en = nx;
+                nx = l2[min(c + 64 + lane, end - 1)];
+                const float stop = bucket_floor(bcast(en.d, 63));
+                const uint64_t in = cmp_mask(c + lane < end);
+                for (uint64_t rest = open; rest; rest &= rest - 1) {
+                    const int o = lowest(rest);
+                    const float pe = bcast(eps, o);
+                    const float dv = coop_xdist(o, (uint32_t)en.j);
+                    const int qz = __builtin_popcountll(in & cmp_mask(en.d < pe));
+                    const int qxz = __builtin_popcountll(in & cmp_mask(fmax_(dv, en.d) < pe));
+                    cz += lane == o ? qz : 0;
+                    cxz += lane == o ? qxz : 0;
+                    seen2 += min(64, end - c);
                 }
-                if (lane == o) {
-                    cz += qz;
-                    cxz += qxz;
-                }
-                if (done) dec |= uint64_t(1) << o;
-                seen2 += min(c, end) - m2;
+                const uint64_t done = open & cmp_mask(stop >= eps);
+                dec |= done;
+                open &= ~done;
             }
         }
     }
@@ -1187,7 +1209,7 @@ __global__ __launch_bounds__(kBlock) void list_scan_kernel(const ListLaunch L) {
             }
         }
         if (L.stats && lane == 0) {
-            const int slot = (int)((b * kScanRows + wave) & (kListStatSlots - 1));
+            const int slot = (int)(b & (kListStatSlots - 1));
             unsigned long long *st =
                 reinterpret_cast<unsigned long long *>(L.counters + kListStatWord + slot * kListStatStride);
             atomicAdd(&st[0], (unsigned long long)seen1);
@@ -1701,7 +1723,7 @@ int launch_list_scan(const ListLaunch &L, void *stream) {
     else return -1;
     ListLaunch arg = L;
     void *args[] = {(void *)&arg};
-    return hipLaunchKernel(fn, dim3((unsigned)L.scan_blocks), dim3(kBlock), args, 0, (hipStream_t)stream) ==
+    return hipLaunchKernel(fn, dim3((unsigned)L.scan_blocks), dim3(kScanLanes), args, 0, (hipStream_t)stream) ==
                    hipSuccess
                ? 0
                : -1;

@@ -1020,7 +1020,7 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
         for (int t = 0; t < unit_t; ++t) {
             xcd_off[(size_t)x * (unit_t + 1) + t] = acc;
             const int u = x + t * kXcds;
-            if (u < nu) acc += (units[u].nrows + kScanRows - 1) / kScanRows;
+            if (u < nu) acc += units[u].nrows;      // one wave, one block per row
         }
         xcd_off[(size_t)x * (unit_t + 1) + unit_t] = acc;
         scan_blocks = std::max(scan_blocks, acc);
