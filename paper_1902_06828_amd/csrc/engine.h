@@ -70,20 +70,26 @@ struct Job {
     int theiler;                  // Theiler window w: pairs with |i - j| <= w are left out
     int reps;                     // replications R (rows: R blocks of n/R, replication-major)
     int rep_shuffle;              // surrogates shuffle the replication order (else rows within each)
-    // list path without Z (dz = 0, dx = 1): the job's X column sorted
-    // ascending (n floats), for the n_x range counts; null otherwise
+    // list path without Z (dz = 0, dx = 1) and jobs counted in a wavelet
+    // matrix (xw): the job's X column sorted ascending (n floats); null
+    // otherwise
     float *xs;
     // list path: each (row, estimate)'s counts in one word,
     // n_xz | n_yz << kPackBits | n_z << 2 kPackBits ([n_est][n])
     uint64_t *pk;
     // list path with one Z column (rank counts, see ListSet::zs): the set's
     // rank of each row, the permuted X in rank order, estimate-major
-    // (xr[e][c][r] = X_c[pi_e(zord[r])], [n_est][dx][n]), and each pair's
-    // radius from the k-NN scan (er[e][i], -1 for a pair left to the
-    // all-rows redo); null otherwise
+    // (xr[e][c][r] = X_c[pi_e(zord[r])], [n_est][dx][n]), or, with one X column
+    // and no Theiler window, the rank of each row of the X column (xrank) and
+    // each row's source row (xw[e][i] = pi_e(i), [n_est][n], followed by
+    // [n_est][n] words for the ranks in rank order), and each pair's radius (low word, -1
+    // for a pair left to the all-rows redo) and n_yz from the scan, by rank
+    // (er[e][r]); null otherwise
     const int32_t *zrank;
     float *xr;
-    float *er;
+    const int32_t *xrank;
+    uint16_t *xw;
+    uint64_t *er;
 };
 
 // Counts of the list path are packed kPackBits to a field: N <= kListMaxN.
@@ -169,6 +175,17 @@ struct ScanUnit {
     int32_t job, group, row0, nrows;
 };
 
+// A column to be ranked by value: its rows' ranks, the row of each rank and
+// the values in rank order (rank and ord may be null).  part: [kRankParts][n]
+// scratch.
+constexpr int kRankParts = 16;
+struct RankCol {
+    const float *col;
+    int n;
+    int32_t *part, *rank, *ord;
+    float *sorted;
+};
+
 // One launch of the list path over `n_jobs` jobs (all with dz > 0).
 struct ListLaunch {
     const Job *jobs;              // device
@@ -196,7 +213,6 @@ struct ListLaunch {
     int kmax, dxm;                // compile-time classes of the scan kernel
     int fb_grid;                  // blocks of the fallback kernel
     int max_chunks;               // largest ceil(n / kChunk) of the jobs (reduction grid)
-    int sortx;                    // some job has no Z: sort the X columns (Job::xs)
     int coop_lanes;               // the scan finishes cooperatively once this many lanes remain
     int grouped;                  // 1: a scan group's rows on as few XCDs as fill them evenly; 0: on all
     // Scan units, dealt to the XCDs in turn (unit u on XCD u % kXcds, each XCD
@@ -209,11 +225,13 @@ struct ListLaunch {
     int unit_t;
     int64_t scan_blocks;          // grid of the scan
     int scan_step;                // list entries per step of the scan's lane-by-lane loops (4, 8)
-    int rank_sets;                // sets counted by ranks (ListSet::zs)
+    const RankCol *rank_cols;     // the columns to rank
+    int n_rank_cols;
+    size_t wavelet_lds;           // LDS bytes of a wavelet block (0: no job is counted there)
     int64_t rank_waves;           // rank-count waves: sum over those sets' jobs of
                                   // n_est * ceil(n / 64)
     const int64_t *rank_off;      // [n_jobs+1] prefix sums of each job's rank-count waves
-    int max_rank_n;               // largest n of a set counted by ranks
+    int max_rank_n;               // largest n of a ranked column
 };
 
 // Counter words of one job (all zero before a launch):
@@ -262,6 +280,12 @@ int kernel_variant_count();
 bool kernel_variant(int i, TileCfg *cfg);
 int variant_blocks_per_cu(int variant);
 int launch_reset(uint32_t *words, int64_t n_words, void *stream);
+// The same for jobs of at most kPermTableMax rows per replication, shuffled
+// within replications: one block per (job, estimate, replication) (item_off:
+// [n_jobs+1] prefix sums), `max_rows` the largest rows per replication.
+constexpr int kPermTableMax = 16384;
+int launch_permute_table(const Job *jobs_dev, int n_jobs, int64_t items, const int64_t *item_off, int max_rows,
+                         void *stream);
 // Permuted X columns: total_blocks work items (blk_off: [n_jobs+1] prefix
 // sums of each job's items), on a grid of at most max_grid blocks (0: one
 // block per item) that take the items in turn.
@@ -274,10 +298,11 @@ int launch_main(int variant, const Job *jobs_dev, int n_jobs, const int64_t *a_o
 int launch_list_zy(const ListLaunch &L, void *stream);      // the sets' contiguous Y,Z copies; clears the counters
 int launch_list_order(const ListLaunch &L, void *stream);  // the scan's row order (several jobs)
 int launch_list_build(const ListLaunch &L, void *stream);
-int launch_list_sortx(const ListLaunch &L, void *stream);
 int launch_list_scan(const ListLaunch &L, void *stream);
-int launch_list_rank_sort(const ListLaunch &L, void *stream);   // ranks of the one-Z-column sets
-int launch_list_rank_count(const ListLaunch &L, void *stream);  // their jobs' counts
+int launch_list_rank(const ListLaunch &L, void *stream);        // ranks of the columns in rank_cols
+int launch_list_rank_count(const ListLaunch &L, void *stream);  // counts of the ranked sets' jobs over rank ranges
+int launch_list_wavelet(const ListLaunch &L, void *stream);     // the same in wavelet matrices
+size_t list_wavelet_lds(int n);                                 // LDS of such a block, 0: does not fit
 int launch_list_fallback(const ListLaunch &L, void *stream);
 int launch_list_reduce(const ListLaunch &L, const double *harm, void *stream);
 

@@ -96,6 +96,22 @@ constexpr int kPermRows = 1024;                        // rows per block
 constexpr int kPermThreads = 256;
 constexpr int kPermPer = kPermRows / kPermThreads;     // rows per thread
 
+// Row i of estimate e takes source row x: every copy of the X columns that the
+// job's path reads.
+__device__ __forceinline__ void store_row(const Job &J, int e, int64_t i, int64_t x) {
+    // the scan's copy: group g's estimates of one row in 64 adjacent words
+    const int gE = J.n_est, gG = scan_groups(gE), gg = scan_group_of(e, gE);
+    const int gl = e - scan_group_first(gg, gE);
+    const int64_t ri = J.xr ? (int64_t)min(max(J.zrank[i], 0), J.n - 1) : 0;
+    if (J.xw) J.xw[(int64_t)e * J.n + i] = (uint16_t)x;
+    for (int c = 0; c < J.dx; ++c) {
+        const float v = J.cols[c][x];
+        if (J.xt) J.xt[(((int64_t)c * gG + gg) * J.n + i) * kScanLanes + gl] = v;
+        J.xp[((int64_t)e * J.dx + c) * J.n + i] = v;
+        if (J.xr) J.xr[((int64_t)e * J.dx + c) * J.n + ri] = v;
+    }
+}
+
 __global__ __launch_bounds__(kPermThreads) void permute_kernel(const Job *__restrict__ jobs, int n_jobs,
                                                               const int64_t *__restrict__ blk_off, int64_t total,
                                                               int64_t grid) {
@@ -151,20 +167,83 @@ __global__ __launch_bounds__(kPermThreads) void permute_kernel(const Job *__rest
         for (int q = 0; q < kPermPer; ++q) {
             const int t = c0 + tid + q * kPermThreads;
             if (t >= nr) break;
-            const int64_t i = base + t;
-            const int64_t x = xbase + (int64_t)src[q];
-            // the scan's copy: group g's estimates of one row in 64 adjacent words
-            const int gE = J.n_est, gG = scan_groups(gE), gg = scan_group_of(e, gE);
-            const int gl = e - scan_group_first(gg, gE);
-            const int64_t ri = J.xr ? (int64_t)min(max(J.zrank[i], 0), J.n - 1) : 0;
-            for (int c = 0; c < J.dx; ++c) {
-                const float v = J.cols[c][x];
-                if (J.xt) J.xt[(((int64_t)c * gG + gg) * J.n + i) * kScanLanes + gl] = v;
-                J.xp[((int64_t)e * J.dx + c) * J.n + i] = v;
-                if (J.xr) J.xr[((int64_t)e * J.dx + c) * J.n + ri] = v;
-            }
+            store_row(J, e, base + t, xbase + (int64_t)src[q]);
         }
     }
+}
+
+// ------------------------------------------------------------------ permute, table
+// The same permutation for up to kPermTableMax rows per replication, as swaps:
+// with pi = s_{R-1} o ... o s_0 the composition of the rounds' involutions,
+// Q_R the identity and Q_r(x) = Q_{r+1}(s_r(x)), Q_0 is pi, and going from
+// Q_{r+1} to Q_r exchanges the entries of each pair (x, x') that round r swaps.
+// A block keeps Q of one estimate (and replication) in LDS as 16-bit words and
+// takes each pair once, where following every row through the rounds computes
+// a pair's bit for both of its rows: half the multiplies, which are a quarter
+// as fast as other instructions.  The pairs of a round are disjoint, so one
+// barrier per round suffices.  In pair p of a round with K: p < (K+1)/2 is the
+// pair (p, K - p), the others are (K+1+q, n-1-q), q = p - (K+1)/2; the second
+// of either is the larger, max(x, x').  It is below 2^30, so the first
+// xor-shift of max ^ rk leaves its bits alone: (max ^ rk) ^ (max ^ rk) >> 30 is
+// max ^ (rk ^ rk >> 30) in the low word.  The round keys are computed once,
+// a thread each.  Beside the list build of 32 served requests (6432 estimates)
+// it takes 0.54 ms a launch, the kernel above 1.51 ms.  In a launch of few
+// estimates, whose build fills the LDS pipe with its atomics, it is the
+// slower one: 201 estimates at N = 10^4, dz = 5 252 us, the kernel above 232
+// (several pairs per step for more loads in flight: 306 to 327 us).
+constexpr int kPermTabThreads = 512;
+constexpr int kPermRoundsMax = 96;                     // 6 ceil(log2 16384) = 84
+
+__global__ __launch_bounds__(kPermTabThreads) void permute_table_kernel(const Job *__restrict__ jobs, int n_jobs,
+                                                                       const int64_t *__restrict__ item_off) {
+    extern __shared__ uint16_t tab[];
+    __shared__ uint4 keys[kPermRoundsMax];
+    const int tid = (int)__builtin_amdgcn_workitem_id_x();
+    const int64_t b = (int64_t)__builtin_amdgcn_workgroup_id_x();
+    int lo = 0, hi = n_jobs - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (item_off[mid] <= b) lo = mid; else hi = mid - 1;
+    }
+    const Job &J = jobs[__builtin_amdgcn_readfirstlane(lo)];
+    const int64_t local = b - item_off[__builtin_amdgcn_readfirstlane(lo)];
+    const int reps = J.reps, n = J.n / reps;
+    const int e = (int)(local / reps), rep = (int)(local - (int64_t)e * reps);
+    const EstKey key = J.keys[e];
+    const uint64_t hh = reps == 1 ? key.h : dmix64(key.h ^ ((uint64_t)(rep + 1) * kGolden));
+    const int rounds = key.ident ? 0 : min(n_rounds_dev((uint32_t)n), kPermRoundsMax);
+    if (tid < rounds) {
+        const SonRound s = son_round_key(hh, tid, (uint32_t)n);
+        keys[tid] = make_uint4(s.k, s.rk_lo ^ __builtin_amdgcn_alignbit(s.rk_hi, s.rk_lo, 30), s.cross, 0u);
+    }
+    for (int x = tid; x < n; x += kPermTabThreads) tab[x] = (uint16_t)x;
+    __syncthreads();
+    for (int r = rounds - 1; r >= 0; --r) {
+        const uint4 kk = keys[r];
+        const uint32_t K = __builtin_amdgcn_readfirstlane(kk.x), C = __builtin_amdgcn_readfirstlane(kk.y),
+                       cross = __builtin_amdgcn_readfirstlane(kk.z);
+        const uint32_t h1 = (K + 1) >> 1, pairs = h1 + (((uint32_t)n - 1 - K) >> 1);
+        const uint32_t da = K + 1 - h1, sb = (uint32_t)n - 1 + h1;
+        for (uint32_t p = (uint32_t)tid; p < pairs; p += kPermTabThreads) {
+            const bool first = p < h1;
+            const uint32_t x = first ? p : p + da, m = (first ? K : sb) - p;
+            const uint32_t l = m ^ C;
+            const uint64_t pr = (uint64_t)l * kMixC1Lo;
+            uint32_t nl = (uint32_t)pr;
+            uint32_t nh = (uint32_t)(pr >> 32) + l * kMixC1Hi + cross;
+            nl ^= __builtin_amdgcn_alignbit(nh, nl, 27);
+            nh ^= nh >> 27;
+            const uint32_t top = (uint32_t)(((uint64_t)nl * kMixC2Lo) >> 32) + nl * kMixC2Hi + nh * kMixC2Lo;
+            if ((int32_t)top < 0) {
+                const uint16_t u = tab[x], v = tab[m];
+                tab[x] = v;
+                tab[m] = u;
+            }
+        }
+        __syncthreads();
+    }
+    const int64_t base = (int64_t)rep * n;
+    for (int t = tid; t < n; t += kPermTabThreads) store_row(J, e, base + t, base + tab[t]);
 }
 
 __global__ void reset_kernel(uint32_t *__restrict__ w, int64_t n) {
@@ -231,6 +310,15 @@ int launch_permute(const Job *jobs_dev, int n_jobs, int64_t total_blocks, const 
     const int64_t grid = max_grid > 0 && max_grid < total_blocks ? max_grid : total_blocks;
     hipLaunchKernelGGL(permute_kernel, dim3((unsigned)grid), dim3(kPermThreads), 0, (hipStream_t)stream, jobs_dev,
                        n_jobs, blk_off, total_blocks, grid);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+int launch_permute_table(const Job *jobs_dev, int n_jobs, int64_t items, const int64_t *item_off, int max_rows,
+                         void *stream) {
+    if (items <= 0) return 0;
+    if (max_rows > kPermTableMax) return -1;
+    hipLaunchKernelGGL(permute_table_kernel, dim3((unsigned)items), dim3(kPermTabThreads),
+                       sizeof(uint16_t) * (size_t)max_rows, (hipStream_t)stream, jobs_dev, n_jobs, item_off);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

@@ -58,6 +58,13 @@ constexpr uint32_t kFloorMask = ~((1u << kKeyShift) - 1u);
 __device__ __forceinline__ int tid_x() { return (int)__builtin_amdgcn_workitem_id_x(); }
 __device__ __forceinline__ int64_t bid_x() { return (int64_t)__builtin_amdgcn_workgroup_id_x(); }
 
+// Read-only memory addressed through the constant address space: a load from
+// a wave-uniform address is then a scalar load.
+template <class T>
+using Const = const __attribute__((address_space(4))) T;
+template <class T>
+__device__ __forceinline__ Const<T> *as_const(const T *p) { return (Const<T> *)p; }
+
 // Load through a global-address-space pointer: a generic (flat) load would
 // count against both the vector-memory and the LDS counters, and the wait for
 // the gathers would then also wait for the next step's entries loaded ahead.
@@ -82,6 +89,7 @@ __device__ __forceinline__ float gload_b(const float *p, uint32_t byte_off) {
 }
 
 constexpr uint64_t kPackMask = (uint64_t(1) << kPackBits) - 1;
+constexpr uint64_t kRankNone = 0xbf800000u;   // radius -1: the pair is in the redo queue
 
 __device__ __forceinline__ uint64_t pack_counts(int cxz, int cyz, int cz) {
     return (uint64_t)(uint32_t)cxz | ((uint64_t)(uint32_t)cyz << kPackBits) |
@@ -689,37 +697,64 @@ __global__ __launch_bounds__(kBlock) void list_zy_kernel(const ListLaunch L) {
     for (int c = 0; c < dy; ++c) S.zy[(dz + c) * n + j] = S.cols[c][j];
 }
 
-// ------------------------------------------------------------------ X sort
-// One block per job without Z: its X column sorted ascending (bitonic, in
-// LDS, padded with +inf to a power of two), for the n_x range counts.
-constexpr int kSortThreads = 1024;
+// ------------------------------------------------------------------ ranks
+// Columns ranked by value, ties by row index (the z column of a set counted
+// by ranks, the X column of a job without Z or counted in a wavelet matrix).
+// Every row's smaller rows are counted, n compares per row, split into
+// kRankParts ranges of rows so that one column fills the chip: a wave takes 64
+// rows and one range, whose values come 16 at a time through the scalar
+// cache.  A second kernel adds the ranges' counts and scatters.  Beside the
+// build at n = 10^4 the two take 75 us for two columns; one block's bitonic
+// sort of one in LDS took 208 us, the same compares on 157 blocks 171 us.
+constexpr int kRankThreads = 256;
 
-__global__ __launch_bounds__(kSortThreads) void list_sortx_kernel(const ListLaunch L) {
-    __shared__ float v[kNoZSortMax];
-    const Job &J = L.jobs[bid_x()];
-    if (!J.xs) return;
-    const int tid = tid_x();
-    const int n = J.n;
-    int P = 1;
-    while (P < n) P <<= 1;
-    for (int x = tid; x < P; x += kSortThreads) v[x] = x < n ? J.cols[0][x] : inf_f();
-    __syncthreads();
-    for (int k = 2; k <= P; k <<= 1) {
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int x = tid; x < P; x += kSortThreads) {
-                const int y = x ^ j;
-                if (y > x) {
-                    const float a = v[x], b = v[y];
-                    if ((a > b) == ((x & k) == 0)) {
-                        v[x] = b;
-                        v[y] = a;
-                    }
-                }
-            }
-            __syncthreads();
-        }
+__global__ __launch_bounds__(kRankThreads) void list_rank_part_kernel(const ListLaunch L) {
+    const RankCol *C = L.rank_cols + __builtin_amdgcn_workgroup_id_z();
+    Const<RankCol> *R = as_const(C);
+    const int n = R->n;
+    const int i0 = (int)bid_x() * kRankThreads;
+    if (i0 >= n) return;
+    __builtin_amdgcn_s_setprio(kBuildPrio);   // short, and the permutation waits for it beside the build
+    const int part = (int)__builtin_amdgcn_workgroup_id_y();
+    const int i = i0 + tid_x();
+    const float *col = R->col;
+    const float vi = gload(col, (uint32_t)min(i, n - 1));
+    const int j0 = (int)((int64_t)n * part / kRankParts), j1 = (int)((int64_t)n * (part + 1) / kRankParts);
+    Const<float> *v = as_const(col);
+    int r = 0;
+    // rows before the block's count with <=, rows after it with <; the rows
+    // of the block itself by their index too
+    const int a = max(j0, min(j1, i0)), b = max(a, min(j1, i0 + kRankThreads));
+    constexpr int RU = 16;
+    int j = j0;
+    for (; j + RU <= a; j += RU) {
+#pragma unroll
+        for (int u = 0; u < RU; ++u) r += v[j + u] <= vi;
     }
-    for (int x = tid; x < n; x += kSortThreads) J.xs[x] = v[x];
+    for (; j < a; ++j) r += v[j] <= vi;
+    for (; j < b; ++j) r += (int)(v[j] < vi) | ((int)(v[j] == vi) & (int)(j < i));
+    for (; j + RU <= j1; j += RU) {
+#pragma unroll
+        for (int u = 0; u < RU; ++u) r += v[j + u] < vi;
+    }
+    for (; j < j1; ++j) r += v[j] < vi;
+    if (i < n) R->part[(int64_t)part * n + i] = r;
+}
+
+__global__ __launch_bounds__(kRankThreads) void list_rank_place_kernel(const ListLaunch L) {
+    const RankCol &C = L.rank_cols[__builtin_amdgcn_workgroup_id_y()];
+    const int n = C.n;
+    const int i = (int)bid_x() * kRankThreads + tid_x();
+    if (i >= n) return;
+    int r = 0;
+#pragma unroll
+    for (int p = 0; p < kRankParts; ++p) r += C.part[(int64_t)p * n + i];
+    // (columns that are not finite, which device calls do not check, may
+    // repeat a rank: a wrong result, never a fault)
+    r = min(r, n - 1);
+    if (C.rank) C.rank[i] = r;
+    if (C.ord) C.ord[r] = i;
+    C.sorted[r] = C.col[i];
 }
 
 // ------------------------------------------------------------------ row order
@@ -735,6 +770,7 @@ __global__ __launch_bounds__(kSortThreads) void list_sortx_kernel(const ListLaun
 // entries.  The order of the rows within a cell follows the scatter's LDS
 // atomics and may differ between launches: only the order in which the scan
 // visits rows depends on it, not any result.
+constexpr int kSortThreads = 1024;
 constexpr int kOrderDims = 6;
 constexpr int kOrderBits = 12;
 constexpr int kOrderCells = 1 << kOrderBits;
@@ -848,13 +884,6 @@ __global__ __launch_bounds__(kSortThreads) void list_order_kernel(const ListLaun
 // bound, i.e. an undecided pair, as it should.
 constexpr int kU = 8;   // the largest step
 static_assert(2 * kU <= kListPad, "a step and the next must stay within the sentinels");
-
-// Read-only memory addressed through the constant address space: a load from
-// a wave-uniform address is then a scalar load.
-template <class T>
-using Const = const __attribute__((address_space(4))) T;
-template <class T>
-__device__ __forceinline__ Const<T> *as_const(const T *p) { return (Const<T> *)p; }
 
 // A step's entries (distance, row) in scalar registers.
 template <int NU>
@@ -1194,15 +1223,17 @@ __global__ __launch_bounds__(kScanLanes) void list_scan_kernel(const ListLaunch 
     }
     if (live) {
         const int64_t at_e = (int64_t)e * n + i;
-        if (ranked) J->er[at_e] = decided ? eps : -1.0f;
+        // a ranked pair hands its radius and n_yz over, by the rank of its row
+        if (ranked)
+            J->er[(int64_t)e * n + as_const(J->zrank)[i]] =
+                decided ? ((uint64_t)(uint32_t)cyz << 32) | __float_as_uint(eps) : kRankNone;
         if (!decided) {
             const uint32_t pos = atomicAdd(&L.counters[0], 1u);
             L.failq[pos] = ((uint64_t)jb << 40) | ((uint64_t)i * E + e);
-        } else {
-            // (of a ranked pair: n_yz, completed by the rank-count kernel)
+        } else if (!ranked) {
             J->pk[at_e] = pack_counts(cxz, cyz, cz);
-            if (!ranked && J->eps) J->eps[at_e] = eps;
-            if (!ranked && J->cnt) {
+            if (J->eps) J->eps[at_e] = eps;
+            if (J->cnt) {
                 J->cnt[((int64_t)e * 3 + 0) * n + i] = cxz;
                 J->cnt[((int64_t)e * 3 + 1) * n + i] = cyz;
                 J->cnt[((int64_t)e * 3 + 2) * n + i] = cz;
@@ -1218,53 +1249,7 @@ __global__ __launch_bounds__(kScanLanes) void list_scan_kernel(const ListLaunch 
     }
 }
 
-// ------------------------------------------------------------------ ranks
-// Sets with one Z column: the rows ranked by z (ties by row index).  A block
-// takes 64 rows; its four waves count, for those rows, the rows before them
-// in a quarter of the set each (z staged in LDS), and the four partial
-// ranks are added.
-constexpr int kRankThreads = 256;
-constexpr int kRankRows = 64;
-
-__global__ __launch_bounds__(kRankThreads) void list_rank_sort_kernel(const ListLaunch L) {
-    const ListSet &S = L.sets[__builtin_amdgcn_workgroup_id_y()];
-    if (!S.zs) return;
-    const int n = S.n;
-    const int i0 = (int)bid_x() * kRankRows;
-    if (i0 >= n) return;
-    const int tid = tid_x(), lane = tid & 63, part = tid >> 6;
-    const float *z = S.cols[S.dy];
-    __shared__ float t[kRankThreads];
-    __shared__ int partial[kRankThreads / 64][kRankRows];
-    const int i = i0 + lane;
-    const float zi = i < n ? z[i] : 0.f;
-    const int span = (n + 3) / 4;
-    const int j_lo = part * span, j_hi = min(n, j_lo + span);
-    int r = 0;
-    // every thread takes part in the staging, so the loop bounds are
-    // those of the longest part
-    for (int j0 = 0; j0 < span; j0 += 64) {
-        __syncthreads();
-        const int jj = j_lo + j0 + lane;
-        t[tid] = jj < j_hi ? z[jj] : 0.f;
-        __syncthreads();
-        const int m = min(64, j_hi - (j_lo + j0));
-        for (int u = 0; u < m; ++u) {
-            const float v = t[part * 64 + u];
-            const int j = j_lo + j0 + u;
-            r += (v < zi) | ((v == zi) & (j < i));
-        }
-    }
-    partial[part][lane] = r;
-    __syncthreads();
-    if (part == 0 && i < n) {
-        const int rank = partial[0][lane] + partial[1][lane] + partial[2][lane] + partial[3][lane];
-        S.zrank[i] = rank;
-        S.zord[rank] = i;
-        S.zs[rank] = zi;
-    }
-}
-
+// ------------------------------------------------------------------ rank counts
 // Counts of the pairs of a set with one Z column.  The rows within the
 // radius of row i in z are the ranks [lo, hi) with fl(zs[r] - z_i) > -eps
 // and fl(zs[r] - z_i) < eps (two binary searches), so n_z = hi - lo, and
@@ -1293,12 +1278,12 @@ __global__ __launch_bounds__(kRankThreads) void list_rank_count_kernel(const Lis
     // (ranks and rows are clamped to the set: inputs that are not finite,
     // which device calls do not check, leave a wrong result, never a fault)
     const int i = min(max(S.zord[rr], 0), n - 1);
-    const float eps = J.er[(int64_t)e * n + i];
+    const uint64_t word = J.er[(int64_t)e * n + rr];
+    const float eps = __uint_as_float((uint32_t)word);
     const bool ok = r < n && eps >= 0.f;      // -1: the pair is in the redo queue
     const float *zs = S.zs;
     const float *xr = J.xr + (int64_t)e * dx * n;
     const float zq = zs[rr];
-    const uint64_t pk = J.pk[(int64_t)e * n + i];   // n_yz, from the scan
     float xq[DXM];
 #pragma unroll
     for (int c = 0; c < DXM; ++c) xq[c] = c < dx ? xr[(int64_t)c * n + rr] : 0.f;
@@ -1387,7 +1372,7 @@ __global__ __launch_bounds__(kRankThreads) void list_rank_count_kernel(const Lis
         }
     }
     if (ok) {
-        const int my = (int)((pk >> kPackBits) & kPackMask);
+        const int my = (int)(word >> 32);     // n_yz, from the scan
         J.pk[(int64_t)e * n + i] = pack_counts(mx, my, mz);
         if (J.eps) J.eps[(int64_t)e * n + i] = eps;
         if (J.cnt) {
@@ -1401,6 +1386,186 @@ __global__ __launch_bounds__(kRankThreads) void list_rank_count_kernel(const Lis
         unsigned long long *st =
             reinterpret_cast<unsigned long long *>(L.counters + kListStatWord + slot * kListStatStride);
         atomicAdd(&st[1], (unsigned long long)ent);
+    }
+}
+
+// ------------------------------------------------------------------ wavelet counts
+// n_xz of the pairs of a set with one Z column, one X column and no Theiler
+// window: the rows of ranks [lo, hi) in z whose x lies within eps of x_i are,
+// in ranks of x, those in [a, b) (two more binary searches, on the job's
+// sorted X).  One block per estimate keeps the wavelet matrix of the sequence
+// "rank of x by rank of z" in LDS: per bit of the rank, from the top, a bit
+// vector with running counts, the sequence stably partitioned by that bit
+// from level to level.  A pair's count then takes one walk over the levels
+// for a and one for b, a lane per pair, instead of reading the hi - lo rows
+// (on average 740 at N = 10^4) with all lanes over one pair after another:
+// 423 -> 160 us at N = 9995, 201 estimates (the whole test 1.06 -> 0.71 ms).
+constexpr int kWvThreads = 1024;
+constexpr int kWvWaves = kWvThreads / 64;
+constexpr int kWvBits = 16;
+
+struct WvNode {
+    uint32_t bits, ones;                      // 32 elements' bits, ones before them
+};
+
+__device__ __forceinline__ int wv_bits(int n) { return 32 - __builtin_clz((unsigned)n); }   // n < 2^bits
+
+__global__ __launch_bounds__(kWvThreads) void list_wavelet_kernel(const ListLaunch L) {
+    extern __shared__ uint64_t wv_lds[];
+    __shared__ int wtot[kWvWaves];
+    __shared__ int zeros[kWvBits];
+    const int64_t g = bid_x();
+    const int jb = __builtin_amdgcn_readfirstlane(find_job(L.est_off, L.n_jobs, g));
+    Const<Job> *J = as_const(L.jobs) + jb;
+    if (!J->xw) return;                       // counted elsewhere (uniform in the block)
+    Const<ListSet> *S = as_const(L.sets) + J->set;
+    const int n = J->n, e = (int)(g - as_const(L.est_off)[jb]);
+    const int tid = tid_x(), lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nblk = (n + 63) / 64, per = (nblk + kWvWaves - 1) / kWvWaves;
+    const int nb = wv_bits(n), stride = 2 * nblk + 1;
+    WvNode *node = reinterpret_cast<WvNode *>(wv_lds);
+    // the sequence, from one buffer into the other level by level
+    uint16_t *sa = reinterpret_cast<uint16_t *>(node + nb * stride), *sb = sa + n;
+    float *xs = reinterpret_cast<float *>(sa);
+    // source row of each row and rank of each source row, then the sequence
+    const uint16_t *src = J->xw + (int64_t)e * n;
+    uint16_t *xw = J->xw + (int64_t)(J->n_est + e) * n;
+    const int32_t *xrank = J->xrank;
+    for (int q = tid; q < n; q += kWvThreads) {
+        sa[q] = src[q];
+        sb[q] = (uint16_t)xrank[q];
+    }
+    __syncthreads();
+    const int32_t *zord = S->zord;
+    const int blk0 = wave * per, blk1 = min(nblk, blk0 + per);
+    for (int blk = blk0; blk < blk1; ++blk) {
+        const int p = blk * 64 + lane;
+        if (p < n) xw[p] = sb[min((int)sa[min(max(zord[p], 0), n - 1)], n - 1)];
+    }
+    __syncthreads();
+    for (int blk = blk0; blk < blk1; ++blk) {
+        const int p = blk * 64 + lane;
+        if (p < n) sa[p] = xw[p];
+    }
+    __syncthreads();
+    for (int lev = 0; lev < nb; ++lev) {
+        const int sh = nb - 1 - lev;
+        WvNode *nd = node + lev * stride;
+        int run = 0;
+        for (int blk = blk0; blk < blk1; ++blk) {
+            const int p = blk * 64 + lane;
+            run += __builtin_popcountll(cmp_mask(p < n && ((sa[p] >> sh) & 1)));
+        }
+        if (lane == 0) wtot[wave] = run;
+        __syncthreads();
+        int before = 0, total = 0;
+#pragma unroll
+        for (int w = 0; w < kWvWaves; ++w) {
+            before += w < wave ? wtot[w] : 0;
+            total += wtot[w];
+        }
+        const int z = n - total;
+        if (tid == 0) {
+            zeros[lev] = z;
+            nd[2 * nblk] = WvNode{0u, (uint32_t)total};
+        }
+        for (int blk = blk0; blk < blk1; ++blk) {
+            const int p = blk * 64 + lane;
+            const uint32_t v = p < n ? sa[p] : 0u;
+            const bool one = (v >> sh) & 1u;
+            const uint64_t m = cmp_mask(one);
+            const uint32_t mlo = (uint32_t)m, mhi = (uint32_t)(m >> 32);
+            if (lane == 0) {
+                nd[2 * blk] = WvNode{mlo, (uint32_t)before};
+                nd[2 * blk + 1] = WvNode{mhi, (uint32_t)(before + __builtin_popcount(mlo))};
+            }
+            const int r1 = before + (int)__builtin_amdgcn_mbcnt_hi(mhi, __builtin_amdgcn_mbcnt_lo(mlo, 0u));
+            if (p < n) sb[one ? z + r1 : p - r1] = (uint16_t)v;
+            before += __builtin_popcountll(m);
+        }
+        __syncthreads();
+        uint16_t *t = sa;
+        sa = sb;
+        sb = t;
+    }
+    // the sorted X column takes the sequence's place
+    const float *xsg = J->xs;
+    for (int q = tid; q < n; q += kWvThreads) xs[q] = gload(xsg, (uint32_t)q);
+    __syncthreads();
+
+    const float *zs = S->zs;
+    const uint64_t *er = J->er + (int64_t)e * n;
+    auto ones = [&](const WvNode *nd, int p) {
+        const WvNode w = nd[p >> 5];
+        return (int)w.ones + __builtin_popcount(w.bits & ((1u << (p & 31)) - 1u));
+    };
+    for (int r = tid; r < n; r += kWvThreads) {
+        const uint64_t word = er[r];
+        const float eps = __uint_as_float((uint32_t)word);
+        const float zq = gload(zs, (uint32_t)r), xq = xs[min((int)xw[r], n - 1)];
+        // ranks of z within eps, then ranks of x
+        int lo, hi, a, b;
+        {
+            int p = 0, q = n;
+            while (p < q) {
+                const int m = (p + q) >> 1;
+                if (gload(zs, (uint32_t)m) - zq > -eps) q = m; else p = m + 1;
+            }
+            lo = p;
+            q = n;
+            while (p < q) {
+                const int m = (p + q) >> 1;
+                if (gload(zs, (uint32_t)m) - zq >= eps) q = m; else p = m + 1;
+            }
+            hi = p;
+            p = 0;
+            q = n;
+            while (p < q) {
+                const int m = (p + q) >> 1;
+                if (xs[m] - xq > -eps) q = m; else p = m + 1;
+            }
+            a = p;
+            q = n;
+            while (p < q) {
+                const int m = (p + q) >> 1;
+                if (xs[m] - xq >= eps) q = m; else p = m + 1;
+            }
+            b = p;
+        }
+        int la = lo, ra = hi, lb = lo, rb = hi, cnt = 0;
+        for (int lev = 0; lev < nb; ++lev) {
+            const WvNode *nd = node + lev * stride;
+            const int z = zeros[lev], sh = nb - 1 - lev;
+            const int la1 = ones(nd, la), ra1 = ones(nd, ra), lb1 = ones(nd, lb), rb1 = ones(nd, rb);
+            if ((b >> sh) & 1) {
+                cnt += (rb - rb1) - (lb - lb1);
+                lb = z + lb1;
+                rb = z + rb1;
+            } else {
+                lb -= lb1;
+                rb -= rb1;
+            }
+            if ((a >> sh) & 1) {
+                cnt -= (ra - ra1) - (la - la1);
+                la = z + la1;
+                ra = z + ra1;
+            } else {
+                la -= la1;
+                ra -= ra1;
+            }
+        }
+        if (!(eps >= 0.f)) continue;          // in the redo queue
+        // the pair's own row is in the range and within eps exactly when eps > 0
+        const int own = eps > 0.f ? 1 : 0;
+        const int i = min(max(zord[r], 0), n - 1), cyz = (int)(word >> 32);
+        J->pk[(int64_t)e * n + i] = pack_counts(cnt - own, cyz, hi - lo - own);
+        if (J->eps) J->eps[(int64_t)e * n + i] = eps;
+        if (J->cnt) {
+            J->cnt[((int64_t)e * 3 + 0) * n + i] = cnt - own;
+            J->cnt[((int64_t)e * 3 + 1) * n + i] = cyz;
+            J->cnt[((int64_t)e * 3 + 2) * n + i] = hi - lo - own;
+        }
     }
 }
 
@@ -1729,11 +1894,38 @@ int launch_list_scan(const ListLaunch &L, void *stream) {
                : -1;
 }
 
-int launch_list_rank_sort(const ListLaunch &L, void *stream) {
-    if (L.rank_sets <= 0) return 0;
-    const dim3 grid((unsigned)((L.max_rank_n + kRankRows - 1) / kRankRows), (unsigned)L.n_sets);
-    hipLaunchKernelGGL(list_rank_sort_kernel, grid, dim3(kRankThreads), 0, (hipStream_t)stream, L);
+int launch_list_rank(const ListLaunch &L, void *stream) {
+    if (L.n_rank_cols <= 0) return 0;
+    const unsigned rows = (unsigned)((L.max_rank_n + kRankThreads - 1) / kRankThreads);
+    hipLaunchKernelGGL(list_rank_part_kernel, dim3(rows, (unsigned)kRankParts, (unsigned)L.n_rank_cols),
+                       dim3(kRankThreads), 0, (hipStream_t)stream, L);
+    hipLaunchKernelGGL(list_rank_place_kernel, dim3(rows, (unsigned)L.n_rank_cols), dim3(kRankThreads), 0,
+                       (hipStream_t)stream, L);
     return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+// LDS of a wavelet block of n rows: the nodes, then the sequence or the
+// sorted X column; 0 when it does not fit.
+size_t list_wavelet_lds(int n) {
+    if (n >= 32768) return 0;
+    int nb = 0;
+    while ((int64_t(1) << nb) <= n) ++nb;
+    const size_t b = sizeof(WvNode) * (size_t)nb * (2 * (((size_t)n + 63) / 64) + 1) + sizeof(float) * (size_t)n;
+    return b <= 163840 - 1024 ? b : 0;
+}
+
+int launch_list_wavelet(const ListLaunch &L, void *stream) {
+    if (L.wavelet_lds == 0) return 0;
+    void *fn = reinterpret_cast<void *>(&list_wavelet_kernel);
+    if (L.wavelet_lds > 65536 - 1024 &&
+        hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 163840 - 1024) != hipSuccess)
+        return -1;
+    ListLaunch arg = L;
+    void *args[] = {(void *)&arg};
+    return hipLaunchKernel(fn, dim3((unsigned)L.ests), dim3(kWvThreads), args, L.wavelet_lds, (hipStream_t)stream) ==
+                   hipSuccess
+               ? 0
+               : -1;
 }
 
 int launch_list_rank_count(const ListLaunch &L, void *stream) {
@@ -1755,12 +1947,6 @@ int launch_list_fallback(const ListLaunch &L, void *stream) {
     else if (L.kmax == 8) hipLaunchKernelGGL(list_fallback_kernel<8>, grid, block, 0, (hipStream_t)stream, L);
     else if (L.kmax == 16) hipLaunchKernelGGL(list_fallback_kernel<16>, grid, block, 0, (hipStream_t)stream, L);
     else return -1;
-    return hipGetLastError() == hipSuccess ? 0 : -1;
-}
-
-int launch_list_sortx(const ListLaunch &L, void *stream) {
-    if (L.n_jobs <= 0) return 0;
-    hipLaunchKernelGGL(list_sortx_kernel, dim3((unsigned)L.n_jobs), dim3(kSortThreads), 0, (hipStream_t)stream, L);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

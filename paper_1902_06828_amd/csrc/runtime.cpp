@@ -967,6 +967,7 @@ static void list_caps(int dx, int dy, int dz, int n, int *m1, int *m2) {
     }
 }
 
+constexpr int kPermTablePerCu = 2;   // estimates per CU from which the permutations run as tables
 constexpr int kUnitsPerXcd = 4;   // fewest scan units per XCD for the XCD-dealt order
 
 int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<int> &set_of, int n_sets,
@@ -977,15 +978,25 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     std::vector<ListSet> sets(n_sets);
     std::vector<int> set_rep(n_sets, -1);
     std::vector<int64_t> lane_off(n_ljobs_ + 1, 0), est_off(n_ljobs_ + 1, 0), blk_off(n_ljobs_ + 1, 0),
-        row_off(n_sets + 1, 0), build_off(n_sets + 1, 0);
+        row_off(n_sets + 1, 0), build_off(n_sets + 1, 0), item_off(n_ljobs_ + 1, 0);
+    lperm_rows_ = 0;
     int kmax = 0, dxm = 0;
     int64_t n_keys = 0;
+    int64_t total_est = 0;
+    for (const JobSpec &sp : specs) total_est += sp.n_est();
     for (int j = 0; j < n_ljobs_; ++j) {
         const JobSpec &sp = specs[j];
         if (set_rep[set_of[j]] < 0) set_rep[set_of[j]] = j;
         lane_off[j + 1] = lane_off[j] + (int64_t)sp.n * sp.n_est();
         est_off[j + 1] = est_off[j] + sp.n_est();
-        blk_off[j + 1] = blk_off[j] + (int64_t)sp.n_est() * permute_blocks(sp.n, sp.reps);
+        // many short permutations run as swaps of a table in LDS; few of them
+        // beside a build, which is bound by its LDS atomics, row by row (one
+        // test of 201 estimates at N = 10^4, dz = 5: 572 us with tables, 513
+        // without; 32 served requests, 6432 estimates: 8.1 and 9.4 ms)
+        const bool table = total_est >= kPermTablePerCu * c.n_cu && !sp.rep_shuffle && sp.n / sp.reps <= kPermTableMax;
+        blk_off[j + 1] = blk_off[j] + (table ? 0 : (int64_t)sp.n_est() * permute_blocks(sp.n, sp.reps));
+        item_off[j + 1] = item_off[j] + (table ? (int64_t)sp.n_est() * sp.reps : 0);
+        if (table) lperm_rows_ = std::max(lperm_rows_, sp.n / sp.reps);
         kmax = std::max(kmax, sp.k);
         dxm = std::max(dxm, sp.dx);
         n_keys += sp.n_est();
@@ -1039,14 +1050,11 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     const char *rk_env = std::getenv("MTE_RANK_COUNTS");
     const bool rank_on = !(rk_env && *rk_env == '0');
     std::vector<char> ranked(n_sets, 0);
-    int rank_sets = 0, max_rank_n = 0;
+    int max_rank_n = 0;
     for (int t = 0; t < n_sets; ++t) {
         const JobSpec &sp = specs[set_rep[t]];
         ranked[t] = rank_on && sp.dz == 1 && sp.dy == 1 && sp.n <= kRankMaxN;
-        if (ranked[t]) {
-            ++rank_sets;
-            max_rank_n = std::max(max_rank_n, sp.n);
-        }
+        if (ranked[t]) max_rank_n = std::max(max_rank_n, sp.n);
     }
     for (int t = 0; t < n_sets; ++t) {
         const JobSpec &sp = specs[set_rep[t]];
@@ -1085,15 +1093,18 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
             o_order[t] = bytes;
             bytes = align_up(bytes + sizeof(int32_t) * (size_t)sp.n, 256);
         }
-        // rank arrays: zs, zord, zrank (n words each)
+        // rank arrays: zs, zord, zrank (n words each), then the partial counts
         if (ranked[t]) {
             o_rank[t] = bytes;
-            bytes = align_up(bytes + 3 * sizeof(float) * (size_t)sp.n, 256);
+            bytes = align_up(bytes + (3 + kRankParts) * sizeof(float) * (size_t)sp.n, 256);
         }
     }
-    struct Off { size_t xt, xp, pk, xs, chunk, xr, er; };
+    struct Off { size_t xt, xp, pk, xs, chunk, xr, er; bool wavelet; };
     std::vector<Off> offs(n_ljobs_);
     std::vector<int64_t> rank_off(n_ljobs_ + 1, 0);
+    size_t wavelet_lds = 0;
+    int n_rank_cols = 0;
+    for (int t = 0; t < n_sets; ++t) n_rank_cols += ranked[t];
     for (int j = 0; j < n_ljobs_; ++j) {
         const JobSpec &sp = specs[j];
         const size_t pairs = (size_t)sp.n * sp.n_est();
@@ -1102,15 +1113,26 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
         offs[j].xp = bytes;
         bytes = align_up(bytes + sizeof(float) * pairs * sp.dx, 256);
         rank_off[j + 1] = rank_off[j];
+        // a ranked set's job with one X column and no window is counted in a
+        // wavelet matrix when that fits a block's LDS (N up to about 21000),
+        // else over the ranges of ranks
+        const size_t wl = ranked[set_of[j]] && sp.dx == 1 && sp.theiler == 0 ? list_wavelet_lds(sp.n) : 0;
+        offs[j].wavelet = wl > 0;
+        wavelet_lds = std::max(wavelet_lds, wl);
         if (ranked[set_of[j]]) {
             offs[j].xr = bytes;
-            bytes = align_up(bytes + sizeof(float) * pairs * sp.dx, 256);
+            bytes = align_up(bytes + (wl ? 2 * sizeof(uint16_t) : sizeof(float) * sp.dx) * pairs, 256);
             offs[j].er = bytes;
-            bytes = align_up(bytes + sizeof(float) * pairs, 256);
-            rank_off[j + 1] += (int64_t)sp.n_est() * ((sp.n + 63) / 64);
+            bytes = align_up(bytes + sizeof(uint64_t) * pairs, 256);
+            if (!wl) rank_off[j + 1] += (int64_t)sp.n_est() * ((sp.n + 63) / 64);
         }
+        // sorted X, its ranks, and the partial counts
         offs[j].xs = bytes;
-        if (sp.dz == 0) bytes = align_up(bytes + sizeof(float) * (size_t)sp.n, 256);
+        if (sp.dz == 0 || wl) {
+            bytes = align_up(bytes + (2 + kRankParts) * sizeof(float) * (size_t)sp.n, 256);
+            max_rank_n = std::max(max_rank_n, sp.n);
+            ++n_rank_cols;
+        }
         offs[j].pk = bytes;
         bytes = align_up(bytes + sizeof(uint64_t) * pairs, 256);
         offs[j].chunk = bytes;
@@ -1123,9 +1145,10 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     const size_t t_sets = align_up(sizeof(ListSet) * n_sets, 256);
     const size_t t_keys = align_up(sizeof(EstKey) * (size_t)n_keys, 256);
     const size_t t_offs = align_up(
-        sizeof(int64_t) * (5 * (size_t)(n_ljobs_ + 1) + 2 * ((size_t)n_sets + 1) + xcd_off.size()), 256);
+        sizeof(int64_t) * (6 * (size_t)(n_ljobs_ + 1) + 2 * ((size_t)n_sets + 1) + xcd_off.size()), 256);
     const size_t t_units = align_up(sizeof(ScanUnit) * units.size(), 256);
-    const size_t tbytes = t_jobs + t_sets + t_keys + t_offs + t_units;
+    const size_t t_cols = align_up(sizeof(RankCol) * (size_t)n_rank_cols, 256);
+    const size_t tbytes = t_jobs + t_sets + t_keys + t_offs + t_units + t_cols;
     if (measure) {
         *measure += bytes + sizeof(uint32_t) * kListCounterWords + tbytes;
         return MTE_OK;
@@ -1134,6 +1157,7 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     if ((rc = lscratch_.ensure(bytes))) return rc;
     if ((rc = lcounters_.ensure(sizeof(uint32_t) * kListCounterWords))) return rc;
     uint8_t *sb = lscratch_.as<uint8_t>();
+    std::vector<RankCol> rank_cols;
     for (int t = 0; t < n_sets; ++t) {
         ListSet &S = sets[t];
         S.l1 = reinterpret_cast<LEnt *>(sb + o_l1[t]);
@@ -1147,6 +1171,8 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
             S.zs = reinterpret_cast<float *>(sb + o_rank[t]);
             S.zord = reinterpret_cast<int32_t *>(sb + o_rank[t] + nb);
             S.zrank = reinterpret_cast<int32_t *>(sb + o_rank[t] + 2 * nb);
+            rank_cols.push_back(RankCol{S.cols[S.dy], S.n, reinterpret_cast<int32_t *>(sb + o_rank[t] + 3 * nb),
+                                        S.zrank, S.zord, S.zs});
         }
     }
     // build blocks: kBuildRows rows each with packed 16-bit histograms when
@@ -1195,14 +1221,22 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
         J.rep_shuffle = sp.rep_shuffle;
         J.xt = reinterpret_cast<float *>(sb + offs[j].xt);
         J.xp = reinterpret_cast<float *>(sb + offs[j].xp);
-        J.xs = sp.dz == 0 ? reinterpret_cast<float *>(sb + offs[j].xs) : nullptr;
+        if (sp.dz == 0 || offs[j].wavelet) {
+            const size_t nb = sizeof(float) * (size_t)sp.n;
+            J.xs = reinterpret_cast<float *>(sb + offs[j].xs);
+            int32_t *rank = offs[j].wavelet ? reinterpret_cast<int32_t *>(sb + offs[j].xs + nb) : nullptr;
+            J.xrank = rank;
+            rank_cols.push_back(
+                RankCol{J.cols[0], sp.n, reinterpret_cast<int32_t *>(sb + offs[j].xs + 2 * nb), rank, nullptr, J.xs});
+        }
         J.eps = sp.diag_eps;
         J.cnt = sp.diag_cnt;
         J.pk = reinterpret_cast<uint64_t *>(sb + offs[j].pk);
         if (ranked[set_of[j]]) {
             J.zrank = sets[set_of[j]].zrank;
-            J.xr = reinterpret_cast<float *>(sb + offs[j].xr);
-            J.er = reinterpret_cast<float *>(sb + offs[j].er);
+            if (offs[j].wavelet) J.xw = reinterpret_cast<uint16_t *>(sb + offs[j].xr);
+            else J.xr = reinterpret_cast<float *>(sb + offs[j].xr);
+            J.er = reinterpret_cast<uint64_t *>(sb + offs[j].er);
         }
         J.chunk = reinterpret_cast<double *>(sb + offs[j].chunk);
         J.out = sp.out;
@@ -1221,13 +1255,17 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     std::memcpy(oh + 3 * nj1, row_off.data(), sizeof(int64_t) * (n_sets + 1));
     std::memcpy(oh + 3 * nj1 + (n_sets + 1), build_off.data(), sizeof(int64_t) * (n_sets + 1));
     std::memcpy(oh + 3 * nj1 + 2 * (n_sets + 1), rank_off.data(), sizeof(int64_t) * nj1);
-    const size_t o_units = 4 * nj1 + 2 * ((size_t)n_sets + 1);
+    const size_t o_items = 4 * nj1 + 2 * ((size_t)n_sets + 1), o_units = o_items + nj1;
+    std::memcpy(oh + o_items, item_off.data(), sizeof(int64_t) * nj1);
     std::memcpy(oh + o_units, xcd_off.data(), sizeof(int64_t) * xcd_off.size());
     const size_t units_at = t_jobs + t_sets + t_keys + t_offs;
     std::memcpy(hs + units_at, units.data(), sizeof(ScanUnit) * units.size());
+    if (!rank_cols.empty()) std::memcpy(hs + units_at + t_units, rank_cols.data(), sizeof(RankCol) * rank_cols.size());
     ljobs_dev_ = reinterpret_cast<Job *>(tb);
     lblk_off_ = od + 2 * nj1;
     lpermute_blocks_ = blk_off[n_ljobs_];
+    litem_off_ = od + o_items;
+    lpermute_items_ = item_off[n_ljobs_];
     ListLaunch &L = ll_;
     L.jobs = ljobs_dev_;
     L.sets = reinterpret_cast<const ListSet *>(tb + t_jobs);
@@ -1253,8 +1291,6 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     L.fb_grid = std::max(1, 2 * c.n_cu);
     L.max_chunks = 0;
     for (const JobSpec &sp : specs) L.max_chunks = std::max(L.max_chunks, (sp.n + kChunk - 1) / kChunk);
-    L.sortx = 0;
-    for (const JobSpec &sp : specs) L.sortx |= sp.dz == 0;
     L.coop_lanes = env_int("MTE_COOP_LANES", tc.coop_lanes > 0 ? tc.coop_lanes : kCoopLanes);
     L.grouped = dealt ? 1 : 0;
     L.xcd_off = od + o_units;
@@ -1263,7 +1299,9 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     L.scan_blocks = scan_blocks;
     L.scan_step = env_int("MTE_SCAN_STEP", tc.scan_step > 0 ? tc.scan_step : (n_ljobs_ == 1 ? 8 : 4)) == 4 ? 4 : 8;
     perm_cu_ = std::max(0, env_int("MTE_PERMUTE_BLOCKS_PER_CU", tc.perm_cu > 0 ? tc.perm_cu : kPermuteBlocksPerCu));
-    L.rank_sets = rank_sets;
+    L.rank_cols = reinterpret_cast<const RankCol *>(tb + units_at + t_units);
+    L.n_rank_cols = (int)rank_cols.size();
+    L.wavelet_lds = wavelet_lds;
     L.max_rank_n = max_rank_n;
     L.rank_off = od + 3 * nj1 + 2 * (n_sets + 1);
     L.rank_waves = rank_off[n_ljobs_];
@@ -1606,17 +1644,21 @@ int Batch::launch_all(hipStream_t s, bool timed) {
         const hipEvent_t fork = timed ? ev[0] : fork_;
         if (!timed) MTE_HIP(hipEventRecord(fork_, s));
         if (launch_list_build(ll_, s)) return hip_fail(hipGetLastError(), "list build launch");
-        if (ll_.sortx && launch_list_sortx(ll_, s)) return hip_fail(hipGetLastError(), "X sort launch");
         if ((rc = end(kStageBuild, s))) return rc;
         MTE_HIP(hipStreamWaitEvent(side, fork, 0));
-        // the ranks of the one-Z-column sets come first: the permutation
-        // writes those sets' jobs' X in rank order
-        if (launch_list_rank_sort(ll_, side)) return hip_fail(hipGetLastError(), "rank launch");
+        // the ranks come first: the permutation writes the X of the jobs
+        // counted by ranks in rank order
+        if (launch_list_rank(ll_, side)) return hip_fail(hipGetLastError(), "rank launch");
         if ((rc = begin(side))) return rc;
-        // capped only while the permutation is the smaller part: a launch of
-        // many estimates over few list sets has more permutation than build
-        const int64_t pgrid = perm_cu_ > 0 && lpermute_blocks_ <= ll_.build_blocks ? (int64_t)perm_cu_ * ctx().n_cu : 0;
-        if (launch_permute(ljobs_dev_, n_ljobs_, lpermute_blocks_, lblk_off_, side, pgrid))
+        // capped only while the permutation is the smaller part (a launch of
+        // many estimates over few list sets has more permutation than build)
+        // and starts with the build: after the ranks it would outlast the
+        // build, which is short then (201 estimates at
+        // N = 9995, dz = 1: 709 us uncapped, 761 with 4 blocks per CU, 844 with 2)
+        const bool cap = perm_cu_ > 0 && lpermute_blocks_ <= ll_.build_blocks && ll_.n_rank_cols == 0;
+        const int64_t pgrid = cap ? (int64_t)perm_cu_ * ctx().n_cu : 0;
+        if (launch_permute_table(ljobs_dev_, n_ljobs_, lpermute_items_, litem_off_, lperm_rows_, side) ||
+            launch_permute(ljobs_dev_, n_ljobs_, lpermute_blocks_, lblk_off_, side, pgrid))
             return hip_fail(hipGetLastError(), "permute launch");
         if ((rc = end(kStagePermute, side))) return rc;
         // the scan's row order (launches of several jobs) is needed by the
@@ -1629,6 +1671,7 @@ int Batch::launch_all(hipStream_t s, bool timed) {
         MTE_HIP(hipStreamWaitEvent(s, join_at_end ? ev[1] : join_, 0));
         if ((rc = begin(s))) return rc;
         if (launch_list_scan(ll_, s)) return hip_fail(hipGetLastError(), "list scan launch");
+        if (launch_list_wavelet(ll_, s)) return hip_fail(hipGetLastError(), "wavelet count launch");
         if (launch_list_rank_count(ll_, s)) return hip_fail(hipGetLastError(), "rank count launch");
         if ((rc = end(kStageScan, s))) return rc;
         if ((rc = begin_after())) return rc;
