@@ -65,7 +65,11 @@ struct Job {
     // holds the same values estimate-major for the fallback).  The per-row
     // counts go to pk; eps and cnt are the caller's diagnostics ([n_est][n],
     // [n_est][3][n]) or null.
-    int set;
+    // A swapped job (swap) scans with the sides exchanged: set is a set over
+    // its X columns, row m stands for the row i with pi_e(i) = m, and xt holds
+    // that row's Z and Y (xt[0] the Z, xt[1] the Y column; sdx = 2 columns,
+    // else sdx = dx).  rset is the set of its (Y, Z) sample (= set otherwise).
+    int set, rset, swap, sdx;
     float *xt;
     int theiler;                  // Theiler window w: pairs with |i - j| <= w are left out
     int reps;                     // replications R (rows: R blocks of n/R, replication-major)
@@ -84,7 +88,7 @@ struct Job {
     // each row's source row (xw[e][i] = pi_e(i), [n_est][n], followed by
     // [n_est][n] words for the ranks in rank order), and each pair's radius (low word, -1
     // for a pair left to the all-rows redo) and n_yz from the scan, by rank
-    // (er[e][r]); null otherwise
+    // (er[e][r]), of a swapped job n_xz, by row m (er[e][m]); null otherwise
     const int32_t *zrank;
     float *xr;
     const int32_t *xrank;
@@ -136,6 +140,18 @@ struct ListSet {
     float *zs;
     int32_t *zord;
     int32_t *zrank;
+    // for swapped jobs (Job::swap): y sorted, and each row's rank in y
+    float *ys;
+    int32_t *yrank;
+};
+
+// A run of list sets built by one kernel form: compiled dimensions (dz Z
+// columns and one Y column) or, dz = 0, the generic form; qb rows per block;
+// pack: 16-bit packed histograms (every set has N <= 2^16).
+struct BuildPart {
+    int set0 = 0, set1 = 0;
+    int dz = 0, qb = 0, pack = 0;
+    int64_t block0 = 0, blocks = 0;
 };
 
 constexpr int kCoopLanes = 4;                 // default cooperative-finish threshold of the scan
@@ -145,7 +161,7 @@ constexpr int kRankListCap = 8;               // Z-list capacity of a set counte
 constexpr int kBuildRows = 2;                // rows per build block when N <= 2^16
 constexpr int kLeanRows = 2;                 // rows per block of the compiled-dimension build
 // Compiled-dimension build: dz <= kBuildFixedDz Z columns and one Y column.
-constexpr int kBuildFixedDz = 12;
+constexpr int kBuildFixedDz = 15;
 constexpr int kXcds = 8;   // accelerator complex dies (one L2 each) of an MI355X
 constexpr int kBuildCopies = 1;              // histogram copies per row (spread LDS atomics)
 constexpr int kListStatWord = 16;
@@ -194,12 +210,6 @@ struct ListLaunch {
     const int64_t *row_off;       // [n_sets+1] prefix sums of the sets' n
     const int64_t *build_off;     // [n_sets+1] prefix sums of the build blocks per set
     int64_t build_blocks;
-    int build_qb;                 // rows per build block: kBuildRows (N <= 2^16) or 1
-    int build_pack;               // 16-bit packed histograms (every set has N <= 2^16)
-    int build_dz;                 // > 0: every set has this many Z columns and one Y column
-                                  // (the build's compiled-dimension forms)
-    int build_kind;               // 0 generic dimensions (list_build_kernel); 1 compiled
-                                  // dimensions (list_build_dz_kernel)
     int stats;                    // non-zero: the scan accumulates its entry counts
     const int64_t *est_off;       // [n_jobs+1] prefix sums of n_est
     int n_jobs, n_sets;
@@ -211,6 +221,7 @@ struct ListLaunch {
                                   // scan, Z-list scan); kListCounterWords words, zeroed
                                   // per launch
     int kmax, dxm;                // compile-time classes of the scan kernel
+    int rank_dxm;                 // largest dx of the jobs counted over rank ranges
     int fb_grid;                  // blocks of the fallback kernel
     int max_chunks;               // largest ceil(n / kChunk) of the jobs (reduction grid)
     int coop_lanes;               // the scan finishes cooperatively once this many lanes remain
@@ -297,7 +308,7 @@ int launch_main(int variant, const Job *jobs_dev, int n_jobs, const int64_t *a_o
 
 int launch_list_zy(const ListLaunch &L, void *stream);      // the sets' contiguous Y,Z copies; clears the counters
 int launch_list_order(const ListLaunch &L, void *stream);  // the scan's row order (several jobs)
-int launch_list_build(const ListLaunch &L, void *stream);
+int launch_list_build(const ListLaunch &L, const BuildPart &P, void *stream);
 int launch_list_scan(const ListLaunch &L, void *stream);
 int launch_list_rank(const ListLaunch &L, void *stream);        // ranks of the columns in rank_cols
 int launch_list_rank_count(const ListLaunch &L, void *stream);  // counts of the ranked sets' jobs over rank ranges

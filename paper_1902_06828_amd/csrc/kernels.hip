@@ -104,9 +104,14 @@ __device__ __forceinline__ void store_row(const Job &J, int e, int64_t i, int64_
     const int gl = e - scan_group_first(gg, gE);
     const int64_t ri = J.xr ? (int64_t)min(max(J.zrank[i], 0), J.n - 1) : 0;
     if (J.xw) J.xw[(int64_t)e * J.n + i] = (uint16_t)x;
+    if (J.swap) {
+        // row x of the swapped scan stands for row i: its Z and Y
+        for (int c = 0; c < 2; ++c)
+            J.xt[(((int64_t)c * gG + gg) * J.n + x) * kScanLanes + gl] = J.cols[J.dx + 1 - c][i];
+    }
     for (int c = 0; c < J.dx; ++c) {
         const float v = J.cols[c][x];
-        if (J.xt) J.xt[(((int64_t)c * gG + gg) * J.n + i) * kScanLanes + gl] = v;
+        if (J.xt && !J.swap) J.xt[(((int64_t)c * gG + gg) * J.n + i) * kScanLanes + gl] = v;
         J.xp[((int64_t)e * J.dx + c) * J.n + i] = v;
         if (J.xr) J.xr[((int64_t)e * J.dx + c) * J.n + ri] = v;
     }

@@ -296,7 +296,7 @@ __global__ __launch_bounds__(kBT) void list_build_kernel(const ListSet *__restri
     __builtin_amdgcn_s_setprio(kBuildPrio);
     const int tid = tid_x();
     const int copy = tid & (C - 1);
-    const int64_t b = bid_x();
+    const int64_t b = bid_x() + blk_off[0];
     if (tid == 0) sm.set = find_job(blk_off, n_sets, b);
     for (int x = tid; x < QB * C * Sm::kCopy; x += kBT) (&sm.h[0][0][0])[x] = 0u;
     __syncthreads();
@@ -471,7 +471,7 @@ __global__ __launch_bounds__(kBT) void list_build_dz_kernel(const ListSet *__res
     __shared__ LeanSmem<QB> sm;
     __builtin_amdgcn_s_setprio(kBuildPrio);
     const int tid = tid_x(), lane = tid & 63, wave = tid >> 6;
-    const int64_t b = bid_x();
+    const int64_t b = bid_x() + blk_off[0];
     if (tid == 0) sm.set = find_job(blk_off, n_sets, b);
     for (int x = tid; x < QB * kKeyBins; x += kBT) (&sm.h[0][0])[x] = 0u;
     __syncthreads();
@@ -973,7 +973,8 @@ __global__ __launch_bounds__(kScanLanes) void list_scan_kernel(const ListLaunch 
     const int jb = U->job, grp = U->group, il = U->row0 + at;
     Const<Job> *J = as_const(L.jobs) + jb;
     Const<ListSet> *S = as_const(L.sets) + J->set;
-    const int n = J->n, E = J->n_est, dx = J->dx;
+    const int n = J->n, E = J->n_est, dx = J->sdx;
+    const bool swap = J->swap;
     const int i = S->order ? as_const(S->order)[il] : il;
     const int e0 = scan_group_first(grp, E), ne = scan_group_first(grp + 1, E) - e0;
     const bool live = lane < ne;
@@ -1001,10 +1002,11 @@ __global__ __launch_bounds__(kScanLanes) void list_scan_kernel(const ListLaunch 
         for (int u = 0; u < KU; ++u) v[u] = xval(0, s.j[u], loff);
     };
     // max-norm over the X columns between the lane's row and a step's rows
-    auto xdist = [&](const Step<KU> &s, const float (&v0)[KU], float (&d)[KU]) {
+    // (the first cd of them)
+    auto xdist = [&](const Step<KU> &s, const float (&v0)[KU], float (&d)[KU], int cd) {
 #pragma unroll
         for (int u = 0; u < KU; ++u) d[u] = absdiff(xq[0], v0[u]);
-        Unroll<1, DXM>::upto(dx, [&](auto cc) {
+        Unroll<1, DXM>::upto(cd, [&](auto cc) {
             constexpr int c = decltype(cc)::value;
             float v[KU];
 #pragma unroll
@@ -1014,10 +1016,10 @@ __global__ __launch_bounds__(kScanLanes) void list_scan_kernel(const ListLaunch 
         });
     };
     // the same between row i and one row per lane under lane o's estimate
-    auto coop_xdist = [&](int o, uint32_t j) {
+    auto coop_xdist = [&](int o, uint32_t j, int cd) {
         const uint32_t oo = (uint32_t)o * 4u;
         float d = absdiff(bcast(xq[0], o), xval(0, j, oo));
-        Unroll<1, DXM>::upto(dx, [&](auto cc) {
+        Unroll<1, DXM>::upto(cd, [&](auto cc) {
             constexpr int c = decltype(cc)::value;
             d = fmax_(d, absdiff(bcast(xq[c], o), xval(c, j, oo)));
         });
@@ -1047,7 +1049,7 @@ __global__ __launch_bounds__(kScanLanes) void list_scan_kernel(const ListLaunch 
             load_step(p + 2 * (m1 + 2 * KU), nxt2);
             __builtin_amdgcn_sched_barrier(0);
             float d[KU];
-            xdist(cur, v, d);
+            xdist(cur, v, d, dx);
             float dmin = inf_f();
 #pragma unroll
             for (int u = 0; u < KU; ++u) {
@@ -1081,7 +1083,7 @@ __global__ __launch_bounds__(kScanLanes) void list_scan_kernel(const ListLaunch 
             const float stop = bucket_floor(bcast(en.d, 63));
             for (uint64_t rest = open; rest; rest &= rest - 1) {
                 const int o = lowest(rest);
-                float d = fmax_(coop_xdist(o, (uint32_t)en.j), en.d);
+                float d = fmax_(coop_xdist(o, (uint32_t)en.j, dx), en.d);
                 if (p + lane >= end) d = inf_f();
                 // +inf leaves the other lanes' lists as they are
                 for (uint64_t cand = cmp_mask(d < bcast(top[KMAX - 1], o)); cand; cand &= cand - 1) {
@@ -1099,7 +1101,7 @@ __global__ __launch_bounds__(kScanLanes) void list_scan_kernel(const ListLaunch 
 
     // n_yz: list 1 below eps
     int cxz = 0, cyz = 0, cz = 0;
-    {
+    if (!swap) {
         Const<uint32_t> *p = as_const(reinterpret_cast<const uint32_t *>(l1));
         open = dec;
         int m = 0;
@@ -1134,11 +1136,14 @@ __global__ __launch_bounds__(kScanLanes) void list_scan_kernel(const ListLaunch 
 
     // n_z and n_xz from list 2 below eps (every row with d_z < eps is listed
     // when eps <= its bound); a job of a set counted by ranks takes them from
-    // the rank-count kernel
+    // the rank-count kernel.  A swapped job counts n_xz on its X list, with the
+    // Z column alone
     const bool noz = J->dz == 0, ranked = J->er != nullptr;
-    if (!noz && !ranked) {
-        const int len2 = as_const(S->len)[2 * (int64_t)i + 1];
-        Const<uint32_t> *p = as_const(reinterpret_cast<const uint32_t *>(l2));
+    const int cd = swap ? 1 : dx;
+    if (swap || (!noz && !ranked)) {
+        const LEnt *lc = swap ? l1 : l2;
+        const int len2 = swap ? len1 : as_const(S->len)[2 * (int64_t)i + 1];
+        Const<uint32_t> *p = as_const(reinterpret_cast<const uint32_t *>(lc));
         const uint64_t want = dec;
         open = want;
         int m2 = 0;
@@ -1154,7 +1159,7 @@ __global__ __launch_bounds__(kScanLanes) void list_scan_kernel(const ListLaunch 
             load_step(p + 2 * (m2 + 2 * KU), nxt2);
             __builtin_amdgcn_sched_barrier(0);
             float d[KU];
-            xdist(cur, v, d);
+            xdist(cur, v, d, cd);
 #pragma unroll
             for (int u = 0; u < KU; ++u) {
                 cz += cur.d[u] < eps;
@@ -1172,16 +1177,16 @@ __global__ __launch_bounds__(kScanLanes) void list_scan_kernel(const ListLaunch 
         dec = want & ~open;
         if (open && m2 <= len2) {
             const int end = len2 + kListPad;
-            LEnt nx = l2[min(m2 + lane, end - 1)];
+            LEnt nx = lc[min(m2 + lane, end - 1)];
             for (int c = m2; open && c < end; c += 64) {
                 const LEnt en = nx;
-                nx = l2[min(c + 64 + lane, end - 1)];
+                nx = lc[min(c + 64 + lane, end - 1)];
                 const float stop = bucket_floor(bcast(en.d, 63));
                 const uint64_t in = cmp_mask(c + lane < end);
                 for (uint64_t rest = open; rest; rest &= rest - 1) {
                     const int o = lowest(rest);
                     const float pe = bcast(eps, o);
-                    const float dv = coop_xdist(o, (uint32_t)en.j);
+                    const float dv = coop_xdist(o, (uint32_t)en.j, cd);
                     const int qz = __builtin_popcountll(in & cmp_mask(en.d < pe));
                     const int qxz = __builtin_popcountll(in & cmp_mask(fmax_(dv, en.d) < pe));
                     cz += lane == o ? qz : 0;
@@ -1223,14 +1228,16 @@ __global__ __launch_bounds__(kScanLanes) void list_scan_kernel(const ListLaunch 
     }
     if (live) {
         const int64_t at_e = (int64_t)e * n + i;
-        // a ranked pair hands its radius and n_yz over, by the rank of its row
+        // a ranked pair hands its radius and n_yz over, by the rank of its row;
+        // a swapped one its radius and n_xz, by the row it stands at (its
+        // count kernel queues it for the redo)
         if (ranked)
-            J->er[(int64_t)e * n + as_const(J->zrank)[i]] =
-                decided ? ((uint64_t)(uint32_t)cyz << 32) | __float_as_uint(eps) : kRankNone;
-        if (!decided) {
+            J->er[(int64_t)e * n + (swap ? i : as_const(J->zrank)[i])] =
+                decided ? ((uint64_t)(uint32_t)(swap ? cxz : cyz) << 32) | __float_as_uint(eps) : kRankNone;
+        if (!decided && !swap) {
             const uint32_t pos = atomicAdd(&L.counters[0], 1u);
             L.failq[pos] = ((uint64_t)jb << 40) | ((uint64_t)i * E + e);
-        } else if (!ranked) {
+        } else if (decided && !ranked) {
             J->pk[at_e] = pack_counts(cxz, cyz, cz);
             if (J->eps) J->eps[at_e] = eps;
             if (J->cnt) {
@@ -1268,7 +1275,7 @@ __global__ __launch_bounds__(kRankThreads) void list_rank_count_kernel(const Lis
     if (w >= L.rank_waves) return;
     const int jb = find_job(L.rank_off, L.n_jobs, w);
     const Job &J = L.jobs[jb];
-    const ListSet &S = L.sets[J.set];
+    const ListSet &S = L.sets[J.rset];
     const int n = J.n, dx = J.dx;
     const int nt = (n + 63) / 64;
     const int64_t loc = w - L.rank_off[jb];
@@ -1393,7 +1400,9 @@ __global__ __launch_bounds__(kRankThreads) void list_rank_count_kernel(const Lis
 // n_xz of the pairs of a set with one Z column, one X column and no Theiler
 // window: the rows of ranks [lo, hi) in z whose x lies within eps of x_i are,
 // in ranks of x, those in [a, b) (two more binary searches, on the job's
-// sorted X).  One block per estimate keeps the wavelet matrix of the sequence
+// sorted X).  Of a swapped job the scan has counted n_xz, and the same
+// structure over y (its sequence is the same for all estimates) gives n_yz.
+// One block per estimate keeps the wavelet matrix of the sequence
 // "rank of x by rank of z" in LDS: per bit of the rank, from the top, a bit
 // vector with running counts, the sequence stably partitioned by that bit
 // from level to level.  A pair's count then takes one walk over the levels
@@ -1418,7 +1427,8 @@ __global__ __launch_bounds__(kWvThreads) void list_wavelet_kernel(const ListLaun
     const int jb = __builtin_amdgcn_readfirstlane(find_job(L.est_off, L.n_jobs, g));
     Const<Job> *J = as_const(L.jobs) + jb;
     if (!J->xw) return;                       // counted elsewhere (uniform in the block)
-    Const<ListSet> *S = as_const(L.sets) + J->set;
+    Const<ListSet> *S = as_const(L.sets) + J->rset;
+    const bool swap = J->swap;
     const int n = J->n, e = (int)(g - as_const(L.est_off)[jb]);
     const int tid = tid_x(), lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1431,7 +1441,7 @@ __global__ __launch_bounds__(kWvThreads) void list_wavelet_kernel(const ListLaun
     // source row of each row and rank of each source row, then the sequence
     const uint16_t *src = J->xw + (int64_t)e * n;
     uint16_t *xw = J->xw + (int64_t)(J->n_est + e) * n;
-    const int32_t *xrank = J->xrank;
+    const int32_t *xrank = swap ? S->yrank : J->xrank;
     for (int q = tid; q < n; q += kWvThreads) {
         sa[q] = src[q];
         sb[q] = (uint16_t)xrank[q];
@@ -1441,7 +1451,10 @@ __global__ __launch_bounds__(kWvThreads) void list_wavelet_kernel(const ListLaun
     const int blk0 = wave * per, blk1 = min(nblk, blk0 + per);
     for (int blk = blk0; blk < blk1; ++blk) {
         const int p = blk * 64 + lane;
-        if (p < n) xw[p] = sb[min((int)sa[min(max(zord[p], 0), n - 1)], n - 1)];
+        if (p < n) {
+            const int i = min(max(zord[p], 0), n - 1);
+            xw[p] = sb[swap ? i : min((int)sa[i], n - 1)];
+        }
     }
     __syncthreads();
     for (int blk = blk0; blk < blk1; ++blk) {
@@ -1490,7 +1503,7 @@ __global__ __launch_bounds__(kWvThreads) void list_wavelet_kernel(const ListLaun
         sb = t;
     }
     // the sorted X column takes the sequence's place
-    const float *xsg = J->xs;
+    const float *xsg = swap ? S->ys : J->xs;
     for (int q = tid; q < n; q += kWvThreads) xs[q] = gload(xsg, (uint32_t)q);
     __syncthreads();
 
@@ -1501,7 +1514,9 @@ __global__ __launch_bounds__(kWvThreads) void list_wavelet_kernel(const ListLaun
         return (int)w.ones + __builtin_popcount(w.bits & ((1u << (p & 31)) - 1u));
     };
     for (int r = tid; r < n; r += kWvThreads) {
-        const uint64_t word = er[r];
+        const int i = min(max(zord[r], 0), n - 1);
+        const int m0 = swap ? min((int)src[i], n - 1) : r;
+        const uint64_t word = er[m0];
         const float eps = __uint_as_float((uint32_t)word);
         const float zq = gload(zs, (uint32_t)r), xq = xs[min((int)xw[r], n - 1)];
         // ranks of z within eps, then ranks of x
@@ -1555,14 +1570,21 @@ __global__ __launch_bounds__(kWvThreads) void list_wavelet_kernel(const ListLaun
                 ra -= ra1;
             }
         }
-        if (!(eps >= 0.f)) continue;          // in the redo queue
+        if (!(eps >= 0.f)) {                  // in the redo queue, a swapped pair from here
+            if (swap) {
+                const uint32_t pos = atomicAdd(&L.counters[0], 1u);
+                L.failq[pos] = ((uint64_t)jb << 40) | ((uint64_t)i * J->n_est + e);
+            }
+            continue;
+        }
         // the pair's own row is in the range and within eps exactly when eps > 0
         const int own = eps > 0.f ? 1 : 0;
-        const int i = min(max(zord[r], 0), n - 1), cyz = (int)(word >> 32);
-        J->pk[(int64_t)e * n + i] = pack_counts(cnt - own, cyz, hi - lo - own);
+        const int other = (int)(word >> 32), ct = cnt - own;
+        const int cxz = swap ? other : ct, cyz = swap ? ct : other;
+        J->pk[(int64_t)e * n + i] = pack_counts(cxz, cyz, hi - lo - own);
         if (J->eps) J->eps[(int64_t)e * n + i] = eps;
         if (J->cnt) {
-            J->cnt[((int64_t)e * 3 + 0) * n + i] = cnt - own;
+            J->cnt[((int64_t)e * 3 + 0) * n + i] = cxz;
             J->cnt[((int64_t)e * 3 + 1) * n + i] = cyz;
             J->cnt[((int64_t)e * 3 + 2) * n + i] = hi - lo - own;
         }
@@ -1829,6 +1851,11 @@ void *scan_fn(int step) {
                      : reinterpret_cast<void *>(&list_scan_kernel<KMAX, DXM, 8>);
 }
 
+template <int KMAX>
+void *scan_dx(int dxm, int step) {
+    return dxm == 1 ? scan_fn<KMAX, 1>(step) : dxm == 2 ? scan_fn<KMAX, 2>(step) : scan_fn<KMAX, kMaxDx>(step);
+}
+
 }  // namespace
 
 int launch_list_zy(const ListLaunch &L, void *stream) {
@@ -1850,28 +1877,26 @@ void *lean_fn(int dz, std::integer_sequence<int, D...>) {
     return dz >= 0 && dz <= (int)sizeof...(D) ? fns[dz] : nullptr;
 }
 
-int launch_list_build(const ListLaunch &L, void *stream) {
-    if (L.build_blocks <= 0) return 0;
-    if (L.build_kind == 1) {
-        void *fn = L.build_qb == 4 ? lean_fn<4>(L.build_dz, std::make_integer_sequence<int, kBuildFixedDz>{})
-                                   : lean_fn<kBuildRows>(L.build_dz, std::make_integer_sequence<int, kBuildFixedDz>{});
+int launch_list_build(const ListLaunch &L, const BuildPart &P, void *stream) {
+    if (P.blocks <= 0) return 0;
+    // the part's sets and their block offsets (absolute: a kernel subtracts
+    // the first)
+    const ListSet *sets = L.sets + P.set0;
+    int n_sets = P.set1 - P.set0;
+    const int64_t *off = L.build_off + P.set0;
+    const dim3 grid((unsigned)P.blocks), block(kBT);
+    if (P.dz > 0) {
+        void *fn = P.qb == 4 ? lean_fn<4>(P.dz, std::make_integer_sequence<int, kBuildFixedDz>{})
+                             : lean_fn<kBuildRows>(P.dz, std::make_integer_sequence<int, kBuildFixedDz>{});
         if (!fn) return -1;
-        const ListSet *sets = L.sets;
-        int n_sets = L.n_sets;
-        const int64_t *off = L.build_off;
         void *args[] = {(void *)&sets, (void *)&n_sets, (void *)&off};
-        return hipLaunchKernel(fn, dim3((unsigned)L.build_blocks), dim3(kBT), args, 0, (hipStream_t)stream) ==
-                       hipSuccess
-                   ? 0
-                   : -1;
+        return hipLaunchKernel(fn, grid, block, args, 0, (hipStream_t)stream) == hipSuccess ? 0 : -1;
     }
-    const dim3 grid((unsigned)L.build_blocks), block(kBT);
-    if (L.build_pack && L.build_qb == kBuildRows)
+    if (P.pack && P.qb == kBuildRows)
         hipLaunchKernelGGL((list_build_kernel<kBuildRows, kBuildCopies, true>), grid, block, 0,
-                           (hipStream_t)stream, L.sets, L.n_sets, L.build_off);
-    else if (!L.build_pack && L.build_qb == 1)
-        hipLaunchKernelGGL((list_build_kernel<1, 1, false>), grid, block, 0, (hipStream_t)stream, L.sets,
-                           L.n_sets, L.build_off);
+                           (hipStream_t)stream, sets, n_sets, off);
+    else if (!P.pack && P.qb == 1)
+        hipLaunchKernelGGL((list_build_kernel<1, 1, false>), grid, block, 0, (hipStream_t)stream, sets, n_sets, off);
     else
         return -1;
     return hipGetLastError() == hipSuccess ? 0 : -1;
@@ -1880,11 +1905,10 @@ int launch_list_build(const ListLaunch &L, void *stream) {
 int launch_list_scan(const ListLaunch &L, void *stream) {
     if (L.lanes <= 0) return 0;
     void *fn = nullptr;
-    const bool wide = L.dxm > 1;
     const int st = L.scan_step;
-    if (L.kmax == 4) fn = wide ? scan_fn<4, kMaxDx>(st) : scan_fn<4, 1>(st);
-    else if (L.kmax == 8) fn = wide ? scan_fn<8, kMaxDx>(st) : scan_fn<8, 1>(st);
-    else if (L.kmax == 16) fn = wide ? scan_fn<16, kMaxDx>(st) : scan_fn<16, 1>(st);
+    if (L.kmax == 4) fn = scan_dx<4>(L.dxm, st);
+    else if (L.kmax == 8) fn = scan_dx<8>(L.dxm, st);
+    else if (L.kmax == 16) fn = scan_dx<16>(L.dxm, st);
     else return -1;
     ListLaunch arg = L;
     void *args[] = {(void *)&arg};
@@ -1931,7 +1955,7 @@ int launch_list_wavelet(const ListLaunch &L, void *stream) {
 int launch_list_rank_count(const ListLaunch &L, void *stream) {
     if (L.rank_waves <= 0) return 0;
     const int64_t blocks = (L.rank_waves + kRankThreads / 64 - 1) / (kRankThreads / 64);
-    if (L.dxm > 1)
+    if (L.rank_dxm > 1)
         hipLaunchKernelGGL(list_rank_count_kernel<kMaxDx>, dim3((unsigned)blocks), dim3(kRankThreads), 0,
                            (hipStream_t)stream, L);
     else

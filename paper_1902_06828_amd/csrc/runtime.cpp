@@ -967,16 +967,113 @@ static void list_caps(int dx, int dy, int dz, int n, int *m1, int *m2) {
     }
 }
 
+// Geometry of a launch's list sets.
+struct SetSpec {
+    const float *cols[kMaxDy + kMaxDz];   // Y columns, then Z columns
+    int n = 0, dy = 0, dz = 0, theiler = 0;
+    int cap1 = 0, cap2 = 0;
+    int ranked = 0;     // counted by ranks of z
+    int rank_y = 0;     // y ranked too (swapped jobs)
+    int lists = 1;      // some job scans its lists
+    int job = -1;       // the swapped job whose X columns it holds
+};
+
+// List capacity of a swapped job's set: the k-NN distances of dx + 2 columns
+// lie within a prefix of its X lists of 223, 111 and 70 entries on average for
+// 2, 3 and 4 columns (N = 9995, autoregressive series), 1802, 1248 and 772 at
+// the 99.9th percentile.
+constexpr int kSwapListCap = 2048;
+
+// The sets of a launch: the jobs' (Y, Z) samples (rset_of), and one per
+// swapped job.  A sample with one Z column and one Y column is counted by
+// ranks of z (MTE_RANK_COUNTS=0 keeps it on the Z list, for comparison).  Its
+// jobs with several X columns and no Theiler window are swapped: the estimate
+// is the same with the roles of the two sides exchanged (X in place, Y and Z
+// permuted by the inverse), and lists over the dx X columns hold far fewer
+// rows below a radius than lists over (Y, Z): at N = 9995, 201 estimates and 4
+// X columns a pair reads 70 entries of 2 permuted columns instead of 1139 of
+// 4, and then 70 instead of about 2900 rows for n_xz: 26.9 -> 1.05 ms a test.
+// Sets of the same number
+// of Z columns follow one another (the build's parts).
+static void list_caps(int dx, int dy, int dz, int n, int *m1, int *m2);
+static std::vector<SetSpec> plan_sets(const std::vector<JobSpec> &specs, int n_rsets, std::vector<int> *rset_io) {
+    const std::vector<int> rset_of = *rset_io;
+    const char *rk_env = std::getenv("MTE_RANK_COUNTS");
+    const bool rank_on = !(rk_env && *rk_env == '0');
+    std::vector<SetSpec> sets((size_t)n_rsets);
+    std::vector<int> dxmax((size_t)n_rsets, 0);
+    for (size_t j = 0; j < specs.size(); ++j) {
+        const JobSpec &sp = specs[j];
+        SetSpec &S = sets[(size_t)rset_of[j]];
+        if (S.n == 0) {
+            for (int c = 0; c < sp.dy + sp.dz; ++c) S.cols[c] = sp.cols[sp.dx + c];
+            S.n = sp.n;
+            S.dy = sp.dy;
+            S.dz = sp.dz;
+            S.theiler = sp.theiler;
+            S.ranked = rank_on && sp.dz == 1 && sp.dy == 1 && sp.n <= kRankMaxN;
+            S.lists = 0;
+        }
+        const bool swap = S.ranked && sp.dx >= 2 && sp.theiler == 0 && list_wavelet_lds(sp.n) > 0;
+        if (!swap) {
+            S.lists = 1;
+            dxmax[(size_t)rset_of[j]] = std::max(dxmax[(size_t)rset_of[j]], sp.dx);
+            continue;
+        }
+        S.rank_y = 1;
+        SetSpec F;
+        // X columns: the last one in Y's place, the others in Z's
+        F.cols[0] = sp.cols[sp.dx - 1];
+        for (int c = 0; c + 1 < sp.dx; ++c) F.cols[1 + c] = sp.cols[c];
+        F.n = sp.n;
+        F.dy = 1;
+        F.dz = sp.dx - 1;
+        F.job = (int)j;
+        int a, b;
+        list_caps(sp.dx, 1, 1, sp.n, &a, &b);   // (its override, else the capacity below)
+        const char *v = std::getenv("MTE_LIST_CAP");
+        F.cap1 = v && *v ? a : kSwapListCap;
+        F.cap2 = kRankListCap;
+        sets.push_back(F);
+    }
+    for (int t = 0; t < n_rsets; ++t) {
+        SetSpec &S = sets[(size_t)t];
+        list_caps(dxmax[(size_t)t], S.dy, S.dz, S.n, &S.cap1, &S.cap2);
+        if (S.ranked) S.cap2 = kRankListCap;
+    }
+    // in order of the build's forms (sets without lists take no part)
+    std::vector<int> order(sets.size()), pos(sets.size());
+    for (size_t t = 0; t < sets.size(); ++t) order[t] = (int)t;
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
+        return std::make_tuple(sets[(size_t)a].dy, sets[(size_t)a].dz, sets[(size_t)a].n >= 65536) <
+               std::make_tuple(sets[(size_t)b].dy, sets[(size_t)b].dz, sets[(size_t)b].n >= 65536);
+    });
+    std::vector<SetSpec> out;
+    for (size_t t = 0; t < sets.size(); ++t) {
+        out.push_back(sets[(size_t)order[t]]);
+        pos[(size_t)order[t]] = (int)t;
+    }
+    for (int &r : *rset_io) r = pos[(size_t)r];
+    return out;
+}
+
 constexpr int kPermTablePerCu = 2;   // estimates per CU from which the permutations run as tables
 constexpr int kUnitsPerXcd = 4;   // fewest scan units per XCD for the XCD-dealt order
 
-int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<int> &set_of, int n_sets,
+int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<int> &sample_of, int n_samples,
                          const TileChoice &tc, hipStream_t s, size_t *measure) {
     Ctx &c = ctx();
     n_ljobs_ = (int)specs.size();
     std::vector<Job> jobs(n_ljobs_);
+    std::vector<int> rset_of = sample_of;
+    const std::vector<SetSpec> geo = plan_sets(specs, n_samples, &rset_of);
+    const int n_sets = (int)geo.size();
     std::vector<ListSet> sets(n_sets);
-    std::vector<int> set_rep(n_sets, -1);
+    // the set a job scans: a swapped job's own, else its (Y, Z) sample's
+    std::vector<int> set_of = rset_of;
+    for (int t = 0; t < n_sets; ++t)
+        if (geo[t].job >= 0) set_of[geo[t].job] = t;
+    auto swapped = [&](int j) { return set_of[j] != rset_of[j]; };
     std::vector<int64_t> lane_off(n_ljobs_ + 1, 0), est_off(n_ljobs_ + 1, 0), blk_off(n_ljobs_ + 1, 0),
         row_off(n_sets + 1, 0), build_off(n_sets + 1, 0), item_off(n_ljobs_ + 1, 0);
     lperm_rows_ = 0;
@@ -986,7 +1083,6 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     for (const JobSpec &sp : specs) total_est += sp.n_est();
     for (int j = 0; j < n_ljobs_; ++j) {
         const JobSpec &sp = specs[j];
-        if (set_rep[set_of[j]] < 0) set_rep[set_of[j]] = j;
         lane_off[j + 1] = lane_off[j] + (int64_t)sp.n * sp.n_est();
         est_off[j + 1] = est_off[j] + sp.n_est();
         // many short permutations run as swaps of a table in LDS; few of them
@@ -998,7 +1094,7 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
         item_off[j + 1] = item_off[j] + (table ? (int64_t)sp.n_est() * sp.reps : 0);
         if (table) lperm_rows_ = std::max(lperm_rows_, sp.n / sp.reps);
         kmax = std::max(kmax, sp.k);
-        dxm = std::max(dxm, sp.dx);
+        dxm = std::max(dxm, swapped(j) ? 2 : sp.dx);
         n_keys += sp.n_est();
     }
     // scan units: every job's groups, cut into row ranges and dealt to the
@@ -1040,40 +1136,33 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     // scratch layout: per set its lists and Y,Z copy; per job xt, xp, the
     // packed counts and the chunk sums; then the queue
     size_t bytes = 0;
-    int nmax_set = 0;
     std::vector<size_t> o_l1(n_sets), o_l2(n_sets), o_len(n_sets), o_bound(n_sets), o_zy(n_sets),
         o_order(n_sets, 0), o_rank(n_sets, 0);
-    std::vector<int> set_dx(n_sets, 0);
-    for (int j = 0; j < n_ljobs_; ++j) set_dx[set_of[j]] = std::max(set_dx[set_of[j]], specs[j].dx);
-    // sets with one Z column and one Y column are counted by ranks of z
-    // (MTE_RANK_COUNTS=0 keeps them on the Z list, for comparison)
-    const char *rk_env = std::getenv("MTE_RANK_COUNTS");
-    const bool rank_on = !(rk_env && *rk_env == '0');
-    std::vector<char> ranked(n_sets, 0);
     int max_rank_n = 0;
     for (int t = 0; t < n_sets; ++t) {
-        const JobSpec &sp = specs[set_rep[t]];
-        ranked[t] = rank_on && sp.dz == 1 && sp.dy == 1 && sp.n <= kRankMaxN;
-        if (ranked[t]) max_rank_n = std::max(max_rank_n, sp.n);
-    }
-    for (int t = 0; t < n_sets; ++t) {
-        const JobSpec &sp = specs[set_rep[t]];
+        const SetSpec &sp = geo[t];
         ListSet &S = sets[t];
         std::memset(&S, 0, sizeof S);
-        int cap1 = 0, cap2 = 0;
-        list_caps(set_dx[t], sp.dy, sp.dz, sp.n, &cap1, &cap2);
-        if (ranked[t]) cap2 = kRankListCap;
-        for (int cc = 0; cc < sp.dy + sp.dz; ++cc) S.cols[cc] = sp.cols[sp.dx + cc];
+        for (int cc = 0; cc < sp.dy + sp.dz; ++cc) S.cols[cc] = sp.cols[cc];
         S.n = sp.n;
         S.dy = sp.dy;
         S.dz = sp.dz;
         S.theiler = sp.theiler;
-        S.m1 = std::min(sp.n - 1, cap1);
-        S.m2 = std::min(sp.n - 1, cap2);
+        // rank arrays: zs, zord, zrank, for swapped jobs ys and yrank (n words
+        // each), and each ranked column's partial counts
+        if (sp.ranked) {
+            max_rank_n = std::max(max_rank_n, sp.n);
+            o_rank[t] = bytes;
+            bytes = align_up(bytes + (3 + kRankParts + (sp.rank_y ? 2 + kRankParts : 0)) * sizeof(float) * (size_t)sp.n,
+                             256);
+        }
+        row_off[t + 1] = row_off[t];
+        if (!sp.lists) continue;              // only its ranks are needed
+        S.m1 = std::min(sp.n - 1, sp.cap1);
+        S.m2 = std::min(sp.n - 1, sp.cap2);
         S.s1 = S.m1 + kListPad;
         S.s2 = S.m2 + kListPad;
-        row_off[t + 1] = row_off[t] + sp.n;
-        nmax_set = std::max(nmax_set, sp.n);
+        row_off[t + 1] += sp.n;
         // kListPad spare entries after each array: the scan loads one step
         // ahead, up to kListPad entries past the last row's sentinels
         o_l1[t] = bytes;
@@ -1093,42 +1182,42 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
             o_order[t] = bytes;
             bytes = align_up(bytes + sizeof(int32_t) * (size_t)sp.n, 256);
         }
-        // rank arrays: zs, zord, zrank (n words each), then the partial counts
-        if (ranked[t]) {
-            o_rank[t] = bytes;
-            bytes = align_up(bytes + (3 + kRankParts) * sizeof(float) * (size_t)sp.n, 256);
-        }
     }
     struct Off { size_t xt, xp, pk, xs, chunk, xr, er; bool wavelet; };
     std::vector<Off> offs(n_ljobs_);
     std::vector<int64_t> rank_off(n_ljobs_ + 1, 0);
     size_t wavelet_lds = 0;
-    int n_rank_cols = 0;
-    for (int t = 0; t < n_sets; ++t) n_rank_cols += ranked[t];
+    int n_rank_cols = 0, rdxm = 1;
+    for (int t = 0; t < n_sets; ++t) n_rank_cols += geo[t].ranked + geo[t].rank_y;
     for (int j = 0; j < n_ljobs_; ++j) {
         const JobSpec &sp = specs[j];
         const size_t pairs = (size_t)sp.n * sp.n_est();
         offs[j].xt = bytes;
-        bytes = align_up(bytes + sizeof(float) * (size_t)sp.n * kScanLanes * scan_groups(sp.n_est()) * sp.dx, 256);
+        bytes = align_up(bytes + sizeof(float) * (size_t)sp.n * kScanLanes * scan_groups(sp.n_est()) * (swapped(j) ? 2 : sp.dx),
+                         256);
         offs[j].xp = bytes;
         bytes = align_up(bytes + sizeof(float) * pairs * sp.dx, 256);
         rank_off[j + 1] = rank_off[j];
         // a ranked set's job with one X column and no window is counted in a
         // wavelet matrix when that fits a block's LDS (N up to about 21000),
         // else over the ranges of ranks
-        const size_t wl = ranked[set_of[j]] && sp.dx == 1 && sp.theiler == 0 ? list_wavelet_lds(sp.n) : 0;
+        const bool ranked = geo[rset_of[j]].ranked;
+        const size_t wl = ranked && (sp.dx == 1 || swapped(j)) && sp.theiler == 0 ? list_wavelet_lds(sp.n) : 0;
         offs[j].wavelet = wl > 0;
         wavelet_lds = std::max(wavelet_lds, wl);
-        if (ranked[set_of[j]]) {
+        if (ranked) {
             offs[j].xr = bytes;
             bytes = align_up(bytes + (wl ? 2 * sizeof(uint16_t) : sizeof(float) * sp.dx) * pairs, 256);
             offs[j].er = bytes;
             bytes = align_up(bytes + sizeof(uint64_t) * pairs, 256);
-            if (!wl) rank_off[j + 1] += (int64_t)sp.n_est() * ((sp.n + 63) / 64);
+            if (!wl) {
+                rank_off[j + 1] += (int64_t)sp.n_est() * ((sp.n + 63) / 64);
+                rdxm = std::max(rdxm, sp.dx);
+            }
         }
         // sorted X, its ranks, and the partial counts
         offs[j].xs = bytes;
-        if (sp.dz == 0 || wl) {
+        if (sp.dz == 0 || (wl && !swapped(j))) {
             bytes = align_up(bytes + (2 + kRankParts) * sizeof(float) * (size_t)sp.n, 256);
             max_rank_n = std::max(max_rank_n, sp.n);
             ++n_rank_cols;
@@ -1160,45 +1249,61 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     std::vector<RankCol> rank_cols;
     for (int t = 0; t < n_sets; ++t) {
         ListSet &S = sets[t];
-        S.l1 = reinterpret_cast<LEnt *>(sb + o_l1[t]);
-        S.l2 = reinterpret_cast<LEnt *>(sb + o_l2[t]);
-        S.len = reinterpret_cast<int32_t *>(sb + o_len[t]);
-        S.bound = reinterpret_cast<float *>(sb + o_bound[t]);
-        S.zy = reinterpret_cast<float *>(sb + o_zy[t]);
-        S.order = o_order[t] ? reinterpret_cast<int32_t *>(sb + o_order[t]) : nullptr;
-        if (ranked[t]) {
+        const SetSpec &sp = geo[t];
+        if (sp.lists) {
+            S.l1 = reinterpret_cast<LEnt *>(sb + o_l1[t]);
+            S.l2 = reinterpret_cast<LEnt *>(sb + o_l2[t]);
+            S.len = reinterpret_cast<int32_t *>(sb + o_len[t]);
+            S.bound = reinterpret_cast<float *>(sb + o_bound[t]);
+            S.zy = reinterpret_cast<float *>(sb + o_zy[t]);
+            S.order = o_order[t] ? reinterpret_cast<int32_t *>(sb + o_order[t]) : nullptr;
+        }
+        if (sp.ranked) {
             const size_t nb = sizeof(float) * (size_t)S.n;
-            S.zs = reinterpret_cast<float *>(sb + o_rank[t]);
-            S.zord = reinterpret_cast<int32_t *>(sb + o_rank[t] + nb);
-            S.zrank = reinterpret_cast<int32_t *>(sb + o_rank[t] + 2 * nb);
-            rank_cols.push_back(RankCol{S.cols[S.dy], S.n, reinterpret_cast<int32_t *>(sb + o_rank[t] + 3 * nb),
-                                        S.zrank, S.zord, S.zs});
+            uint8_t *r = sb + o_rank[t];
+            S.zs = reinterpret_cast<float *>(r);
+            S.zord = reinterpret_cast<int32_t *>(r + nb);
+            S.zrank = reinterpret_cast<int32_t *>(r + 2 * nb);
+            rank_cols.push_back(
+                RankCol{S.cols[S.dy], S.n, reinterpret_cast<int32_t *>(r + 3 * nb), S.zrank, S.zord, S.zs});
+            if (sp.rank_y) {
+                r += (3 + kRankParts) * nb;
+                S.ys = reinterpret_cast<float *>(r);
+                S.yrank = reinterpret_cast<int32_t *>(r + nb);
+                rank_cols.push_back(
+                    RankCol{S.cols[0], S.n, reinterpret_cast<int32_t *>(r + 2 * nb), S.yrank, nullptr, S.ys});
+            }
         }
     }
-    // build blocks: kBuildRows rows each with packed 16-bit histograms when
-    // every set has N <= 2^16, one row each with 32-bit histograms otherwise;
-    // the compiled-dimension form when every set has the same dz <=
-    // kBuildFixedDz, one Y column and N < 2^16 (kLeanRows rows per block)
-    const bool pack = nmax_set <= 65536;
-    int build_dz = 0, build_kind = 0;
-    {
-        const char *bk = std::getenv("MTE_BUILD_KIND");
-        const int want = bk && *bk ? std::atoi(bk) : 1;
-        bool fixed = pack && want == 1;
-        for (int t = 0; t < n_sets; ++t) {
-            const JobSpec &sp = specs[set_rep[t]];
-            fixed = fixed && sp.dz == specs[set_rep[0]].dz && sp.dy == 1 && sp.n < 65536;
-        }
-        const int dz0 = specs[set_rep[0]].dz;
-        if (fixed && dz0 >= 1 && dz0 <= kBuildFixedDz) {
-            build_dz = dz0;
-            build_kind = 1;
-        }
-    }
-    const char *bq = std::getenv("MTE_BUILD_QB");
+    // build parts: runs of sets with the same number of Z columns (<=
+    // kBuildFixedDz), one Y column and N < 2^16 take the compiled-dimension
+    // form (kLeanRows or 4 rows per block), the others the generic one
+    // (kBuildRows rows each with packed 16-bit histograms when N <= 2^16, one
+    // row each with 32-bit histograms otherwise).  A launch whose sets differ
+    // in their Z columns took the generic form for all of them: 32 served
+    // requests 8.2 ms, 7.5 by parts
+    const char *bk = std::getenv("MTE_BUILD_KIND"), *bq = std::getenv("MTE_BUILD_QB");
+    const bool want_fixed = !(bk && *bk) || std::atoi(bk) == 1;
     const int lean_qb = bq && *bq ? std::atoi(bq) : (tc.build_qb == 4 ? 4 : kLeanRows);
-    const int qb = build_kind == 1 ? lean_qb : (pack ? kBuildRows : 1);
-    for (int t = 0; t < n_sets; ++t) build_off[t + 1] = build_off[t] + (row_off[t + 1] - row_off[t] + qb - 1) / qb;
+    build_parts_.clear();
+    for (int t = 0; t < n_sets; ++t) {
+        build_off[t + 1] = build_off[t];
+        const SetSpec &sp = geo[t];
+        if (!sp.lists) continue;
+        BuildPart bp;
+        bp.dz = want_fixed && sp.dy == 1 && sp.dz >= 1 && sp.dz <= kBuildFixedDz && sp.n < 65536 ? sp.dz : 0;
+        bp.pack = sp.n <= 65536;
+        bp.qb = bp.dz > 0 ? lean_qb : (bp.pack ? kBuildRows : 1);
+        const int64_t blocks = (sp.n + bp.qb - 1) / bp.qb;
+        build_off[t + 1] += blocks;
+        if (build_parts_.empty() || build_parts_.back().dz != bp.dz || build_parts_.back().pack != bp.pack) {
+            bp.set0 = t;
+            bp.block0 = build_off[t];
+            build_parts_.push_back(bp);
+        }
+        build_parts_.back().set1 = t + 1;
+        build_parts_.back().blocks += blocks;
+    }
     if ((rc = ltables_.ensure(tbytes))) return rc;
     static thread_local HostBuf *staging = new HostBuf;
     if ((rc = staging->ensure(tbytes))) return rc;
@@ -1216,12 +1321,15 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
         J.n_est = sp.n_est();
         J.rs = 1;
         J.set = set_of[j];
+        J.rset = rset_of[j];
+        J.swap = swapped(j) ? 1 : 0;
+        J.sdx = swapped(j) ? 2 : sp.dx;
         J.theiler = sp.theiler;
         J.reps = sp.reps;
         J.rep_shuffle = sp.rep_shuffle;
         J.xt = reinterpret_cast<float *>(sb + offs[j].xt);
         J.xp = reinterpret_cast<float *>(sb + offs[j].xp);
-        if (sp.dz == 0 || offs[j].wavelet) {
+        if (sp.dz == 0 || (offs[j].wavelet && !swapped(j))) {
             const size_t nb = sizeof(float) * (size_t)sp.n;
             J.xs = reinterpret_cast<float *>(sb + offs[j].xs);
             int32_t *rank = offs[j].wavelet ? reinterpret_cast<int32_t *>(sb + offs[j].xs + nb) : nullptr;
@@ -1232,8 +1340,8 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
         J.eps = sp.diag_eps;
         J.cnt = sp.diag_cnt;
         J.pk = reinterpret_cast<uint64_t *>(sb + offs[j].pk);
-        if (ranked[set_of[j]]) {
-            J.zrank = sets[set_of[j]].zrank;
+        if (geo[rset_of[j]].ranked) {
+            J.zrank = sets[rset_of[j]].zrank;
             if (offs[j].wavelet) J.xw = reinterpret_cast<uint16_t *>(sb + offs[j].xr);
             else J.xr = reinterpret_cast<float *>(sb + offs[j].xr);
             J.er = reinterpret_cast<uint64_t *>(sb + offs[j].er);
@@ -1274,10 +1382,6 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     L.row_off = od + 3 * nj1;
     L.build_off = od + 3 * nj1 + (n_sets + 1);
     L.build_blocks = build_off[n_sets];
-    L.build_qb = qb;
-    L.build_pack = pack ? 1 : 0;
-    L.build_dz = build_dz;
-    L.build_kind = build_kind;
     L.stats = 0;
     L.n_jobs = n_ljobs_;
     L.n_sets = n_sets;
@@ -1287,7 +1391,8 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     L.failq = reinterpret_cast<uint64_t *>(sb + o_failq);
     L.counters = lcounters_.as<uint32_t>();
     L.kmax = kmax <= 4 ? 4 : (kmax <= 8 ? 8 : 16);
-    L.dxm = dxm <= 1 ? 1 : kMaxDx;
+    L.dxm = dxm <= 2 ? dxm : kMaxDx;
+    L.rank_dxm = rdxm;
     L.fb_grid = std::max(1, 2 * c.n_cu);
     L.max_chunks = 0;
     for (const JobSpec &sp : specs) L.max_chunks = std::max(L.max_chunks, (sp.n + kChunk - 1) / kChunk);
@@ -1643,7 +1748,8 @@ int Batch::launch_all(hipStream_t s, bool timed) {
         if ((rc = begin(s))) return rc;
         const hipEvent_t fork = timed ? ev[0] : fork_;
         if (!timed) MTE_HIP(hipEventRecord(fork_, s));
-        if (launch_list_build(ll_, s)) return hip_fail(hipGetLastError(), "list build launch");
+        for (const BuildPart &bp : build_parts_)
+            if (launch_list_build(ll_, bp, s)) return hip_fail(hipGetLastError(), "list build launch");
         if ((rc = end(kStageBuild, s))) return rc;
         MTE_HIP(hipStreamWaitEvent(side, fork, 0));
         // the ranks come first: the permutation writes the X of the jobs

@@ -164,6 +164,7 @@ private:
     int64_t lpermute_blocks_ = 0;
     Job *ljobs_dev_ = nullptr;
     int64_t *lblk_off_ = nullptr, *litem_off_ = nullptr;
+    std::vector<BuildPart> build_parts_;
     int64_t lpermute_items_ = 0;        // blocks of the table permutation
     int lperm_rows_ = 0;                // and its largest table
     DevBuf ltables_, lscratch_, lcounters_;
