@@ -94,6 +94,12 @@ struct Job {
     const int32_t *xrank;
     uint16_t *xw;
     uint64_t *er;
+    // A job without Z, one X and one Y column (walk) takes no lists: its rows
+    // go by rank in y (zrank, xr and xt's rows), neighbours in y are
+    // neighbouring ranks (xt has kWalkPad rows before and after each group's).
+    // rad: radii by row ([n_est][n])
+    int walk;
+    float *rad;
 };
 
 // Counts of the list path are packed kPackBits to a field: N <= kListMaxN.
@@ -140,10 +146,13 @@ struct ListSet {
     float *zs;
     int32_t *zord;
     int32_t *zrank;
-    // for swapped jobs (Job::swap): y sorted, and each row's rank in y
+    // for swapped and walk jobs (Job::swap, Job::walk): y sorted, each row's
+    // rank in y and, for walk jobs, the row of each rank; ys then has kWalkPad
+    // words of -inf before and +inf after it
     float *ys;
-    int32_t *yrank;
+    int32_t *yrank, *yord;
 };
+constexpr int kWalkPad = 16;
 
 // A run of list sets built by one kernel form: compiled dimensions (dz Z
 // columns and one Y column) or, dz = 0, the generic form; qb rows per block;
@@ -200,6 +209,7 @@ struct RankCol {
     int n;
     int32_t *part, *rank, *ord;
     float *sorted;
+    int pad;                      // words of -inf before and +inf after `sorted`
 };
 
 // One launch of the list path over `n_jobs` jobs (all with dz > 0).
@@ -225,7 +235,6 @@ struct ListLaunch {
     int fb_grid;                  // blocks of the fallback kernel
     int max_chunks;               // largest ceil(n / kChunk) of the jobs (reduction grid)
     int coop_lanes;               // the scan finishes cooperatively once this many lanes remain
-    int grouped;                  // 1: a scan group's rows on as few XCDs as fill them evenly; 0: on all
     // Scan units, dealt to the XCDs in turn (unit u on XCD u % kXcds, each XCD
     // taking its units one after another): xcd_off[x * (unit_t + 1) + t] is
     // the first block, counting XCD x's blocks alone, of x's t-th unit
@@ -235,9 +244,16 @@ struct ListLaunch {
     const ScanUnit *units;
     int unit_t;
     int64_t scan_blocks;          // grid of the scan
+    // the same for the walk jobs
+    const int64_t *walk_xcd_off;
+    const ScanUnit *walk_units;
+    int walk_unit_t, walk_window; // walk_window: some walk job has a Theiler window
+    int64_t walk_blocks;
+    size_t walk_lds;              // LDS bytes of their counts: two sorted columns
     int scan_step;                // list entries per step of the scan's lane-by-lane loops (4, 8)
     const RankCol *rank_cols;     // the columns to rank
     int n_rank_cols;
+    int est_cuts;                 // blocks per estimate of the walk counts
     size_t wavelet_lds;           // LDS bytes of a wavelet block (0: no job is counted there)
     int64_t rank_waves;           // rank-count waves: sum over those sets' jobs of
                                   // n_est * ceil(n / 64)
@@ -310,6 +326,7 @@ int launch_list_zy(const ListLaunch &L, void *stream);      // the sets' contigu
 int launch_list_order(const ListLaunch &L, void *stream);  // the scan's row order (several jobs)
 int launch_list_build(const ListLaunch &L, const BuildPart &P, void *stream);
 int launch_list_scan(const ListLaunch &L, void *stream);
+int launch_list_walk(const ListLaunch &L, void *stream);        // radii and counts of the walk jobs
 int launch_list_rank(const ListLaunch &L, void *stream);        // ranks of the columns in rank_cols
 int launch_list_rank_count(const ListLaunch &L, void *stream);  // counts of the ranked sets' jobs over rank ranges
 int launch_list_wavelet(const ListLaunch &L, void *stream);     // the same in wavelet matrices

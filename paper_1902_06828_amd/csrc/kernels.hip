@@ -111,7 +111,8 @@ __device__ __forceinline__ void store_row(const Job &J, int e, int64_t i, int64_
     }
     for (int c = 0; c < J.dx; ++c) {
         const float v = J.cols[c][x];
-        if (J.xt && !J.swap) J.xt[(((int64_t)c * gG + gg) * J.n + i) * kScanLanes + gl] = v;
+        if (J.walk) J.xt[((int64_t)gg * (J.n + 2 * kWalkPad) + kWalkPad + ri) * kScanLanes + gl] = v;
+        else if (J.xt && !J.swap) J.xt[(((int64_t)c * gG + gg) * J.n + i) * kScanLanes + gl] = v;
         J.xp[((int64_t)e * J.dx + c) * J.n + i] = v;
         if (J.xr) J.xr[((int64_t)e * J.dx + c) * J.n + ri] = v;
     }

@@ -755,6 +755,16 @@ __global__ __launch_bounds__(kRankThreads) void list_rank_place_kernel(const Lis
     if (C.rank) C.rank[i] = r;
     if (C.ord) C.ord[r] = i;
     C.sorted[r] = C.col[i];
+    if (i < C.pad) {
+        C.sorted[-1 - i] = -inf_f();
+        C.sorted[n + i] = inf_f();
+    }
+    // (fewer rows than pads: the last thread writes the rest)
+    if (i == n - 1)
+        for (int q = n; q < C.pad; ++q) {
+            C.sorted[-1 - q] = -inf_f();
+            C.sorted[n + q] = inf_f();
+        }
 }
 
 // ------------------------------------------------------------------ row order
@@ -1252,6 +1262,203 @@ __global__ __launch_bounds__(kScanLanes) void list_scan_kernel(const ListLaunch 
                 reinterpret_cast<unsigned long long *>(L.counters + kListStatWord + slot * kListStatStride);
             atomicAdd(&st[0], (unsigned long long)seen1);
             atomicAdd(&st[1], (unsigned long long)seen2);
+        }
+    }
+}
+
+// ------------------------------------------------------------------ walk
+// Jobs without Z, with one X and one Y column: the rows nearest to row i in y
+// are the ranks next to its own, so the k-NN radius needs no lists.  As in the
+// scan a wave takes one row (by rank in y) and one scan group of estimates; it
+// walks outwards, kWalkU ranks at a time on the side whose next rank is nearer
+// in y, until that distance reaches the k-th (for all but kWalkFew lanes; those
+// go on one after the other, 64 ranks per step).  xt's rows are in rank order,
+// so a step's X values are adjacent rows, and neighbouring waves read the same
+// ones; for the last lanes xr holds an estimate's X by rank.  Every pair is
+// decided.  n_x and n_y are two binary searches each, on the sorted columns in
+// LDS (a block per estimate).  At N = 9995, 201 estimates the lists of every
+// row (800 MB) took 0.53 ms to build and 0.62 ms to scan (1.22 ms for
+// the whole test, 0.51 this way): the walk takes 0.33 ms, bound by the waves'
+// chains of dependent loads, the counts 43 us.
+constexpr int kWalkU = 8;
+constexpr int kWalkFew = 16;
+static_assert(2 * kWalkU <= kWalkPad, "a step past the end stays within the pads");
+
+template <int KMAX, bool WIN>
+__global__ __launch_bounds__(kScanLanes) void list_walk_kernel(const ListLaunch L) {
+    const int lane = tid_x();
+    const int64_t b = bid_x();
+    const int x = (int)(b % kXcds);
+    const int64_t k = b / kXcds;
+    Const<int64_t> *xo = as_const(L.walk_xcd_off) + (int64_t)x * (L.walk_unit_t + 1);
+    if (k >= xo[L.walk_unit_t]) return;
+    int lo = 0, hi = L.walk_unit_t - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (xo[mid] <= k) lo = mid; else hi = mid - 1;
+    }
+    Const<ScanUnit> *U = as_const(L.walk_units) + (x + lo * kXcds);
+    const int r = U->row0 + (int)(k - xo[lo]), grp = U->group;
+    Const<Job> *J = as_const(L.jobs) + U->job;
+    Const<ListSet> *S = as_const(L.sets) + J->rset;
+    const int n = J->n, E = J->n_est, w = J->theiler;
+    const float *ysg = S->ys;
+    Const<float> *ys = as_const(ysg);
+    Const<int32_t> *yord = as_const(S->yord);
+    const int i = min(max(yord[r], 0), n - 1);
+    const int e0 = scan_group_first(grp, E), ne = scan_group_first(grp + 1, E) - e0;
+    const bool live = lane < ne;
+    const uint64_t livem = ballot(live);
+    // rank q's row of the group, q from -kWalkPad to n + kWalkPad - 1 (the pads'
+    // distances in y are +inf, whatever their X)
+    const float *xg = J->xt + ((int64_t)grp * (n + 2 * kWalkPad) + kWalkPad) * kScanLanes;
+    const uint32_t loff = (uint32_t)min(lane, ne - 1) * 4u;
+    const float xq = gload_b(xg + (int64_t)r * kScanLanes, loff), yq = ys[r];
+    float top[KMAX];
+    const int pad_front = KMAX - J->k;
+#pragma unroll
+    for (int m = 0; m < KMAX; ++m) top[m] = m < pad_front ? -inf_f() : inf_f();
+
+    // ranks a .. a+kWalkU-1: y, X and, with a window, the rows
+    struct Blk {
+        float y[kWalkU], v[kWalkU];
+        int j[kWalkU];
+    };
+    auto fetch = [&](int a, Blk &B) {
+        const float *xa = xg + (int64_t)a * kScanLanes;
+#pragma unroll
+        for (int u = 0; u < kWalkU; ++u) {
+            B.y[u] = ys[a + u];
+            B.v[u] = gload_b(xa, loff + u * (kScanLanes * 4u));
+            if (WIN) B.j[u] = yord[min(max(a + u, 0), n - 1)];
+        }
+    };
+    auto use = [&](const Blk &B) {
+        float d[kWalkU], dmin = inf_f();
+#pragma unroll
+        for (int u = 0; u < kWalkU; ++u) {
+            d[u] = fmax_(absdiff(xq, B.v[u]), absdiff(B.y[u], yq));
+            if (WIN && abs(B.j[u] - i) <= w) d[u] = inf_f();
+            dmin = __builtin_fminf(dmin, d[u]);
+        }
+        if (cmp_mask(dmin < top[KMAX - 1])) {
+#pragma unroll
+            for (int u = 0; u < kWalkU; ++u) topk_insert<KMAX>(top, d[u]);
+        }
+    };
+    // the next ranks: lt - 1 downwards, rt upwards
+    int lt = r, rt = r + 1;
+    uint64_t open = livem, seen = 0;
+    {
+        Blk bl, br;
+        fetch(lt - kWalkU, bl);
+        fetch(rt, br);
+        for (;;) {
+            const float dl = absdiff(bl.y[kWalkU - 1], yq), dr = absdiff(br.y[0], yq);
+            const float dn = __builtin_fminf(dl, dr);
+            open = livem & ~cmp_mask(dn >= top[KMAX - 1]);
+            // (no rank is left: every radius stands.  The steps go by the
+            // indices, so that values that are not finite end the walk too)
+            if (lt <= 0 && rt >= n) open = 0;
+            if (__builtin_popcountll(open) <= kWalkFew) break;
+            seen += (uint64_t)__builtin_popcountll(open) * kWalkU;
+            Blk cur;
+            if (lt > 0 && (rt >= n || cmp_mask(dl <= dr))) {
+                cur = bl;
+                lt -= kWalkU;
+                fetch(lt - kWalkU, bl);
+            } else {
+                cur = br;
+                rt += kWalkU;
+                fetch(rt, br);
+            }
+            use(cur);
+        }
+    }
+    while (open && (lt > 0 || rt < n)) {
+        const float dl = lt > 0 ? absdiff(ys[lt - 1], yq) : inf_f(), dr = rt < n ? absdiff(ys[rt], yq) : inf_f();
+        const float dn = __builtin_fminf(dl, dr);
+        open &= ~cmp_mask(dn >= top[KMAX - 1]);
+        if (!open) break;
+        const bool left = lt > 0 && (rt >= n || cmp_mask(dl <= dr) != 0);
+        const int q = left ? lt - 1 - lane : rt + lane, qc = min(max(q, 0), n - 1);
+        float dy = absdiff(gload(ysg, (uint32_t)qc), yq);
+        if (q < 0 || q >= n) dy = inf_f();
+        if (WIN && abs(S->yord[qc] - i) <= w) dy = inf_f();
+        if (left) lt -= 64; else rt += 64;
+        for (uint64_t rest = open; rest; rest &= rest - 1) {
+            const int o = lowest(rest);
+            const float *xr = J->xr + (int64_t)(e0 + o) * n;
+            const float d = fmax_(absdiff(bcast(xq, o), gload(xr, (uint32_t)qc)), dy);
+            // +inf leaves the other lanes' lists as they are
+            for (uint64_t cand = cmp_mask(d < bcast(top[KMAX - 1], o)); cand; cand &= cand - 1) {
+                const float dv = bcast(d, lowest(cand));
+                topk_insert<KMAX>(top, lane == o ? dv : inf_f());
+            }
+            seen += 64;
+        }
+    }
+    if (live) J->rad[(int64_t)(e0 + lane) * n + i] = top[KMAX - 1];
+    if (L.stats && lane == 0) {
+        const int slot = (int)(b & (kListStatSlots - 1));
+        unsigned long long *st =
+            reinterpret_cast<unsigned long long *>(L.counters + kListStatWord + slot * kListStatStride);
+        atomicAdd(&st[0], (unsigned long long)seen);
+    }
+}
+
+constexpr int kWalkThreads = 1024;
+
+__global__ __launch_bounds__(kWalkThreads) void list_walk_count_kernel(const ListLaunch L) {
+    extern __shared__ uint64_t wv_lds[];
+    const int64_t g = bid_x();
+    const int cut = (int)__builtin_amdgcn_workgroup_id_y();
+    const int jb = __builtin_amdgcn_readfirstlane(find_job(L.est_off, L.n_jobs, g));
+    Const<Job> *J = as_const(L.jobs) + jb;
+    if (!J->walk) return;
+    Const<ListSet> *S = as_const(L.sets) + J->rset;
+    const int n = J->n, w = J->theiler, tid = tid_x();
+    const int64_t e = g - as_const(L.est_off)[jb];
+    float *xs = reinterpret_cast<float *>(wv_lds), *ys = xs + n;
+    const float *xsg = J->xs, *ysg = S->ys, *yc = J->cols[1], *xe = J->xp + e * n;
+    for (int q = tid; q < n; q += kWalkThreads) {
+        xs[q] = gload(xsg, (uint32_t)q);
+        ys[q] = gload(ysg, (uint32_t)q);
+    }
+    __syncthreads();
+    // rows of a sorted column within eps of v: (s - v) > -eps and < eps
+    auto range = [&](const float *s, float v, float eps) {
+        int p = 0, q = n;
+        while (p < q) {
+            const int m = (p + q) >> 1;
+            if (s[m] - v > -eps) q = m; else p = m + 1;
+        }
+        const int first = p;
+        q = n;
+        while (p < q) {
+            const int m = (p + q) >> 1;
+            if (s[m] - v >= eps) q = m; else p = m + 1;
+        }
+        return p - first;
+    };
+    const int c0 = (int)((int64_t)n * cut / L.est_cuts), c1 = (int)((int64_t)n * (cut + 1) / L.est_cuts);
+    for (int i = c0 + tid; i < c1; i += kWalkThreads) {
+        const float eps = J->rad[e * n + i], xq = gload(xe, (uint32_t)i), yq = gload(yc, (uint32_t)i);
+        // the row itself is in both ranges exactly when eps > 0
+        const int own = 0.f < eps ? 1 : 0;
+        int nx = range(xs, xq, eps) - own, ny = range(ys, yq, eps) - own;
+        for (int j = max(0, i - w); j <= min(n - 1, i + w); ++j) {
+            if (j == i) continue;
+            nx -= absdiff(xq, gload(xe, (uint32_t)j)) < eps;
+            ny -= absdiff(yq, gload(yc, (uint32_t)j)) < eps;
+        }
+        const int nz = n - 1 - min(i, w) - min(n - 1 - i, w);
+        J->pk[e * n + i] = pack_counts(nx, ny, nz);
+        if (J->eps) J->eps[e * n + i] = eps;
+        if (J->cnt) {
+            J->cnt[(e * 3 + 0) * n + i] = nx;
+            J->cnt[(e * 3 + 1) * n + i] = ny;
+            J->cnt[(e * 3 + 2) * n + i] = nz;
         }
     }
 }
@@ -1903,7 +2110,7 @@ int launch_list_build(const ListLaunch &L, const BuildPart &P, void *stream) {
 }
 
 int launch_list_scan(const ListLaunch &L, void *stream) {
-    if (L.lanes <= 0) return 0;
+    if (L.scan_blocks <= 0) return 0;
     void *fn = nullptr;
     const int st = L.scan_step;
     if (L.kmax == 4) fn = scan_dx<4>(L.dxm, st);
@@ -1947,6 +2154,31 @@ int launch_list_wavelet(const ListLaunch &L, void *stream) {
     ListLaunch arg = L;
     void *args[] = {(void *)&arg};
     return hipLaunchKernel(fn, dim3((unsigned)L.ests), dim3(kWvThreads), args, L.wavelet_lds, (hipStream_t)stream) ==
+                   hipSuccess
+               ? 0
+               : -1;
+}
+
+int launch_list_walk(const ListLaunch &L, void *stream) {
+    if (L.walk_blocks <= 0) return 0;
+    const bool win = L.walk_window != 0;
+    void *fn = L.kmax == 4   ? (win ? reinterpret_cast<void *>(&list_walk_kernel<4, true>)
+                                    : reinterpret_cast<void *>(&list_walk_kernel<4, false>))
+               : L.kmax == 8 ? (win ? reinterpret_cast<void *>(&list_walk_kernel<8, true>)
+                                    : reinterpret_cast<void *>(&list_walk_kernel<8, false>))
+                             : (win ? reinterpret_cast<void *>(&list_walk_kernel<16, true>)
+                                    : reinterpret_cast<void *>(&list_walk_kernel<16, false>));
+    ListLaunch arg = L;
+    void *args[] = {(void *)&arg};
+    if (hipLaunchKernel(fn, dim3((unsigned)L.walk_blocks), dim3(kScanLanes), args, 0, (hipStream_t)stream) !=
+        hipSuccess)
+        return -1;
+    void *cf = reinterpret_cast<void *>(&list_walk_count_kernel);
+    static_assert(2 * sizeof(float) * kNoZSortMax <= 163840 - 1024, "two sorted columns in LDS");
+    if (L.walk_lds > 65536 - 1024 &&
+        hipFuncSetAttribute(cf, hipFuncAttributeMaxDynamicSharedMemorySize, 163840 - 1024) != hipSuccess)
+        return -1;
+    return hipLaunchKernel(cf, dim3((unsigned)L.ests, (unsigned)L.est_cuts), dim3(kWalkThreads), args, L.walk_lds, (hipStream_t)stream) ==
                    hipSuccess
                ? 0
                : -1;

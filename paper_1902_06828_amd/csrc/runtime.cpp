@@ -975,6 +975,7 @@ struct SetSpec {
     int ranked = 0;     // counted by ranks of z
     int rank_y = 0;     // y ranked too (swapped jobs)
     int lists = 1;      // some job scans its lists
+    int walk = 0;       // its jobs walk the ranks of y
     int job = -1;       // the swapped job whose X columns it holds
 };
 
@@ -1013,7 +1014,12 @@ static std::vector<SetSpec> plan_sets(const std::vector<JobSpec> &specs, int n_r
             S.theiler = sp.theiler;
             S.ranked = rank_on && sp.dz == 1 && sp.dy == 1 && sp.n <= kRankMaxN;
             S.lists = 0;
+            // without Z, with one Y column: no lists (MTE_LIST_CAP keeps them)
+            const char *cap = std::getenv("MTE_LIST_CAP");
+            S.walk = sp.dz == 0 && sp.dy == 1 && !(cap && *cap);
+            S.rank_y = S.walk;
         }
+        if (S.walk) continue;
         const bool swap = S.ranked && sp.dx >= 2 && sp.theiler == 0 && list_wavelet_lds(sp.n) > 0;
         if (!swap) {
             S.lists = 1;
@@ -1102,37 +1108,54 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     // evenly among the XCDs (C2's 4 groups: halves, so an XCD's L2 holds one
     // group's columns); MTE_GROUPED=0 and MTE_GROUPED_MANY=0 cut every group
     // into one range per XCD instead
-    int n_groups_all = 0;
-    for (int j = 0; j < n_ljobs_; ++j) n_groups_all += scan_groups(specs[j].n_est());
-    const bool dealt = n_ljobs_ == 1 ? env_int("MTE_GROUPED", tc.grouped != 0 ? 1 : 0) != 0
-                                     : env_int("MTE_GROUPED_MANY", 1) != 0;
-    int cuts = kXcds;
-    if (dealt && n_groups_all >= kUnitsPerXcd * kXcds) cuts = 1;
-    else if (dealt)
-        while (cuts > 1 && n_groups_all * (cuts / 2) % kXcds == 0) cuts /= 2;
-    std::vector<ScanUnit> units;
-    for (int j = 0; j < n_ljobs_; ++j) {
-        const JobSpec &sp = specs[j];
-        for (int g = 0; g < scan_groups(sp.n_est()); ++g)
-            for (int q = 0; q < cuts; ++q) {
-                const int r0 = (int)((int64_t)sp.n * q / cuts), r1 = (int)((int64_t)sp.n * (q + 1) / cuts);
-                units.push_back(ScanUnit{j, g, r0, r1 - r0});
+    auto walks = [&](int j) { return geo[rset_of[j]].walk != 0; };
+    struct Units {
+        std::vector<ScanUnit> u;
+        std::vector<int64_t> xcd_off;
+        int t = 0;
+        int64_t blocks = 0;
+    };
+    auto plan_units = [&](bool walk) {
+        Units out;
+        int n_groups = 0, n_of = 0;
+        for (int j = 0; j < n_ljobs_; ++j)
+            if (walks(j) == walk) {
+                n_groups += scan_groups(specs[j].n_est());
+                ++n_of;
             }
-    }
-    const int nu = (int)units.size(), unit_t = (nu + kXcds - 1) / kXcds;
-    std::vector<int64_t> xcd_off((size_t)kXcds * (unit_t + 1), 0);
-    int64_t scan_blocks = 0;
-    for (int x = 0; x < kXcds; ++x) {
-        int64_t acc = 0;
-        for (int t = 0; t < unit_t; ++t) {
-            xcd_off[(size_t)x * (unit_t + 1) + t] = acc;
-            const int u = x + t * kXcds;
-            if (u < nu) acc += units[u].nrows;      // one wave, one block per row
+        if (n_of == 0) return out;
+        const bool dealt = n_ljobs_ == 1 ? env_int("MTE_GROUPED", tc.grouped != 0 ? 1 : 0) != 0
+                                         : env_int("MTE_GROUPED_MANY", 1) != 0;
+        int cuts = kXcds;
+        if (dealt && n_groups >= kUnitsPerXcd * kXcds) cuts = 1;
+        else if (dealt)
+            while (cuts > 1 && n_groups * (cuts / 2) % kXcds == 0) cuts /= 2;
+        for (int j = 0; j < n_ljobs_; ++j) {
+            if (walks(j) != walk) continue;
+            const JobSpec &sp = specs[j];
+            for (int g = 0; g < scan_groups(sp.n_est()); ++g)
+                for (int q = 0; q < cuts; ++q) {
+                    const int r0 = (int)((int64_t)sp.n * q / cuts), r1 = (int)((int64_t)sp.n * (q + 1) / cuts);
+                    out.u.push_back(ScanUnit{j, g, r0, r1 - r0});
+                }
         }
-        xcd_off[(size_t)x * (unit_t + 1) + unit_t] = acc;
-        scan_blocks = std::max(scan_blocks, acc);
-    }
-    scan_blocks *= kXcds;
+        const int nu = (int)out.u.size();
+        out.t = (nu + kXcds - 1) / kXcds;
+        out.xcd_off.assign((size_t)kXcds * (out.t + 1), 0);
+        for (int x = 0; x < kXcds; ++x) {
+            int64_t acc = 0;
+            for (int t = 0; t < out.t; ++t) {
+                out.xcd_off[(size_t)x * (out.t + 1) + t] = acc;
+                const int u = x + t * kXcds;
+                if (u < nu) acc += out.u[u].nrows;      // one wave, one block per row
+            }
+            out.xcd_off[(size_t)x * (out.t + 1) + out.t] = acc;
+            out.blocks = std::max(out.blocks, acc);
+        }
+        out.blocks *= kXcds;
+        return out;
+    };
+    const Units su = plan_units(false), wu = plan_units(true);
     // scratch layout: per set its lists and Y,Z copy; per job xt, xp, the
     // packed counts and the chunk sums; then the queue
     size_t bytes = 0;
@@ -1150,6 +1173,12 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
         S.theiler = sp.theiler;
         // rank arrays: zs, zord, zrank, for swapped jobs ys and yrank (n words
         // each), and each ranked column's partial counts
+        if (sp.walk) {
+            // yord, yrank, the partial counts and the padded sorted column
+            max_rank_n = std::max(max_rank_n, sp.n);
+            o_rank[t] = bytes;
+            bytes = align_up(bytes + ((3 + kRankParts) * (size_t)sp.n + 2 * kWalkPad) * sizeof(float), 256);
+        }
         if (sp.ranked) {
             max_rank_n = std::max(max_rank_n, sp.n);
             o_rank[t] = bytes;
@@ -1183,17 +1212,18 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
             bytes = align_up(bytes + sizeof(int32_t) * (size_t)sp.n, 256);
         }
     }
-    struct Off { size_t xt, xp, pk, xs, chunk, xr, er; bool wavelet; };
+    struct Off { size_t xt, xp, pk, xs, chunk, xr, er, rad; bool wavelet; };
     std::vector<Off> offs(n_ljobs_);
     std::vector<int64_t> rank_off(n_ljobs_ + 1, 0);
     size_t wavelet_lds = 0;
     int n_rank_cols = 0, rdxm = 1;
-    for (int t = 0; t < n_sets; ++t) n_rank_cols += geo[t].ranked + geo[t].rank_y;
+    for (int t = 0; t < n_sets; ++t) n_rank_cols += geo[t].ranked + geo[t].rank_y;   // z, y
     for (int j = 0; j < n_ljobs_; ++j) {
         const JobSpec &sp = specs[j];
         const size_t pairs = (size_t)sp.n * sp.n_est();
         offs[j].xt = bytes;
-        bytes = align_up(bytes + sizeof(float) * (size_t)sp.n * kScanLanes * scan_groups(sp.n_est()) * (swapped(j) ? 2 : sp.dx),
+        bytes = align_up(bytes + sizeof(float) * ((size_t)sp.n + (walks(j) ? 2 * kWalkPad : 0)) * kScanLanes *
+                                     scan_groups(sp.n_est()) * (swapped(j) ? 2 : sp.dx),
                          256);
         offs[j].xp = bytes;
         bytes = align_up(bytes + sizeof(float) * pairs * sp.dx, 256);
@@ -1215,6 +1245,12 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
                 rdxm = std::max(rdxm, sp.dx);
             }
         }
+        if (walks(j)) {
+            offs[j].xr = bytes;
+            bytes = align_up(bytes + sizeof(float) * pairs, 256);
+            offs[j].rad = bytes;
+            bytes = align_up(bytes + sizeof(float) * pairs, 256);
+        }
         // sorted X, its ranks, and the partial counts
         offs[j].xs = bytes;
         if (sp.dz == 0 || (wl && !swapped(j))) {
@@ -1234,8 +1270,9 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     const size_t t_sets = align_up(sizeof(ListSet) * n_sets, 256);
     const size_t t_keys = align_up(sizeof(EstKey) * (size_t)n_keys, 256);
     const size_t t_offs = align_up(
-        sizeof(int64_t) * (6 * (size_t)(n_ljobs_ + 1) + 2 * ((size_t)n_sets + 1) + xcd_off.size()), 256);
-    const size_t t_units = align_up(sizeof(ScanUnit) * units.size(), 256);
+        sizeof(int64_t) * (6 * (size_t)(n_ljobs_ + 1) + 2 * ((size_t)n_sets + 1) + su.xcd_off.size() + wu.xcd_off.size()),
+        256);
+    const size_t t_units = align_up(sizeof(ScanUnit) * (su.u.size() + wu.u.size()), 256);
     const size_t t_cols = align_up(sizeof(RankCol) * (size_t)n_rank_cols, 256);
     const size_t tbytes = t_jobs + t_sets + t_keys + t_offs + t_units + t_cols;
     if (measure) {
@@ -1258,6 +1295,15 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
             S.zy = reinterpret_cast<float *>(sb + o_zy[t]);
             S.order = o_order[t] ? reinterpret_cast<int32_t *>(sb + o_order[t]) : nullptr;
         }
+        if (sp.walk) {
+            const size_t nb = sizeof(float) * (size_t)S.n;
+            uint8_t *r = sb + o_rank[t];
+            S.yord = reinterpret_cast<int32_t *>(r);
+            S.yrank = reinterpret_cast<int32_t *>(r + nb);
+            S.ys = reinterpret_cast<float *>(r + (2 + kRankParts) * nb) + kWalkPad;
+            rank_cols.push_back(RankCol{S.cols[0], S.n, reinterpret_cast<int32_t *>(r + 2 * nb), S.yrank, S.yord, S.ys,
+                                        kWalkPad});
+        }
         if (sp.ranked) {
             const size_t nb = sizeof(float) * (size_t)S.n;
             uint8_t *r = sb + o_rank[t];
@@ -1265,13 +1311,13 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
             S.zord = reinterpret_cast<int32_t *>(r + nb);
             S.zrank = reinterpret_cast<int32_t *>(r + 2 * nb);
             rank_cols.push_back(
-                RankCol{S.cols[S.dy], S.n, reinterpret_cast<int32_t *>(r + 3 * nb), S.zrank, S.zord, S.zs});
+                RankCol{S.cols[S.dy], S.n, reinterpret_cast<int32_t *>(r + 3 * nb), S.zrank, S.zord, S.zs, 0});
             if (sp.rank_y) {
                 r += (3 + kRankParts) * nb;
                 S.ys = reinterpret_cast<float *>(r);
                 S.yrank = reinterpret_cast<int32_t *>(r + nb);
                 rank_cols.push_back(
-                    RankCol{S.cols[0], S.n, reinterpret_cast<int32_t *>(r + 2 * nb), S.yrank, nullptr, S.ys});
+                    RankCol{S.cols[0], S.n, reinterpret_cast<int32_t *>(r + 2 * nb), S.yrank, nullptr, S.ys, 0});
             }
         }
     }
@@ -1323,6 +1369,12 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
         J.set = set_of[j];
         J.rset = rset_of[j];
         J.swap = swapped(j) ? 1 : 0;
+        J.walk = walks(j) ? 1 : 0;
+        if (J.walk) {
+            J.zrank = sets[rset_of[j]].yrank;
+            J.xr = reinterpret_cast<float *>(sb + offs[j].xr);
+            J.rad = reinterpret_cast<float *>(sb + offs[j].rad);
+        }
         J.sdx = swapped(j) ? 2 : sp.dx;
         J.theiler = sp.theiler;
         J.reps = sp.reps;
@@ -1335,7 +1387,7 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
             int32_t *rank = offs[j].wavelet ? reinterpret_cast<int32_t *>(sb + offs[j].xs + nb) : nullptr;
             J.xrank = rank;
             rank_cols.push_back(
-                RankCol{J.cols[0], sp.n, reinterpret_cast<int32_t *>(sb + offs[j].xs + 2 * nb), rank, nullptr, J.xs});
+                RankCol{J.cols[0], sp.n, reinterpret_cast<int32_t *>(sb + offs[j].xs + 2 * nb), rank, nullptr, J.xs, 0});
         }
         J.eps = sp.diag_eps;
         J.cnt = sp.diag_cnt;
@@ -1365,10 +1417,15 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     std::memcpy(oh + 3 * nj1 + 2 * (n_sets + 1), rank_off.data(), sizeof(int64_t) * nj1);
     const size_t o_items = 4 * nj1 + 2 * ((size_t)n_sets + 1), o_units = o_items + nj1;
     std::memcpy(oh + o_items, item_off.data(), sizeof(int64_t) * nj1);
-    std::memcpy(oh + o_units, xcd_off.data(), sizeof(int64_t) * xcd_off.size());
+    auto put = [](void *dst, const auto &v) {
+        if (!v.empty()) std::memcpy(dst, v.data(), sizeof(v[0]) * v.size());
+    };
+    put(oh + o_units, su.xcd_off);
+    put(oh + o_units + su.xcd_off.size(), wu.xcd_off);
     const size_t units_at = t_jobs + t_sets + t_keys + t_offs;
-    std::memcpy(hs + units_at, units.data(), sizeof(ScanUnit) * units.size());
-    if (!rank_cols.empty()) std::memcpy(hs + units_at + t_units, rank_cols.data(), sizeof(RankCol) * rank_cols.size());
+    put(hs + units_at, su.u);
+    put(hs + units_at + sizeof(ScanUnit) * su.u.size(), wu.u);
+    put(hs + units_at + t_units, rank_cols);
     ljobs_dev_ = reinterpret_cast<Job *>(tb);
     lblk_off_ = od + 2 * nj1;
     lpermute_blocks_ = blk_off[n_ljobs_];
@@ -1397,15 +1454,28 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     L.max_chunks = 0;
     for (const JobSpec &sp : specs) L.max_chunks = std::max(L.max_chunks, (sp.n + kChunk - 1) / kChunk);
     L.coop_lanes = env_int("MTE_COOP_LANES", tc.coop_lanes > 0 ? tc.coop_lanes : kCoopLanes);
-    L.grouped = dealt ? 1 : 0;
     L.xcd_off = od + o_units;
     L.units = reinterpret_cast<const ScanUnit *>(tb + units_at);
-    L.unit_t = unit_t;
-    L.scan_blocks = scan_blocks;
+    L.unit_t = su.t;
+    L.scan_blocks = su.blocks;
+    L.walk_xcd_off = od + o_units + su.xcd_off.size();
+    L.walk_units = L.units + su.u.size();
+    L.walk_unit_t = wu.t;
+    L.walk_blocks = wu.blocks;
+    L.walk_lds = 0;
+    L.walk_window = 0;
+    for (int j = 0; j < n_ljobs_; ++j)
+        if (walks(j)) {
+            L.walk_lds = std::max(L.walk_lds, 2 * sizeof(float) * (size_t)specs[j].n);
+            L.walk_window |= specs[j].theiler > 0;
+        }
     L.scan_step = env_int("MTE_SCAN_STEP", tc.scan_step > 0 ? tc.scan_step : (n_ljobs_ == 1 ? 8 : 4)) == 4 ? 4 : 8;
     perm_cu_ = std::max(0, env_int("MTE_PERMUTE_BLOCKS_PER_CU", tc.perm_cu > 0 ? tc.perm_cu : kPermuteBlocksPerCu));
     L.rank_cols = reinterpret_cast<const RankCol *>(tb + units_at + t_units);
     L.n_rank_cols = (int)rank_cols.size();
+    // two blocks per estimate where one each leaves CUs idle or half filled (at
+    // N = 9995: 43 us for 201 estimates, 52 with one block each)
+    L.est_cuts = L.ests < 2 * (int64_t)c.n_cu ? 2 : 1;
     L.wavelet_lds = wavelet_lds;
     L.max_rank_n = max_rank_n;
     L.rank_off = od + 3 * nj1 + 2 * (n_sets + 1);
@@ -1777,6 +1847,7 @@ int Batch::launch_all(hipStream_t s, bool timed) {
         MTE_HIP(hipStreamWaitEvent(s, join_at_end ? ev[1] : join_, 0));
         if ((rc = begin(s))) return rc;
         if (launch_list_scan(ll_, s)) return hip_fail(hipGetLastError(), "list scan launch");
+        if (launch_list_walk(ll_, s)) return hip_fail(hipGetLastError(), "walk launch");
         if (launch_list_wavelet(ll_, s)) return hip_fail(hipGetLastError(), "wavelet count launch");
         if (launch_list_rank_count(ll_, s)) return hip_fail(hipGetLastError(), "rank count launch");
         if ((rc = end(kStageScan, s))) return rc;
