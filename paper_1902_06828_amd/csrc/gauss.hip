@@ -20,6 +20,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "gauss.h"
 
@@ -94,23 +95,36 @@ __device__ __forceinline__ void tile_pair(int y, int n_tiles, int *tp, int *tq) 
 // group of 4 rows, D[m][n] += sum_k A[m][k] B[k][n] with A[m][k] the centered
 // value of column p0+m at row k and B[k][n] that of column q0+n.  Operand
 // layout: lane l supplies row k = l/16 of column l%16; the 4 results of lane
-// l are D[l/16 + 4v][l%16], v = 0..3 (checked on the device).  Tiles are
-// staged column-major in LDS, 33 doubles per column: the 16 columns one
-// operand load touches per row start 66 dwords apart, so each group of 16
-// lanes covers the 32 banks once (no bank conflicts in the counters; a
-// 34-double stride conflicted), and the staging stores are consecutive.  Every
-// entry sees the same sequence of 4-row groups in the same order whatever the
-// tile, so its bits do not depend on the other columns.  On gfx950 the fp64
-// matrix rate equals the fp64 vector rate (78.6 TFLOP/s); the matrix cores
-// need 4x fewer LDS reads per fma than a 4x4 vector register tile.
+// l are D[l/16 + 4v][l%16], v = 0..3 (checked on the device).  Every entry
+// sees the same sequence of 4-row groups in the same order whatever the tile,
+// so its bits do not depend on the other columns.
+//
+// Bound by the SIMDs' issue: an fp64 MFMA holds its SIMD 64 cycles and vector
+// instructions do not run beside it, so what counts is the vector work per
+// MFMA.  A thread stages 4 adjacent rows of a column by one 16-byte load, with
+// its columns' means in registers, and only a chunk's last, partial step is
+// masked; columns past D are the last one again (their entries are not
+// stored).  A tile of the diagonal stages one side, and multiplies no 16x16
+// block below the diagonal; the wave left idle there changes with the chunk,
+// so that no SIMD of a CU is spared more often than the others.
+//
+// LDS: value (row 4g + k, column) at g kGroup + 64 k + (column ^ 16 (k & 1)):
+// one operand is 16 adjacent doubles per k, on different banks for k and k+1,
+// and a group stride of 2 mod 16 spreads the eight groups a wave stores.
+// D = 512, N = 10^6 (270 GFLOP in these blocks): 6.15 ms with masked 4-byte
+// loads, means from LDS and whole diagonal tiles, 4.69 ms so (58 TFLOP/s; 4.91
+// ms with the three blocks per CU that the compiler's own register count gives).
 typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+template <typename T>
+using Global = const __attribute__((address_space(1))) T;
 
-__global__ __launch_bounds__(kThreads) void gauss_gram_kernel(GaussCov a) {
-    constexpr int T = 64;
-    constexpr int LDC = kRB + 1;      // column stride in LDS (doubles)
-    __shared__ double mu[2][T];
-    __shared__ __align__(16) double As[T][LDC];
-    __shared__ __align__(16) double Bs[T][LDC];
+__global__ __launch_bounds__(kThreads, 4) void gauss_gram_kernel(GaussCov a) {
+    constexpr int T = 64, G = kRB / 4;
+    constexpr int kGroup = 4 * T + 2;    // doubles from a 4-row group to the next
+    constexpr int M = kRB * T / kThreads / 4;   // 4-row pieces per thread and side
+    __shared__ __align__(16) double As[G * kGroup];
+    __shared__ __align__(16) double Bs[G * kGroup];
     const int tid = tid_x();
     // One block per (row chunk, tile pair), numbered chunk-major.  With
     // several tile pairs, the blocks, which the hardware deals to the XCDs in
@@ -129,13 +143,11 @@ __global__ __launch_bounds__(kThreads) void gauss_gram_kernel(GaussCov a) {
     int tp, tq;
     tile_pair(b - c * pairs, a.n_tiles, &tp, &tq);
     const int p0 = tp * T, q0 = tq * T;
+    const bool diag = tp == tq;
     const int r0 = c * a.chunk_rows;
     const int r1 = min(a.n, r0 + a.chunk_rows);
-    if (tid < 2 * T) {
-        const int col = (tid < T ? p0 : q0 - T) + tid;
-        mu[tid / T][tid % T] = col < a.D ? a.mean[col] : 0.0;
-    }
-    const int lane = tid & 63, w = tid >> 6;
+    const int lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(((tid >> 6) + c) & 3);
     const int pw = (w & 1) * 32, qw = (w >> 1) * 32;
     const int kk = lane >> 4, cc = lane & 15;
     f64x4 acc[2][2];
@@ -144,50 +156,91 @@ __global__ __launch_bounds__(kThreads) void gauss_gram_kernel(GaussCov a) {
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};
 
-    // Staging: element m of this thread is row (tid + 256 m) % 32 of tile
-    // column (tid + 256 m) / 32.  The next step's values are loaded into
-    // registers while the matrix cores work on the current one.
-    constexpr int M = kRB * T / kThreads;
-    const int sr = tid % kRB;
-    const float *pa[M], *pb[M];
+    // Staging: piece m of this thread is rows 4 sg .. 4 sg + 3 of tile column
+    // sc + 32 m.  The next step's values are loaded into registers while the
+    // matrix cores work on the current one.
+    const int sg = tid % G, sc = tid / G;
+    Global<float> *pa[M], *pb[M];
+    double ma[M], mb[M];
 #pragma unroll
     for (int m = 0; m < M; ++m) {
-        const int col = tid / kRB + m * (kThreads / kRB);
-        pa[m] = p0 + col < a.D ? a.cols[p0 + col] : nullptr;
-        pb[m] = q0 + col < a.D ? a.cols[q0 + col] : nullptr;
+        const int ca = min(p0 + sc + m * (T / M), a.D - 1), cb = min(q0 + sc + m * (T / M), a.D - 1);
+        pa[m] = (Global<float> *)a.cols[ca] + r0 + 4 * sg;
+        pb[m] = (Global<float> *)a.cols[cb] + r0 + 4 * sg;
+        ma[m] = a.mean[ca];
+        mb[m] = a.mean[cb];
     }
-    float na[M], nb[M];
-    auto fetch = [&](int rs) {
-        const int row = rs + sr;
+    f32x4u na[M], nb[M];
+    auto load = [&](int step) {   // whole step `step` of the chunk
 #pragma unroll
-        for (int m = 0; m < M; ++m) {
-            na[m] = (pa[m] && row < r1) ? pa[m][row] : 0.0f;
-            nb[m] = (pb[m] && row < r1) ? pb[m][row] : 0.0f;
-        }
+        for (int m = 0; m < M; ++m) na[m] = *(Global<f32x4u> *)(pa[m] + step * kRB);
+        if (!diag)
+#pragma unroll
+            for (int m = 0; m < M; ++m) nb[m] = *(Global<f32x4u> *)(pb[m] + step * kRB);
     };
-    fetch(r0);
-    for (int rs = r0; rs < r1; rs += kRB) {
-        __syncthreads();
-        const bool in = rs + sr < r1;
+    auto put = [&](double *S, int m, f32x4u v, double mu, int rows) {
+        const int col = sc + m * (T / M);
 #pragma unroll
-        for (int m = 0; m < M; ++m) {
-            const int col = tid / kRB + m * (kThreads / kRB);
-            As[col][sr] = (pa[m] && in) ? (double)na[m] - mu[0][col] : 0.0;
-            Bs[col][sr] = (pb[m] && in) ? (double)nb[m] - mu[1][col] : 0.0;
-        }
-        __syncthreads();
-        if (rs + kRB < r1) fetch(rs + kRB);
+        for (int k = 0; k < 4; ++k)
+            S[sg * kGroup + k * T + (col ^ (k & 1) * 16)] = k < rows ? (double)v[k] - mu : 0.0;
+    };
+    const int x16 = (kk & 1) * 16;
+    const double *ra0 = As + kk * T + (pw ^ x16) + cc, *ra1 = As + kk * T + ((pw + 16) ^ x16) + cc;
+    const double *Bq = diag ? As : Bs;
+    const double *rb0 = Bq + kk * T + (qw ^ x16) + cc, *rb1 = Bq + kk * T + ((qw + 16) ^ x16) + cc;
+    // 16x16 blocks of this wave: all four; on the diagonal those not below it
+    const bool full = !diag || pw < qw, some = full || pw == qw;
+    auto multiply = [&](auto lower) {
 #pragma unroll
-        for (int g = 0; g < kRB / 4; ++g) {
-            const int rr = 4 * g + kk;
-            const double a0 = As[pw + cc][rr], a1 = As[pw + 16 + cc][rr];
-            const double b0 = Bs[qw + cc][rr], b1 = Bs[qw + 16 + cc][rr];
+        for (int g = 0; g < G; ++g) {
+            const double a0 = ra0[g * kGroup], a1 = ra1[g * kGroup];
+            const double b0 = rb0[g * kGroup], b1 = rb1[g * kGroup];
             acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc[0][0], 0, 0, 0);
             acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc[0][1], 0, 0, 0);
-            acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc[1][0], 0, 0, 0);
+            if (decltype(lower)::value)
+                acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc[1][0], 0, 0, 0);
             acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc[1][1], 0, 0, 0);
         }
+    };
+    auto step = [&] {
+        if (full)
+            multiply(std::true_type{});
+        else if (some)
+            multiply(std::false_type{});
+    };
+    const int whole = (r1 - r0) / kRB;
+    if (whole > 0) load(0);
+    for (int t = 0; t < whole; ++t) {
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < M; ++m) put(As, m, na[m], ma[m], 4);
+        if (!diag)
+#pragma unroll
+            for (int m = 0; m < M; ++m) put(Bs, m, nb[m], mb[m], 4);
+        __syncthreads();
+        if (t + 1 < whole) load(t + 1);
+        step();
     }
+    if (r0 + whole * kRB < r1) {
+        // the last rows: those past r1 add 0 * 0
+        const int rows = min(max(r1 - (r0 + whole * kRB + 4 * sg), 0), 4);
+        auto part = [&](Global<float> *p) {
+            f32x4u v{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (k < rows) v[k] = p[whole * kRB + k];
+            return v;
+        };
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            put(As, m, part(pa[m]), ma[m], rows);
+            if (!diag) put(Bs, m, part(pb[m]), mb[m], rows);
+        }
+        __syncthreads();
+        step();
+    }
+    if (!some) return;
     double *out = a.part + (int64_t)c * a.D * a.D;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -197,18 +250,33 @@ __global__ __launch_bounds__(kThreads) void gauss_gram_kernel(GaussCov a) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int p = p0 + pw + 16 * i + kk + 4 * v;
-                if (p < a.D && q < a.D) out[(int64_t)p * a.D + q] = acc[i][j][v];
+                if (p <= q && q < a.D) out[(int64_t)p * a.D + q] = acc[i][j][v];
             }
         }
 }
 
-__global__ __launch_bounds__(kThreads) void gauss_cov_reduce_kernel(GaussCov a) {
-    const int64_t e = (int64_t)bid_x() * kThreads + tid_x();
-    if (e >= (int64_t)a.D * a.D) return;
-    const int p = (int)(e / a.D), q = (int)(e % a.D);
-    if (p > q) return;
+// One thread per entry (64-thread blocks: a small matrix still reaches many
+// CUs), its chunk partials added in chunk order, kReduceU of them loaded ahead
+// of the additions.  Bound by the loads' latency for small matrices (D = 51,
+// 157 chunks: 38.6 us one load at a time, 9.2 us so) and by HBM for large ones
+// (D = 512, 256 chunks, 270 MB: 118 and 76 us).
+constexpr int kReduceThreads = 64, kReduceU = 16;
+
+__global__ __launch_bounds__(kReduceThreads) void gauss_cov_reduce_kernel(GaussCov a) {
+    const int p = bid_y(), q = bid_x() * kReduceThreads + tid_x();
+    if (q < p || q >= a.D) return;
+    const int64_t dd = (int64_t)a.D * a.D;
+    const double *pt = a.part + (int64_t)p * a.D + q;
     double s = 0.0;
-    for (int h = 0; h < a.n_chunks; ++h) s += a.part[(int64_t)h * a.D * a.D + e];
+    int h = 0;
+    for (; h + kReduceU <= a.n_chunks; h += kReduceU) {
+        double v[kReduceU];
+#pragma unroll
+        for (int u = 0; u < kReduceU; ++u) v[u] = pt[(h + u) * dd];
+#pragma unroll
+        for (int u = 0; u < kReduceU; ++u) s += v[u];
+    }
+    for (; h < a.n_chunks; ++h) s += pt[h * dd];
     s /= (double)a.n;
     a.cov[(int64_t)p * a.D + q] = s;
     a.cov[(int64_t)q * a.D + p] = s;
@@ -287,9 +355,9 @@ int launch_gauss_gram(const GaussCov &a, hipStream_t s) {
 
 int launch_gauss_cov_reduce(const GaussCov &a, hipStream_t s) {
     if (a.D < 1 || a.n < 1) return 0;
-    const int64_t entries = (int64_t)a.D * a.D;
-    hipLaunchKernelGGL(gauss_cov_reduce_kernel, dim3((unsigned)((entries + kThreads - 1) / kThreads)),
-                       dim3(kThreads), 0, s, a);
+    hipLaunchKernelGGL(gauss_cov_reduce_kernel,
+                       dim3((unsigned)((a.D + kReduceThreads - 1) / kReduceThreads), (unsigned)a.D),
+                       dim3(kReduceThreads), 0, s, a);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
