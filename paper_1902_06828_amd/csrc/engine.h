@@ -30,6 +30,7 @@ constexpr int kMaxK = 16;
 constexpr int kBlock = 256;        // threads per block (4 wave64)
 constexpr int kWaves = kBlock / 64;
 constexpr int kChunk = 64;         // rows per fixed-order partial sum
+constexpr int kSumChunks = 512;    // chunks that one block sums
 
 // One estimate's surrogate key (identity when `ident` != 0).
 struct EstKey {

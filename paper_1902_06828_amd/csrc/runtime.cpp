@@ -1746,7 +1746,7 @@ int Batch::prepare_solo(const std::vector<JobSpec> &specs, hipStream_t s, size_t
 
 // Launch sequence: the all-pairs part (reset, permute, main kernel), then
 // the list part (reset, Y,Z copy; permute into xt on the side stream beside
-// the build and the X sort, which read only the unpermuted columns; joined
+// the build and the ranks, which read only the unpermuted columns; joined
 // before the scan; then scan, fallback, reduce).
 int Batch::launch_all(hipStream_t s, bool timed) {
     // timed: a stage's events bracket its kernels; a stage that follows
