@@ -85,11 +85,11 @@ def build_ops(n, dy, dz):
 
 
 def scan_bytes(dx, entries):
-    """Neighbour-list scan, from the list entries it reads: an entry of a
-    (Y,Z) list is 8 bytes (d_yz, row), of a Z list 12 bytes (d_z, d_yz, row),
-    and each entry also reads the row's dx permuted X values (4 bytes each)."""
+    """Neighbour-list scan, from the list entries it reads: an entry is
+    8 bytes (distance, row) and also reads the row's dx permuted X values (4
+    bytes each)."""
     knn, zl = entries
-    return knn * (8 + 4 * dx) + zl * (12 + 4 * dx)
+    return (knn + zl) * (8 + 4 * dx)
 
 
 def counter_record(kernel):
