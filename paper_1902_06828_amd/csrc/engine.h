@@ -22,6 +22,12 @@
 
 namespace mte {
 
+#ifdef __HIP__
+#define MTE_HD __host__ __device__
+#else
+#define MTE_HD
+#endif
+
 constexpr int kMaxCols = 64;       // dx + dy + dz per job
 constexpr int kMaxDx = 16;
 constexpr int kMaxDy = 8;
@@ -106,6 +112,25 @@ struct Job {
 // Counts of the list path are packed kPackBits to a field: N <= kListMaxN.
 constexpr int kPackBits = 21;
 constexpr int kListMaxN = 1 << kPackBits;
+constexpr uint64_t kPackMask = (uint64_t(1) << kPackBits) - 1;
+
+// A row's counts as that word, and back as places in the harmonic table, which
+// holds n + 1 values.  Inputs that are not finite, which device calls do not
+// check, can leave a range that lacks the row itself, so that the range less
+// the row is -1 (0 here), and rows that no kernel wrote a word for: whatever a
+// word holds, its three places lie inside the table.
+MTE_HD inline uint64_t pack_counts(int cxz, int cyz, int cz) {
+    return (uint64_t)(uint32_t)(cxz < 0 ? 0 : cxz) | ((uint64_t)(uint32_t)(cyz < 0 ? 0 : cyz) << kPackBits) |
+           ((uint64_t)(uint32_t)(cz < 0 ? 0 : cz) << (2 * kPackBits));
+}
+struct Counts {
+    uint32_t xz, yz, z;
+};
+MTE_HD inline Counts unpack_counts(uint64_t w, int n) {
+    const uint32_t xz = (uint32_t)(w & kPackMask), yz = (uint32_t)((w >> kPackBits) & kPackMask),
+                   z = (uint32_t)(w >> (2 * kPackBits)), m = (uint32_t)n;
+    return Counts{xz < m ? xz : m, yz < m ? yz : m, z < m ? z : m};
+}
 
 // Largest N of a list-path job without Z (its X column is sorted in LDS).
 constexpr int kNoZSortMax = 16384;
@@ -185,11 +210,6 @@ constexpr int kKeyBins = 1 << (32 - kKeyShift - 1);
 // equal size, group g holding the estimates g*E/G .. (g+1)*E/G - 1, one lane
 // each.
 constexpr int kScanLanes = 64;
-#ifdef __HIP__
-#define MTE_HD __host__ __device__
-#else
-#define MTE_HD
-#endif
 MTE_HD inline int scan_groups(int n_est) { return (n_est + kScanLanes - 1) / kScanLanes; }
 MTE_HD inline int scan_group_first(int g, int n_est) { return (int)((int64_t)g * n_est / scan_groups(n_est)); }
 MTE_HD inline int scan_group_of(int e, int n_est) {

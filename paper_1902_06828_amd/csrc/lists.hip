@@ -88,13 +88,7 @@ __device__ __forceinline__ float gload_b(const float *p, uint32_t byte_off) {
                                                               byte_off);
 }
 
-constexpr uint64_t kPackMask = (uint64_t(1) << kPackBits) - 1;
 constexpr uint64_t kRankNone = 0xbf800000u;   // radius -1: the pair is in the redo queue
-
-__device__ __forceinline__ uint64_t pack_counts(int cxz, int cyz, int cz) {
-    return (uint64_t)(uint32_t)cxz | ((uint64_t)(uint32_t)cyz << kPackBits) |
-           ((uint64_t)(uint32_t)cz << (2 * kPackBits));
-}
 
 // Bucket key of a distance d >= 0 (+inf included): its exponent and top
 // mantissa bits.  The sign bit is clear, so a plain shift (which gfx950
@@ -750,7 +744,8 @@ __global__ __launch_bounds__(kRankThreads) void list_rank_place_kernel(const Lis
 #pragma unroll
     for (int p = 0; p < kRankParts; ++p) r += C.part[(int64_t)p * n + i];
     // (columns that are not finite, which device calls do not check, may
-    // repeat a rank: a wrong result, never a fault)
+    // repeat a rank, and then another names no row: readers of ord clamp what
+    // they find, and the sums the word of a row that nobody counted)
     r = min(r, n - 1);
     if (C.rank) C.rank[i] = r;
     if (C.ord) C.ord[r] = i;
@@ -1489,8 +1484,8 @@ __global__ __launch_bounds__(kRankThreads) void list_rank_count_kernel(const Lis
     const int e = (int)(loc / nt);
     const int r = (int)(loc - (int64_t)e * nt) * 64 + lane;
     const int rr = min(r, n - 1);
-    // (ranks and rows are clamped to the set: inputs that are not finite,
-    // which device calls do not check, leave a wrong result, never a fault)
+    // (ranks and rows are clamped to the set: with inputs that are not finite,
+    // which device calls do not check, a rank may name no row)
     const int i = min(max(S.zord[rr], 0), n - 1);
     const uint64_t word = J.er[(int64_t)e * n + rr];
     const float eps = __uint_as_float((uint32_t)word);
@@ -2017,8 +2012,8 @@ __global__ __launch_bounds__(kBlock) void list_chunk_kernel(const ListLaunch L, 
     const int i = c * kChunk + lane;
     double v = 0.0;
     if (i < n) {
-        const uint64_t w = J.pk[(int64_t)e * n + i];
-        v = (harm[w & kPackMask] + harm[(w >> kPackBits) & kPackMask]) - harm[w >> (2 * kPackBits)];
+        const Counts c3 = unpack_counts(J.pk[(int64_t)e * n + i], n);
+        v = (harm[c3.xz] + harm[c3.yz]) - harm[c3.z];
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) v = v + __shfl_xor(v, off, 64);
@@ -2085,9 +2080,8 @@ __global__ __launch_bounds__(kSumThreads) void list_sum_kernel(const ListLaunch 
 #pragma unroll
         for (int u = 0; u < kSumU; ++u) {
             const bool in = (c0 + u * kSumWaves) * kChunk + lane < n;
-            v[u] = in ? (h((uint32_t)(w[u] & kPackMask)) + h((uint32_t)((w[u] >> kPackBits) & kPackMask))) -
-                            h((uint32_t)(w[u] >> (2 * kPackBits)))
-                      : 0.0;
+            const Counts c3 = unpack_counts(w[u], n);
+            v[u] = in ? (h(c3.xz) + h(c3.yz)) - h(c3.z) : 0.0;
         }
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1)

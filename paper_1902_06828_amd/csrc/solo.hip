@@ -286,8 +286,7 @@ __global__ __launch_bounds__(kSoloBlock) void ksg_solo_kernel(const Job *__restr
             if (dz == 0) c = n - 1 - min(i, w) - min(n - 1 - i, w);
             if (lane == 0 && gg < gc && i < n) {
                 const int e = e0 + gg;
-                J.pk[(int64_t)e * n + i] = (uint64_t)(uint32_t)a | ((uint64_t)(uint32_t)b << kPackBits) |
-                                           ((uint64_t)(uint32_t)c << (2 * kPackBits));
+                J.pk[(int64_t)e * n + i] = pack_counts(a, b, c);
                 if (J.diag_eps) J.diag_eps[(int64_t)e * n + i] = eps[gg][q];
                 if (J.diag_cnt) {
                     J.diag_cnt[((int64_t)e * 3 + 0) * n + i] = a;
