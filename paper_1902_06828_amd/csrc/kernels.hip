@@ -109,6 +109,13 @@ __device__ __forceinline__ void store_row(const Job &J, int e, int64_t i, int64_
         for (int c = 0; c < 2; ++c)
             J.xt[(((int64_t)c * gG + gg) * J.n + x) * kScanLanes + gl] = J.cols[J.dx + 1 - c][i];
     }
+    if (J.walk && i < kWalkPad) {
+        // the rows past either end, which a step may load (with fewer rows than
+        // pads the last row's thread writes the rest)
+        float *xt = J.xt + ((int64_t)gg * (J.n + 2 * kWalkPad) + kWalkPad) * kScanLanes + gl;
+        const int64_t end = i == J.n - 1 ? kWalkPad : i + 1;
+        for (int64_t q = i; q < end; ++q) xt[(-1 - q) * kScanLanes] = xt[(J.n + q) * kScanLanes] = 0.f;
+    }
     for (int c = 0; c < J.dx; ++c) {
         const float v = J.cols[c][x];
         if (J.walk) J.xt[((int64_t)gg * (J.n + 2 * kWalkPad) + kWalkPad + ri) * kScanLanes + gl] = v;

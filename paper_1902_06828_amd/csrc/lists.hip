@@ -1304,8 +1304,8 @@ __global__ __launch_bounds__(kScanLanes) void list_walk_kernel(const ListLaunch 
     const int e0 = scan_group_first(grp, E), ne = scan_group_first(grp + 1, E) - e0;
     const bool live = lane < ne;
     const uint64_t livem = ballot(live);
-    // rank q's row of the group, q from -kWalkPad to n + kWalkPad - 1 (the pads'
-    // distances in y are +inf, whatever their X)
+    // rank q's row of the group, q from -kWalkPad to n + kWalkPad - 1 (the pads
+    // hold 0 and are +inf away in y)
     const float *xg = J->xt + ((int64_t)grp * (n + 2 * kWalkPad) + kWalkPad) * kScanLanes;
     const uint32_t loff = (uint32_t)min(lane, ne - 1) * 4u;
     const float xq = gload_b(xg + (int64_t)r * kScanLanes, loff), yq = ys[r];
