@@ -994,9 +994,11 @@ constexpr int kSwapListCap = 2048;
 // rows below a radius than lists over (Y, Z): at N = 9995, 201 estimates and 4
 // X columns a pair reads 70 entries of 2 permuted columns instead of 1139 of
 // 4, and then 70 instead of about 2900 rows for n_xz: 26.9 -> 1.05 ms a test.
-// Sets of the same number
-// of Z columns follow one another (the build's parts).
-static void list_caps(int dx, int dy, int dz, int n, int *m1, int *m2);
+// A job of fewer than kListMinEstimates estimates does not pay for lists of
+// its own, 16 KB a row (200 requests of one estimate on one sample, N = 5000,
+// 2 X columns: 15.3 ms and 16.6 GB exchanged, 3.9 ms and 0.65 GB on the
+// sample's lists).
+// Sets of the same number of Z columns follow one another (the build's parts).
 static std::vector<SetSpec> plan_sets(const std::vector<JobSpec> &specs, int n_rsets, std::vector<int> *rset_io) {
     const std::vector<int> rset_of = *rset_io;
     const char *rk_env = std::getenv("MTE_RANK_COUNTS");
@@ -1020,7 +1022,8 @@ static std::vector<SetSpec> plan_sets(const std::vector<JobSpec> &specs, int n_r
             S.rank_y = S.walk;
         }
         if (S.walk) continue;
-        const bool swap = S.ranked && sp.dx >= 2 && sp.theiler == 0 && list_wavelet_lds(sp.n) > 0;
+        const bool swap = S.ranked && sp.dx >= 2 && sp.theiler == 0 && sp.n_est() >= kListMinEstimates &&
+                          list_wavelet_lds(sp.n) > 0;
         if (!swap) {
             S.lists = 1;
             dxmax[(size_t)rset_of[j]] = std::max(dxmax[(size_t)rset_of[j]], sp.dx);
