@@ -67,16 +67,19 @@ struct Job {
     int32_t *diag_cnt;            // optional [n_est][3][n] (n_xz, n_yz, n_z)
     // neighbour-list path only (see ListSet): list set index, and the
     // permuted X columns transposed so that the estimates of one row are
-    // adjacent, in scan groups (scan_groups): xt[c][g][i][l] = X_c[pi_e(i)],
-    // e the l-th estimate of group g ([dx][groups][n][64]) for the scan (xp
-    // holds the same values estimate-major for the fallback).  The per-row
-    // counts go to pk; eps and cnt are the caller's diagnostics ([n_est][n],
-    // [n_est][3][n]) or null.
+    // adjacent, in scan groups: the jobs of a set with the same k and dx (a scan
+    // class) take their estimates together, this one's from place t0 of the
+    // class's T on, and xt, the class's, is xt[c][g][i][l] = X_c[pi(i)] of the
+    // l-th estimate of group g ([dx][groups][n][xtw], scan_groups and
+    // scan_width of T) for the scan (xp holds the same values estimate-major
+    // for the fallback).  The per-row counts go to pk; eps and cnt are the
+    // caller's diagnostics ([n_est][n], [n_est][3][n]) or null.
     // A swapped job (swap) scans with the sides exchanged: set is a set over
     // its X columns, row m stands for the row i with pi_e(i) = m, and xt holds
     // that row's Z and Y (xt[0] the Z, xt[1] the Y column; sdx = 2 columns,
     // else sdx = dx).  rset is the set of its (Y, Z) sample (= set otherwise).
     int set, rset, swap, sdx;
+    int t0, T, xtw;
     float *xt;
     int theiler;                  // Theiler window w: pairs with |i - j| <= w are left out
     int reps;                     // replications R (rows: R blocks of n/R, replication-major)
@@ -103,7 +106,8 @@ struct Job {
     uint64_t *er;
     // A job without Z, one X and one Y column (walk) takes no lists: its rows
     // go by rank in y (zrank, xr and xt's rows), neighbours in y are
-    // neighbouring ranks (xt has kWalkPad rows before and after each group's).
+    // neighbouring ranks (xt has kWalkPad rows before and after each group's,
+    // and xtw is kScanLanes: a step's rows are then constant offsets).
     // rad: radii by row ([n_est][n])
     int walk;
     float *rad;
@@ -206,19 +210,25 @@ constexpr int kListCounterWords = kListStatWord + kListStatSlots * kListStatStri
 constexpr int kKeyShift = 19;                 // 4096 key buckets
 constexpr int kKeyBins = 1 << (32 - kKeyShift - 1);
 
-// Scan groups of a job: its E estimates in ceil(E / 64) groups of nearly
+// Scan groups of a class: its E estimates in G = ceil(E / 64) groups of nearly
 // equal size, group g holding the estimates g*E/G .. (g+1)*E/G - 1, one lane
-// each.
+// each; a row of a group takes scan_width(E) words of xt.
 constexpr int kScanLanes = 64;
+MTE_HD inline int scan_width(int n_est) { return n_est < kScanLanes ? n_est : kScanLanes; }
 MTE_HD inline int scan_groups(int n_est) { return (n_est + kScanLanes - 1) / kScanLanes; }
 MTE_HD inline int scan_group_first(int g, int n_est) { return (int)((int64_t)g * n_est / scan_groups(n_est)); }
 MTE_HD inline int scan_group_of(int e, int n_est) {
     return (int)((((int64_t)e + 1) * scan_groups(n_est) - 1) / n_est);
 }
 
-// A range of rows (positions in the set's row order) of one scan group.
+// A range of rows (positions in the set's row order) of one scan group; `job`
+// is the first job of its class, whose jobs are class_jobs[first .. first +
+// n_jobs - 1] in order of their t0.
 struct ScanUnit {
-    int32_t job, group, row0, nrows;
+    int32_t job, group, row0, nrows, first, n_jobs;
+};
+struct ClassJob {
+    int32_t t0, job;
 };
 
 // A column to be ranked by value: its rows' ranks, the row of each rank and
@@ -263,12 +273,14 @@ struct ListLaunch {
     // is x's block count).
     const int64_t *xcd_off;
     const ScanUnit *units;
+    const ClassJob *class_jobs;
     int unit_t;
     int64_t scan_blocks;          // grid of the scan
     // the same for the walk jobs
     const int64_t *walk_xcd_off;
     const ScanUnit *walk_units;
     int walk_unit_t, walk_window; // walk_window: some walk job has a Theiler window
+    int walk_many;                // some walk unit's lanes belong to several jobs
     int64_t walk_blocks;
     size_t walk_lds;              // LDS bytes of their counts: two sorted columns
     int scan_step;                // list entries per step of the scan's lane-by-lane loops (4, 8)

@@ -99,27 +99,27 @@ constexpr int kPermPer = kPermRows / kPermThreads;     // rows per thread
 // Row i of estimate e takes source row x: every copy of the X columns that the
 // job's path reads.
 __device__ __forceinline__ void store_row(const Job &J, int e, int64_t i, int64_t x) {
-    // the scan's copy: group g's estimates of one row in 64 adjacent words
-    const int gE = J.n_est, gG = scan_groups(gE), gg = scan_group_of(e, gE);
-    const int gl = e - scan_group_first(gg, gE);
+    // the scan's copy: group g's estimates of one row in gw adjacent words, gc
+    // from a column to the next (row times width fits a 24-bit multiply)
+    const int gT = max(J.T, 1), t = J.t0 + e, gg = scan_group_of(t, gT), gw = J.xtw;
+    const int64_t gr = J.n + (J.walk ? 2 * kWalkPad : 0), gc = scan_groups(gT) * gr * gw;
+    float *xg = J.xt + (gg * gr + (J.walk ? kWalkPad : 0)) * gw + (t - scan_group_first(gg, gT));
+    auto row = [&](int64_t r) { return ((uint32_t)r & 0xffffffu) * ((uint32_t)gw & 0xffu); };
     const int64_t ri = J.xr ? (int64_t)min(max(J.zrank[i], 0), J.n - 1) : 0;
     if (J.xw) J.xw[(int64_t)e * J.n + i] = (uint16_t)x;
     if (J.swap) {
         // row x of the swapped scan stands for row i: its Z and Y
-        for (int c = 0; c < 2; ++c)
-            J.xt[(((int64_t)c * gG + gg) * J.n + x) * kScanLanes + gl] = J.cols[J.dx + 1 - c][i];
+        for (int c = 0; c < 2; ++c) xg[c * gc + row(x)] = J.cols[J.dx + 1 - c][i];
     }
     if (J.walk && i < kWalkPad) {
         // the rows past either end, which a step may load (with fewer rows than
         // pads the last row's thread writes the rest)
-        float *xt = J.xt + ((int64_t)gg * (J.n + 2 * kWalkPad) + kWalkPad) * kScanLanes + gl;
-        const int64_t end = i == J.n - 1 ? kWalkPad : i + 1;
-        for (int64_t q = i; q < end; ++q) xt[(-1 - q) * kScanLanes] = xt[(J.n + q) * kScanLanes] = 0.f;
+        const int end = i == J.n - 1 ? kWalkPad : (int)i + 1;
+        for (int q = (int)i; q < end; ++q) xg[(-1 - q) * gw] = xg[row(J.n + q)] = 0.f;
     }
     for (int c = 0; c < J.dx; ++c) {
         const float v = J.cols[c][x];
-        if (J.walk) J.xt[((int64_t)gg * (J.n + 2 * kWalkPad) + kWalkPad + ri) * kScanLanes + gl] = v;
-        else if (J.xt && !J.swap) J.xt[(((int64_t)c * gG + gg) * J.n + i) * kScanLanes + gl] = v;
+        if (J.xt && !J.swap) xg[c * gc + row(J.walk ? ri : i)] = v;
         J.xp[((int64_t)e * J.dx + c) * J.n + i] = v;
         if (J.xr) J.xr[((int64_t)e * J.dx + c) * J.n + ri] = v;
     }

@@ -916,6 +916,21 @@ __device__ __forceinline__ void pin_step(const Step<NU> &s) {
                      "s"(s.d[u + 3]), "s"(s.j[u + 3]));
 }
 
+// The job of each lane's estimate, the t-th of the unit's class (lanes may
+// belong to different jobs of one set).
+struct LaneJob {
+    int job, e;
+};
+__device__ __forceinline__ LaneJob lane_job(const ListLaunch &L, Const<ScanUnit> *U, int t) {
+    const ClassJob *c = L.class_jobs + U->first;
+    int lo = 0, hi = U->n_jobs - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (c[mid].t0 <= t) lo = mid; else hi = mid - 1;
+    }
+    return LaneJob{c[lo].job, t - c[lo].t0};
+}
+
 // Wave-uniform helpers.
 __device__ __forceinline__ uint64_t ballot(bool p) { return __ballot(p); }
 // The lane mask of one compare as the compare writes it (no round trip of the
@@ -926,8 +941,12 @@ __device__ __forceinline__ float bcast(float v, int o) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), o));
 }
 __device__ __forceinline__ int bcast(int v, int o) { return __builtin_amdgcn_readlane(v, o); }
+__device__ __forceinline__ const float *bcast(const float *v, int o) {
+    const uint64_t a = (uint64_t)v;
+    return (const float *)((uint64_t)(uint32_t)bcast((int)(a >> 32), o) << 32 | (uint32_t)bcast((int)a, o));
+}
 
-// A wave takes one row and one scan group of a job, a lane per estimate, so
+// A wave takes one row and one scan group of a class, a lane per estimate, so
 // that a step's list entries are the same for all lanes: they come through
 // the scalar cache into scalar registers, and the only vector loads are the
 // X gathers, 256 aligned bytes per entry (xt holds a group's estimates of one
@@ -976,24 +995,27 @@ __global__ __launch_bounds__(kScanLanes) void list_scan_kernel(const ListLaunch 
     Const<ScanUnit> *U = as_const(L.units) + (x + lo * kXcds);
     const int at = (int)(k - xo[lo]);
     const int jb = U->job, grp = U->group, il = U->row0 + at;
+    const bool one_job = U->n_jobs == 1;
     Const<Job> *J = as_const(L.jobs) + jb;
     Const<ListSet> *S = as_const(L.sets) + J->set;
-    const int n = J->n, E = J->n_est, dx = J->sdx;
+    const int n = J->n, E = J->T, dx = J->sdx;
     const bool swap = J->swap;
     const int i = S->order ? as_const(S->order)[il] : il;
     const int e0 = scan_group_first(grp, E), ne = scan_group_first(grp + 1, E) - e0;
     const bool live = lane < ne;
-    const int e = e0 + min(lane, ne - 1);
     const uint64_t livem = ballot(live);
     const int coop = L.coop_lanes;
     const LEnt *l1 = S->l1 + (int64_t)i * S->s1, *l2 = S->l2 + (int64_t)i * S->s2;
 
-    // X of row j under this lane's estimate: group column + 64 j + lane
-    const int64_t cs = (int64_t)scan_groups(E) * n * kScanLanes;
-    const float *xg = J->xt + (int64_t)grp * n * kScanLanes;
+    // X of row j under this lane's estimate: group column + xtw j + lane
+    const int64_t cs = (int64_t)scan_groups(E) * n * J->xtw;
+    const float *xg = J->xt + (int64_t)grp * n * J->xtw;
+    // (row4 in a vector register: the offset is then one multiply-add of 24 bits)
     const uint32_t loff = (uint32_t)min(lane, ne - 1) * 4u;
+    uint32_t row4 = (uint32_t)J->xtw * 4u;
+    asm volatile("" : "+v"(row4));
     auto xval = [&](int c, uint32_t j, uint32_t off) {
-        return gload_b(xg + c * cs, j * (kScanLanes * 4u) + off);
+        return gload_b(xg + c * cs, (j & 0xffffffu) * (row4 & 0xffffffu) + off);
     };
     float xq[DXM];
     Unroll<0, DXM>::upto(dx, [&](auto cc) {
@@ -1205,51 +1227,60 @@ __global__ __launch_bounds__(kScanLanes) void list_scan_kernel(const ListLaunch 
         }
     }
     const bool decided = (dec >> lane) & 1u;
-    if (noz && decided) {
-        // Without Z: n_z is the number of rows outside the window; n_x counts
-        // the rows j != i with |x_j - x_i| < eps.  The permuted values x_j run
-        // over the job's X column, so that count is the range of the sorted
-        // column around x_i: the s with -eps < fl(xs[s] - x_i) < eps
-        // (fl(. - x_i) is monotone), less row i itself and the rows of its
-        // Theiler window.
-        const int w = J->theiler;
-        cz = n - 1 - min(i, w) - min(n - 1 - i, w);
-        const float xv = xq[0];
-        const float *xs = J->xs;
-        int lo2 = 0, hi2 = n;
-        while (lo2 < hi2) {
-            const int mid = (lo2 + hi2) >> 1;
-            if (gload(xs, mid) - xv > -eps) hi2 = mid; else lo2 = mid + 1;
+    // the lane's own job Jl, number jl, and its estimate e there
+    auto finish = [&](auto *Jl, int jl, int e) {
+        if (noz && decided) {
+            // Without Z: n_z is the number of rows outside the window; n_x counts
+            // the rows j != i with |x_j - x_i| < eps.  The permuted values x_j run
+            // over the job's X column, so that count is the range of the sorted
+            // column around x_i: the s with -eps < fl(xs[s] - x_i) < eps
+            // (fl(. - x_i) is monotone), less row i itself and the rows of its
+            // Theiler window.
+            const int w = J->theiler;
+            cz = n - 1 - min(i, w) - min(n - 1 - i, w);
+            const float xv = xq[0];
+            const float *xs = Jl->xs;
+            int lo2 = 0, hi2 = n;
+            while (lo2 < hi2) {
+                const int mid = (lo2 + hi2) >> 1;
+                if (gload(xs, mid) - xv > -eps) hi2 = mid; else lo2 = mid + 1;
+            }
+            const int first = lo2;
+            hi2 = n;
+            while (lo2 < hi2) {
+                const int mid = (lo2 + hi2) >> 1;
+                if (gload(xs, mid) - xv >= eps) hi2 = mid; else lo2 = mid + 1;
+            }
+            cxz = lo2 - first - (0.f < eps ? 1 : 0);
+            for (int j = max(0, i - w); j <= min(n - 1, i + w); ++j)
+                if (j != i && absdiff(xv, xval(0, (uint32_t)j, loff)) < eps) --cxz;
         }
-        const int first = lo2;
-        hi2 = n;
-        while (lo2 < hi2) {
-            const int mid = (lo2 + hi2) >> 1;
-            if (gload(xs, mid) - xv >= eps) hi2 = mid; else lo2 = mid + 1;
-        }
-        cxz = lo2 - first - (0.f < eps ? 1 : 0);
-        for (int j = max(0, i - w); j <= min(n - 1, i + w); ++j)
-            if (j != i && absdiff(xv, xval(0, (uint32_t)j, loff)) < eps) --cxz;
-    }
-    if (live) {
         const int64_t at_e = (int64_t)e * n + i;
         // a ranked pair hands its radius and n_yz over, by the rank of its row;
         // a swapped one its radius and n_xz, by the row it stands at (its
         // count kernel queues it for the redo)
         if (ranked)
-            J->er[(int64_t)e * n + (swap ? i : as_const(J->zrank)[i])] =
+            Jl->er[(int64_t)e * n + (swap ? i : as_const(J->zrank)[i])] =
                 decided ? ((uint64_t)(uint32_t)(swap ? cxz : cyz) << 32) | __float_as_uint(eps) : kRankNone;
         if (!decided && !swap) {
             const uint32_t pos = atomicAdd(&L.counters[0], 1u);
-            L.failq[pos] = ((uint64_t)jb << 40) | ((uint64_t)i * E + e);
+            L.failq[pos] = ((uint64_t)jl << 40) | ((uint64_t)i * Jl->n_est + e);
         } else if (decided && !ranked) {
-            J->pk[at_e] = pack_counts(cxz, cyz, cz);
-            if (J->eps) J->eps[at_e] = eps;
-            if (J->cnt) {
-                J->cnt[((int64_t)e * 3 + 0) * n + i] = cxz;
-                J->cnt[((int64_t)e * 3 + 1) * n + i] = cyz;
-                J->cnt[((int64_t)e * 3 + 2) * n + i] = cz;
+            Jl->pk[at_e] = pack_counts(cxz, cyz, cz);
+            if (Jl->eps) Jl->eps[at_e] = eps;
+            if (Jl->cnt) {
+                Jl->cnt[((int64_t)e * 3 + 0) * n + i] = cxz;
+                Jl->cnt[((int64_t)e * 3 + 1) * n + i] = cyz;
+                Jl->cnt[((int64_t)e * 3 + 2) * n + i] = cz;
             }
+        }
+    };
+    if (live) {
+        if (one_job) {
+            finish(J, jb, e0 + lane);
+        } else {
+            const LaneJob lj = lane_job(L, U, e0 + lane);
+            finish(L.jobs + lj.job, lj.job, lj.e);
         }
         if (L.stats && lane == 0) {
             const int slot = (int)(b & (kListStatSlots - 1));
@@ -1279,7 +1310,10 @@ constexpr int kWalkU = 8;
 constexpr int kWalkFew = 16;
 static_assert(2 * kWalkU <= kWalkPad, "a step past the end stays within the pads");
 
-template <int KMAX, bool WIN>
+// MANY: some unit's lanes belong to several jobs (an instance of its own: with
+// both cases in one the kernel held 76 registers instead of 66, 6 waves per
+// SIMD instead of 7, and took 5% longer).
+template <int KMAX, bool WIN, bool MANY>
 __global__ __launch_bounds__(kScanLanes) void list_walk_kernel(const ListLaunch L) {
     const int lane = tid_x();
     const int64_t b = bid_x();
@@ -1296,7 +1330,7 @@ __global__ __launch_bounds__(kScanLanes) void list_walk_kernel(const ListLaunch 
     const int r = U->row0 + (int)(k - xo[lo]), grp = U->group;
     Const<Job> *J = as_const(L.jobs) + U->job;
     Const<ListSet> *S = as_const(L.sets) + J->rset;
-    const int n = J->n, E = J->n_est, w = J->theiler;
+    const int n = J->n, E = J->T, w = J->theiler;
     const float *ysg = S->ys;
     Const<float> *ys = as_const(ysg);
     Const<int32_t> *yord = as_const(S->yord);
@@ -1370,6 +1404,14 @@ __global__ __launch_bounds__(kScanLanes) void list_walk_kernel(const ListLaunch 
             use(cur);
         }
     }
+    // X by rank of the lane's estimate, and its radii
+    const float *xrow = nullptr;
+    float *rad = nullptr;
+    if constexpr (MANY) {
+        const LaneJob lj = lane_job(L, U, e0 + min(lane, ne - 1));
+        xrow = L.jobs[lj.job].xr + (int64_t)lj.e * n;
+        rad = L.jobs[lj.job].rad + (int64_t)lj.e * n;
+    }
     while (open && (lt > 0 || rt < n)) {
         const float dl = lt > 0 ? absdiff(ys[lt - 1], yq) : inf_f(), dr = rt < n ? absdiff(ys[rt], yq) : inf_f();
         const float dn = __builtin_fminf(dl, dr);
@@ -1383,7 +1425,7 @@ __global__ __launch_bounds__(kScanLanes) void list_walk_kernel(const ListLaunch 
         if (left) lt -= 64; else rt += 64;
         for (uint64_t rest = open; rest; rest &= rest - 1) {
             const int o = lowest(rest);
-            const float *xr = J->xr + (int64_t)(e0 + o) * n;
+            const float *xr = MANY ? bcast(xrow, o) : J->xr + (int64_t)(e0 + o) * n;
             const float d = fmax_(absdiff(bcast(xq, o), gload(xr, (uint32_t)qc)), dy);
             // +inf leaves the other lanes' lists as they are
             for (uint64_t cand = cmp_mask(d < bcast(top[KMAX - 1], o)); cand; cand &= cand - 1) {
@@ -1393,7 +1435,8 @@ __global__ __launch_bounds__(kScanLanes) void list_walk_kernel(const ListLaunch 
             seen += 64;
         }
     }
-    if (live) J->rad[(int64_t)(e0 + lane) * n + i] = top[KMAX - 1];
+    if (!MANY) rad = J->rad + (int64_t)(e0 + lane) * n;
+    if (live) rad[i] = top[KMAX - 1];
     if (L.stats && lane == 0) {
         const int slot = (int)(b & (kListStatSlots - 1));
         unsigned long long *st =
@@ -2109,6 +2152,15 @@ void *scan_fn(int step) {
 }
 
 template <int KMAX>
+void *walk_fn(bool win, bool many) {
+    if (many)
+        return win ? reinterpret_cast<void *>(&list_walk_kernel<KMAX, true, true>)
+                   : reinterpret_cast<void *>(&list_walk_kernel<KMAX, false, true>);
+    return win ? reinterpret_cast<void *>(&list_walk_kernel<KMAX, true, false>)
+               : reinterpret_cast<void *>(&list_walk_kernel<KMAX, false, false>);
+}
+
+template <int KMAX>
 void *scan_dx(int dxm, int step) {
     return dxm == 1 ? scan_fn<KMAX, 1>(step) : dxm == 2 ? scan_fn<KMAX, 2>(step) : scan_fn<KMAX, kMaxDx>(step);
 }
@@ -2212,12 +2264,8 @@ int launch_list_wavelet(const ListLaunch &L, void *stream) {
 int launch_list_walk(const ListLaunch &L, void *stream) {
     if (L.walk_blocks <= 0) return 0;
     const bool win = L.walk_window != 0;
-    void *fn = L.kmax == 4   ? (win ? reinterpret_cast<void *>(&list_walk_kernel<4, true>)
-                                    : reinterpret_cast<void *>(&list_walk_kernel<4, false>))
-               : L.kmax == 8 ? (win ? reinterpret_cast<void *>(&list_walk_kernel<8, true>)
-                                    : reinterpret_cast<void *>(&list_walk_kernel<8, false>))
-                             : (win ? reinterpret_cast<void *>(&list_walk_kernel<16, true>)
-                                    : reinterpret_cast<void *>(&list_walk_kernel<16, false>));
+    void *fn = L.kmax == 4 ? walk_fn<4>(win, L.walk_many) : L.kmax == 8 ? walk_fn<8>(win, L.walk_many)
+                                                                        : walk_fn<16>(win, L.walk_many);
     ListLaunch arg = L;
     void *args[] = {(void *)&arg};
     if (hipLaunchKernel(fn, dim3((unsigned)L.walk_blocks), dim3(kScanLanes), args, 0, (hipStream_t)stream) !=

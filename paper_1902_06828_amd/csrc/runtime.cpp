@@ -1106,12 +1106,51 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
         dxm = std::max(dxm, swapped(j) ? 2 : sp.dx);
         n_keys += sp.n_est();
     }
-    // scan units: every job's groups, cut into row ranges and dealt to the
-    // XCDs in turn.  With few groups a group is cut so that the units divide
-    // evenly among the XCDs (C2's 4 groups: halves, so an XCD's L2 holds one
-    // group's columns); MTE_GROUPED=0 and MTE_GROUPED_MANY=0 cut every group
-    // into one range per XCD instead
     auto walks = [&](int j) { return geo[rset_of[j]].walk != 0; };
+    // scan classes: the jobs of one set with the same k and as many X columns
+    // fill the lanes of a wave together.  A wave per job left 63 of 64 lanes
+    // idle where jobs have one estimate: bursts of 400 such requests on one
+    // sample (N = 5000, 3 Z columns) took 7.7 ms with 2 X columns and 14.6 ms
+    // with 3, and take 4.4 and 5.5 so; 40 requests of 4 estimates, one X
+    // column, no Z 1.41 and 0.86 ms; network of 8 targets, T = 3000 50.4 and
+    // 47.8 ms
+    struct Class {
+        int job, T = 0, n_jobs = 0, first = 0;   // first job, estimates, jobs and their place in class_jobs
+        size_t xt = 0;
+    };
+    std::vector<Class> classes;
+    std::vector<int> cls_of(n_ljobs_), t0_of(n_ljobs_);
+    {
+        std::map<std::tuple<int, int, int>, int> ids;
+        for (int j = 0; j < n_ljobs_; ++j) {
+            const JobSpec &sp = specs[j];
+            const int id = ids.emplace(std::make_tuple(set_of[j], sp.dx, sp.k), (int)classes.size()).first->second;
+            if (id == (int)classes.size()) {
+                classes.emplace_back();
+                classes.back().job = j;
+            }
+            cls_of[j] = id;
+            t0_of[j] = classes[id].T;
+            classes[id].T += sp.n_est();
+            ++classes[id].n_jobs;
+        }
+    }
+    std::vector<ClassJob> class_jobs((size_t)n_ljobs_);
+    {
+        int at = 0;
+        for (Class &c : classes) {
+            c.first = at;
+            at += c.n_jobs;
+        }
+        std::vector<int> next;
+        for (const Class &c : classes) next.push_back(c.first);
+        for (int j = 0; j < n_ljobs_; ++j) class_jobs[next[cls_of[j]]++] = ClassJob{t0_of[j], j};
+    }
+    // scan units: every class's groups, cut into row ranges and dealt to the
+    // XCDs in turn.  With few groups a group is cut so that the units divide
+    // evenly among the XCDs (4 groups of 201 estimates: halves, so an XCD's L2
+    // holds one group's columns); MTE_GROUPED=0 and MTE_GROUPED_MANY=0 cut
+    // every group into one range per XCD instead
     struct Units {
         std::vector<ScanUnit> u;
         std::vector<int64_t> xcd_off;
@@ -1120,26 +1159,23 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     };
     auto plan_units = [&](bool walk) {
         Units out;
-        int n_groups = 0, n_of = 0;
-        for (int j = 0; j < n_ljobs_; ++j)
-            if (walks(j) == walk) {
-                n_groups += scan_groups(specs[j].n_est());
-                ++n_of;
-            }
-        if (n_of == 0) return out;
+        int n_groups = 0;
+        for (const Class &cl : classes)
+            if (walks(cl.job) == walk) n_groups += scan_groups(cl.T);
+        if (n_groups == 0) return out;
         const bool dealt = n_ljobs_ == 1 ? env_int("MTE_GROUPED", tc.grouped != 0 ? 1 : 0) != 0
                                          : env_int("MTE_GROUPED_MANY", 1) != 0;
         int cuts = kXcds;
         if (dealt && n_groups >= kUnitsPerXcd * kXcds) cuts = 1;
         else if (dealt)
             while (cuts > 1 && n_groups * (cuts / 2) % kXcds == 0) cuts /= 2;
-        for (int j = 0; j < n_ljobs_; ++j) {
-            if (walks(j) != walk) continue;
-            const JobSpec &sp = specs[j];
-            for (int g = 0; g < scan_groups(sp.n_est()); ++g)
+        for (const Class &cl : classes) {
+            if (walks(cl.job) != walk) continue;
+            const int n = specs[cl.job].n;
+            for (int g = 0; g < scan_groups(cl.T); ++g)
                 for (int q = 0; q < cuts; ++q) {
-                    const int r0 = (int)((int64_t)sp.n * q / cuts), r1 = (int)((int64_t)sp.n * (q + 1) / cuts);
-                    out.u.push_back(ScanUnit{j, g, r0, r1 - r0});
+                    const int r0 = (int)((int64_t)n * q / cuts), r1 = (int)((int64_t)n * (q + 1) / cuts);
+                    out.u.push_back(ScanUnit{cl.job, g, r0, r1 - r0, cl.first, cl.n_jobs});
                 }
         }
         const int nu = (int)out.u.size();
@@ -1215,7 +1251,15 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
             bytes = align_up(bytes + sizeof(int32_t) * (size_t)sp.n, 256);
         }
     }
-    struct Off { size_t xt, xp, pk, xs, chunk, xr, er, rad; bool wavelet; };
+    auto width_of = [&](const Class &cl) { return walks(cl.job) ? kScanLanes : scan_width(cl.T); };
+    for (Class &cl : classes) {
+        const JobSpec &sp = specs[cl.job];
+        cl.xt = bytes;
+        bytes = align_up(bytes + sizeof(float) * ((size_t)sp.n + (walks(cl.job) ? 2 * kWalkPad : 0)) *
+                                     width_of(cl) * scan_groups(cl.T) * (swapped(cl.job) ? 2 : sp.dx),
+                         256);
+    }
+    struct Off { size_t xp, pk, xs, chunk, xr, er, rad; bool wavelet; };
     std::vector<Off> offs(n_ljobs_);
     std::vector<int64_t> rank_off(n_ljobs_ + 1, 0);
     size_t wavelet_lds = 0;
@@ -1224,10 +1268,6 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     for (int j = 0; j < n_ljobs_; ++j) {
         const JobSpec &sp = specs[j];
         const size_t pairs = (size_t)sp.n * sp.n_est();
-        offs[j].xt = bytes;
-        bytes = align_up(bytes + sizeof(float) * ((size_t)sp.n + (walks(j) ? 2 * kWalkPad : 0)) * kScanLanes *
-                                     scan_groups(sp.n_est()) * (swapped(j) ? 2 : sp.dx),
-                         256);
         offs[j].xp = bytes;
         bytes = align_up(bytes + sizeof(float) * pairs * sp.dx, 256);
         rank_off[j + 1] = rank_off[j];
@@ -1275,7 +1315,8 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     const size_t t_offs = align_up(
         sizeof(int64_t) * (6 * (size_t)(n_ljobs_ + 1) + 2 * ((size_t)n_sets + 1) + su.xcd_off.size() + wu.xcd_off.size()),
         256);
-    const size_t t_units = align_up(sizeof(ScanUnit) * (su.u.size() + wu.u.size()), 256);
+    const size_t t_units = align_up(
+        sizeof(ScanUnit) * (su.u.size() + wu.u.size()) + sizeof(ClassJob) * class_jobs.size(), 256);
     const size_t t_cols = align_up(sizeof(RankCol) * (size_t)n_rank_cols, 256);
     const size_t tbytes = t_jobs + t_sets + t_keys + t_offs + t_units + t_cols;
     if (measure) {
@@ -1382,7 +1423,10 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
         J.theiler = sp.theiler;
         J.reps = sp.reps;
         J.rep_shuffle = sp.rep_shuffle;
-        J.xt = reinterpret_cast<float *>(sb + offs[j].xt);
+        J.t0 = t0_of[j];
+        J.T = classes[cls_of[j]].T;
+        J.xtw = width_of(classes[cls_of[j]]);
+        J.xt = reinterpret_cast<float *>(sb + classes[cls_of[j]].xt);
         J.xp = reinterpret_cast<float *>(sb + offs[j].xp);
         if (sp.dz == 0 || (offs[j].wavelet && !swapped(j))) {
             const size_t nb = sizeof(float) * (size_t)sp.n;
@@ -1428,6 +1472,7 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     const size_t units_at = t_jobs + t_sets + t_keys + t_offs;
     put(hs + units_at, su.u);
     put(hs + units_at + sizeof(ScanUnit) * su.u.size(), wu.u);
+    put(hs + units_at + sizeof(ScanUnit) * (su.u.size() + wu.u.size()), class_jobs);
     put(hs + units_at + t_units, rank_cols);
     ljobs_dev_ = reinterpret_cast<Job *>(tb);
     lblk_off_ = od + 2 * nj1;
@@ -1459,6 +1504,7 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     L.coop_lanes = env_int("MTE_COOP_LANES", tc.coop_lanes > 0 ? tc.coop_lanes : kCoopLanes);
     L.xcd_off = od + o_units;
     L.units = reinterpret_cast<const ScanUnit *>(tb + units_at);
+    L.class_jobs = reinterpret_cast<const ClassJob *>(L.units + su.u.size() + wu.u.size());
     L.unit_t = su.t;
     L.scan_blocks = su.blocks;
     L.walk_xcd_off = od + o_units + su.xcd_off.size();
@@ -1466,7 +1512,8 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     L.walk_unit_t = wu.t;
     L.walk_blocks = wu.blocks;
     L.walk_lds = 0;
-    L.walk_window = 0;
+    L.walk_window = L.walk_many = 0;
+    for (const ScanUnit &u : wu.u) L.walk_many |= u.n_jobs > 1;
     for (int j = 0; j < n_ljobs_; ++j)
         if (walks(j)) {
             L.walk_lds = std::max(L.walk_lds, 2 * sizeof(float) * (size_t)specs[j].n);
