@@ -1068,6 +1068,15 @@ static std::vector<SetSpec> plan_sets(const std::vector<JobSpec> &specs, int n_r
 
 constexpr int kPermTablePerCu = 2;   // estimates per CU from which the permutations run as tables
 constexpr int kUnitsPerXcd = 4;   // fewest scan units per XCD for the XCD-dealt order
+// Counts in wavelet matrices take one block per estimate however few there
+// are, ranges of ranks a wave per 64 rows of each.  A test with one Z column,
+// ranges and wavelets: N = 9995, 8 estimates 315 and 420 us, 32 389 and 443,
+// 64 488 and 494, 96 586 and 543; N = 4000, 8 172 and 193, 64 209 and 211;
+// N = 2000, 8 122 and 123, 96 143 and 135; N = 1000, 8 101 and 91.  The X column
+// of a job that a wavelet counts is ranked first, N^2 compares, which its
+// estimates share: jobs of fewer than kListMinEstimates take the ranges.
+constexpr int kWaveletMinEstimates = 64;
+constexpr int kWaveletSmallN = 2048;
 
 int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<int> &sample_of, int n_samples,
                          const TileChoice &tc, hipStream_t s, size_t *measure) {
@@ -1262,6 +1271,10 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     struct Off { size_t xp, pk, xs, chunk, xr, er, rad; bool wavelet; };
     std::vector<Off> offs(n_ljobs_);
     std::vector<int64_t> rank_off(n_ljobs_ + 1, 0);
+    int64_t wavelet_est = 0;      // estimates that wavelet blocks could count
+    for (int j = 0; j < n_ljobs_; ++j)
+        if (geo[rset_of[j]].ranked && (specs[j].dx == 1 || swapped(j)) && specs[j].theiler == 0)
+            wavelet_est += specs[j].n_est();
     size_t wavelet_lds = 0;
     int n_rank_cols = 0, rdxm = 1;
     for (int t = 0; t < n_sets; ++t) n_rank_cols += geo[t].ranked + geo[t].rank_y;   // z, y
@@ -1272,10 +1285,12 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
         bytes = align_up(bytes + sizeof(float) * pairs * sp.dx, 256);
         rank_off[j + 1] = rank_off[j];
         // a ranked set's job with one X column and no window is counted in a
-        // wavelet matrix when that fits a block's LDS (N up to about 21000),
-        // else over the ranges of ranks
+        // wavelet matrix when that fits a block's LDS (N up to about 21000) and
+        // pays, else over the ranges of ranks
         const bool ranked = geo[rset_of[j]].ranked;
-        const size_t wl = ranked && (sp.dx == 1 || swapped(j)) && sp.theiler == 0 ? list_wavelet_lds(sp.n) : 0;
+        const bool pays = swapped(j) || (sp.dx == 1 && sp.n_est() >= kListMinEstimates &&
+                                         (wavelet_est >= kWaveletMinEstimates || sp.n <= kWaveletSmallN));
+        const size_t wl = ranked && pays && sp.theiler == 0 ? list_wavelet_lds(sp.n) : 0;
         offs[j].wavelet = wl > 0;
         wavelet_lds = std::max(wavelet_lds, wl);
         if (ranked) {

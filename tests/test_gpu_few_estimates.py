@@ -9,6 +9,7 @@ import numpy as np
 import pytest
 
 import paper_1902_06828_amd as mte
+import synth
 
 pytestmark = pytest.mark.gpu
 
@@ -101,3 +102,17 @@ def test_bytes_of_few_estimates(n, dx, dz, S, m1, m2):
     row = 8 * (m1 + 16) + 8 * (m2 + 16) + 16 + 4 * (1 + dz) + (S + 1) * (8 * dx + 16.125)
     say("bytes", n, dx, dz, S, got, row * n)
     assert got < row * n + 65536
+
+
+# one Z column: wavelet matrices from 64 estimates on or up to 2048 rows, rank ranges else; the
+# largest sizes of one and of two wavelet blocks per CU and the last that fits
+@pytest.mark.parametrize("n,S", [(2048, 7), (2049, 7), (2049, 62), (2049, 63), (9984, 63), (16384, 63), (20990, 63)])
+def test_one_z_column_count_forms(monkeypatch, n, S):
+    X, Y, Z = synth.random_points(n, (1, 1, 1), seed=n)
+    out = {}
+    for mode in ("brute", "list"):
+        monkeypatch.setenv("MTE_FORCE_MODE", mode)
+        say("one Z column", n, S, mode)
+        out[mode] = mte.cmi_ksg_diag(X, Y, Z, 4, S, 5, 1)
+    for a, b in zip(out["brute"], out["list"]):
+        assert np.array_equal(a, b)
