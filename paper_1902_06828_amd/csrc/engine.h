@@ -108,9 +108,8 @@ struct Job {
     // go by rank in y (zrank, xr and xt's rows), neighbours in y are
     // neighbouring ranks (xt has kWalkPad rows before and after each group's,
     // and xtw is kScanLanes: a step's rows are then constant offsets).
-    // rad: radii by row ([n_est][n])
+    // A row's radius waits in the low half of its count word (pk).
     int walk;
-    float *rad;
 };
 
 // Counts of the list path are packed kPackBits to a field: N <= kListMaxN.
@@ -144,9 +143,10 @@ constexpr int kNoZSortMax = 16384;
 // the (Y,Z) max-norm distance d_yz(i,j) in the smallest key buckets that fit
 // m1 entries, list 2 the same for the Z distance d_z(i,j) and m2.  A key is
 // the top 12 bits of the distance's float encoding (8 exponent and 4
-// mantissa bits), so a list is ordered by bucket, not fully sorted.  bound[i][w] is a
-// lower bound of every unlisted distance (+inf when nothing is left out), so
-// a radius r <= bound[i][w] is decided by the list alone.
+// mantissa bits), so a list is ordered by bucket, not fully sorted.  Its bound, the
+// floor of the first bucket left out (+inf when nothing is), is a lower bound
+// of every unlisted distance, so a radius up to it is decided by the list
+// alone; the sentinels after the list carry it to the scan.
 struct LEnt {
     float d;                      // d_yz in list 1, d_z in list 2 (the list key)
     int32_t j;                    // row
@@ -166,7 +166,6 @@ struct ListSet {
     LEnt *l1;                     // [n][s1]  (Y,Z) list
     LEnt *l2;                     // [n][s2]  Z list
     int32_t *len;                 // [n][2]
-    float *bound;                 // [n][2]
     // One Z column and n <= kRankMaxN: the rows sorted by z, so that the rows
     // within a radius of a row's z are one range of ranks (float subtraction
     // is monotone in its first operand).  zs[r] the r-th smallest z, zord[r]
@@ -195,7 +194,7 @@ struct BuildPart {
 
 constexpr int kCoopLanes = 4;                 // default cooperative-finish threshold of the scan
 constexpr int kRankMaxN = 32768;              // rank counts: rows ranked by O(n^2) compares
-constexpr int kRankListCap = 8;               // Z-list capacity of a set counted by ranks
+constexpr int kRankListCap = 1;               // Z-list capacity of a set counted by ranks (nothing reads it)
 
 constexpr int kBuildRows = 2;                // rows per build block when N <= 2^16
 constexpr int kLeanRows = 2;                 // rows per block of the compiled-dimension build
@@ -212,10 +211,12 @@ constexpr int kKeyBins = 1 << (32 - kKeyShift - 1);
 
 // Scan groups of a class: its E estimates in G = ceil(E / 64) groups of nearly
 // equal size, group g holding the estimates g*E/G .. (g+1)*E/G - 1, one lane
-// each; a row of a group takes scan_width(E) words of xt.
+// each; a row of a group takes scan_width(E) words of xt, the largest group's
+// (64 words took 11.4 ms where 51 take 10.5: 201 estimates, N = 9995, 4 X and 3
+// Z columns; 3.64 and 3.49 ms at N = 30011, 4 Z columns).
 constexpr int kScanLanes = 64;
-MTE_HD inline int scan_width(int n_est) { return n_est < kScanLanes ? n_est : kScanLanes; }
 MTE_HD inline int scan_groups(int n_est) { return (n_est + kScanLanes - 1) / kScanLanes; }
+MTE_HD inline int scan_width(int n_est) { return (n_est + scan_groups(n_est) - 1) / scan_groups(n_est); }
 MTE_HD inline int scan_group_first(int g, int n_est) { return (int)((int64_t)g * n_est / scan_groups(n_est)); }
 MTE_HD inline int scan_group_of(int e, int n_est) {
     return (int)((((int64_t)e + 1) * scan_groups(n_est) - 1) / n_est);
@@ -233,7 +234,8 @@ struct ClassJob {
 
 // A column to be ranked by value: its rows' ranks, the row of each rank and
 // the values in rank order (rank and ord may be null).  part: [kRankParts][n]
-// scratch.
+// scratch, which lies among the launch's count words (nothing else is written
+// there before the ranks are placed).
 constexpr int kRankParts = 16;
 struct RankCol {
     const float *col;
@@ -247,7 +249,8 @@ struct RankCol {
 struct ListLaunch {
     const Job *jobs;              // device
     const ListSet *sets;          // device
-    const int64_t *lane_off;      // [n_jobs+1] prefix sums of n * n_est
+    const int64_t *fail_off;      // [n_jobs+1] prefix sums of the pairs that may be redone: n * n_est,
+                                  // none of a walk job
     const int64_t *row_off;       // [n_sets+1] prefix sums of the sets' n
     const int64_t *build_off;     // [n_sets+1] prefix sums of the build blocks per set
     int64_t build_blocks;
@@ -255,7 +258,8 @@ struct ListLaunch {
     const int64_t *est_off;       // [n_jobs+1] prefix sums of n_est
     int n_jobs, n_sets;
     int64_t lanes, rows, ests;
-    uint64_t *failq;              // [lanes] (job << 40 | i * n_est + e) of undecided pairs
+    void *failq;                  // undecided pairs, fail_off[job] + i * n_est + e each, in
+    int fail_wide;                // uint64 words if the launch has 2^32 pairs or more, else uint32
     uint32_t *counters;           // [0] undecided pairs; from word kListStatWord,
                                   // kListStatSlots slots of kListStatStride words each
                                   // holding two uint64 totals of list entries read (k-NN
@@ -366,6 +370,15 @@ int launch_list_wavelet(const ListLaunch &L, void *stream);     // the same in w
 size_t list_wavelet_lds(int n);                                 // LDS of such a block, 0: does not fit
 int launch_list_fallback(const ListLaunch &L, void *stream);
 int launch_list_reduce(const ListLaunch &L, const double *harm, void *stream);
+// The digamma sums take one launch where a block per estimate is enough, and
+// then no Job::chunk: a few chunks each, or estimates for a quarter of the
+// chip.  Measured, both launches and one: N = 1000, 1 estimate 8.5 and 4.2 us;
+// N = 1003, 101 estimates 10.4 and 5.8; N = 10^4, 201 estimates 20.1 and 14.0;
+// but 1 estimate 9.6 and 11.5.
+constexpr int kSumFew = 64, kSumEsts = 64;
+inline bool sums_in_one(int max_chunks, int64_t ests) {
+    return max_chunks <= kSumFew || (max_chunks <= kSumChunks && ests >= kSumEsts);
+}
 
 // Host reference of the surrogate permutation (same definition as the device).
 uint64_t mix64(uint64_t z);

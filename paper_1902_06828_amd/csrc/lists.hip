@@ -390,13 +390,13 @@ __global__ __launch_bounds__(kBT) void list_build_kernel(const ListSet *__restri
             if (pos < m2) gstore(out2[r], pos, LEnt{a, j});
         }
     });
-    // lengths, bounds and the sentinels after each list.  A list is whole
+    // lengths and the sentinels after each list.  A list is whole
     // when it holds every row outside the window, or when the first bucket
     // left out is the +inf bucket (every row at a finite distance fitted and
     // the others' differences overflow): a row at +inf can enter neither a
     // radius (every listed distance is at most +inf) nor a strict count below
     // any radius, so leaving it out changes nothing.  Whole lists get +inf
-    // for the bound and the sentinels; bound + 1 ulp would be a NaN there.
+    // sentinels; the bound + 1 ulp would be a NaN there.
     for (int x = tid; x < QB * 2 * kListPad; x += kBT) {
         const int r = x / (2 * kListPad), w = (x / kListPad) & 1, u = x % kListPad;
         if (r >= nq) continue;
@@ -405,14 +405,10 @@ __global__ __launch_bounds__(kBT) void list_build_kernel(const ListSet *__restri
         const uint32_t total = (uint32_t)(n - 1 - min((int)i, tw) - min(n - 1 - (int)i, tw));
         const uint32_t kb = sm.kept_bins[r][w], kr = sm.kept_rows[r][w];
         const bool whole = kr == total || (kb << kKeyShift) >= __float_as_uint(inf_f());
-        const float bound = whole ? inf_f() : __uint_as_float(kb << kKeyShift);
         const float sent = whole ? inf_f() : __uint_as_float((kb << kKeyShift) + 1u);
         if (w == 0) S.l1[i * S.s1 + kr + u] = LEnt{sent, (int32_t)i};
         else S.l2[i * S.s2 + kr + u] = LEnt{sent, (int32_t)i};
-        if (u == 0) {
-            S.len[2 * i + w] = (int32_t)kr;
-            S.bound[2 * i + w] = bound;
-        }
+        if (u == 0) S.len[2 * i + w] = (int32_t)kr;
     }
 }
 
@@ -645,7 +641,7 @@ __global__ __launch_bounds__(kBT) void list_build_dz_kernel(const ListSet *__res
     j0 = tid;
     for (; j0 < full; j0 += step) write_step(j0, false);
     if (j0 < n) write_step(j0, true);
-    // lengths, bounds and the sentinels (as in list_build_kernel; they lie
+    // lengths and the sentinels (as in list_build_kernel; they lie
     // past the kept entries, so no barrier is needed before them)
     for (int x = tid; x < QB * 2 * kListPad; x += kBT) {
         const int r = x / (2 * kListPad), w = (x / kListPad) & 1, u = x % kListPad;
@@ -662,14 +658,10 @@ __global__ __launch_bounds__(kBT) void list_build_dz_kernel(const ListSet *__res
         }
         const uint32_t kbw = w == 0 ? nb & 0xffffu : nb >> 16, krw = w == 0 ? nr & 0xffffu : nr >> 16;
         const bool whole = krw == total || (kbw << kKeyShift) >= __float_as_uint(inf_f());
-        const float bound = whole ? inf_f() : __uint_as_float(kbw << kKeyShift);
         const float sent = whole ? inf_f() : __uint_as_float((kbw << kKeyShift) + 1u);
         if (w == 0) S.l1[i * S.s1 + krw + u] = LEnt{sent, (int32_t)i};
         else S.l2[i * S.s2 + krw + u] = LEnt{sent, (int32_t)i};
-        if (u == 0) {
-            S.len[2 * i + w] = (int32_t)krw;
-            S.bound[2 * i + w] = bound;
-        }
+        if (u == 0) S.len[2 * i + w] = (int32_t)krw;
     }
 }
 
@@ -914,6 +906,14 @@ __device__ __forceinline__ void pin_step(const Step<NU> &s) {
     for (int u = 0; u < NU; u += 4)
         asm volatile("" ::"s"(s.d[u]), "s"(s.j[u]), "s"(s.d[u + 1]), "s"(s.j[u + 1]), "s"(s.d[u + 2]), "s"(s.j[u + 2]),
                      "s"(s.d[u + 3]), "s"(s.j[u + 3]));
+}
+
+// Queue pair (i, e) of job jb, whose E estimates make n * E pairs, for the redo.
+__device__ __forceinline__ void push_failed(const ListLaunch &L, int jb, int64_t i, int E, int e) {
+    const uint32_t pos = atomicAdd(&L.counters[0], 1u);
+    const int64_t at = L.fail_off[jb] + i * E + e;
+    if (L.fail_wide) static_cast<uint64_t *>(L.failq)[pos] = (uint64_t)at;
+    else static_cast<uint32_t *>(L.failq)[pos] = (uint32_t)at;
 }
 
 // The job of each lane's estimate, the t-th of the unit's class (lanes may
@@ -1263,8 +1263,7 @@ __global__ __launch_bounds__(kScanLanes) void list_scan_kernel(const ListLaunch 
             Jl->er[(int64_t)e * n + (swap ? i : as_const(J->zrank)[i])] =
                 decided ? ((uint64_t)(uint32_t)(swap ? cxz : cyz) << 32) | __float_as_uint(eps) : kRankNone;
         if (!decided && !swap) {
-            const uint32_t pos = atomicAdd(&L.counters[0], 1u);
-            L.failq[pos] = ((uint64_t)jl << 40) | ((uint64_t)i * Jl->n_est + e);
+            push_failed(L, jl, i, Jl->n_est, e);
         } else if (decided && !ranked) {
             Jl->pk[at_e] = pack_counts(cxz, cyz, cz);
             if (Jl->eps) Jl->eps[at_e] = eps;
@@ -1406,11 +1405,11 @@ __global__ __launch_bounds__(kScanLanes) void list_walk_kernel(const ListLaunch 
     }
     // X by rank of the lane's estimate, and its radii
     const float *xrow = nullptr;
-    float *rad = nullptr;
+    uint64_t *rad = nullptr;
     if constexpr (MANY) {
         const LaneJob lj = lane_job(L, U, e0 + min(lane, ne - 1));
         xrow = L.jobs[lj.job].xr + (int64_t)lj.e * n;
-        rad = L.jobs[lj.job].rad + (int64_t)lj.e * n;
+        rad = L.jobs[lj.job].pk + (int64_t)lj.e * n;
     }
     while (open && (lt > 0 || rt < n)) {
         const float dl = lt > 0 ? absdiff(ys[lt - 1], yq) : inf_f(), dr = rt < n ? absdiff(ys[rt], yq) : inf_f();
@@ -1435,8 +1434,8 @@ __global__ __launch_bounds__(kScanLanes) void list_walk_kernel(const ListLaunch 
             seen += 64;
         }
     }
-    if (!MANY) rad = J->rad + (int64_t)(e0 + lane) * n;
-    if (live) rad[i] = top[KMAX - 1];
+    if (!MANY) rad = J->pk + (int64_t)(e0 + lane) * n;
+    if (live) *reinterpret_cast<float *>(rad + i) = top[KMAX - 1];
     if (L.stats && lane == 0) {
         const int slot = (int)(b & (kListStatSlots - 1));
         unsigned long long *st =
@@ -1481,7 +1480,8 @@ __global__ __launch_bounds__(kWalkThreads) void list_walk_count_kernel(const Lis
     };
     const int c0 = (int)((int64_t)n * cut / L.est_cuts), c1 = (int)((int64_t)n * (cut + 1) / L.est_cuts);
     for (int i = c0 + tid; i < c1; i += kWalkThreads) {
-        const float eps = J->rad[e * n + i], xq = gload(xe, (uint32_t)i), yq = gload(yc, (uint32_t)i);
+        const float eps = __uint_as_float((uint32_t)J->pk[e * n + i]), xq = gload(xe, (uint32_t)i),
+                    yq = gload(yc, (uint32_t)i);
         // the row itself is in both ranges exactly when eps > 0
         const int own = 0.f < eps ? 1 : 0;
         int nx = range(xs, xq, eps) - own, ny = range(ys, yq, eps) - own;
@@ -1817,8 +1817,7 @@ __global__ __launch_bounds__(kWvThreads) void list_wavelet_kernel(const ListLaun
         }
         if (!(eps >= 0.f)) {                  // in the redo queue, a swapped pair from here
             if (swap) {
-                const uint32_t pos = atomicAdd(&L.counters[0], 1u);
-                L.failq[pos] = ((uint64_t)jb << 40) | ((uint64_t)i * J->n_est + e);
+                push_failed(L, jb, i, J->n_est, e);
             }
             continue;
         }
@@ -1856,9 +1855,10 @@ struct FbPair {
 };
 
 __device__ __forceinline__ FbPair fb_pair(const ListLaunch &L, uint32_t it) {
-    const uint64_t item = L.failq[it];
-    const int jb = (int)(item >> 40);
-    const int64_t r = (int64_t)(item & ((1ull << 40) - 1));
+    const int64_t item = L.fail_wide ? (int64_t) static_cast<const uint64_t *>(L.failq)[it]
+                                     : (int64_t) static_cast<const uint32_t *>(L.failq)[it];
+    const int jb = find_job(L.fail_off, L.n_jobs, item);
+    const int64_t r = item - L.fail_off[jb];
     FbPair p;
     p.J = &L.jobs[jb];
     const int E = p.J->n_est;
@@ -2095,11 +2095,10 @@ __global__ __launch_bounds__(kBlock) void list_reduce_kernel(const ListLaunch L,
 // one thread adds them in index order.  A gather of 64 harmonic numbers costs a
 // CU 64 cycles, so their first kSumHead (the neighbour counts of most rows) are
 // read from LDS.  Bound by latency (a launch, two dependent loads, the last
-// additions); the figures stand with the choice between the two forms.
+// additions); the figures stand with the choice (sums_in_one).
 constexpr int kSumThreads = 1024, kSumWaves = kSumThreads / 64;
 constexpr int kSumHead = 2048;
 constexpr int kSumU = 4;          // chunks of a wave in flight
-constexpr int kSumFew = 64, kSumEsts = 64;
 
 __global__ __launch_bounds__(kSumThreads) void list_sum_kernel(const ListLaunch L, const double *__restrict__ harm) {
     __shared__ double head[kSumHead];
@@ -2306,11 +2305,7 @@ int launch_list_fallback(const ListLaunch &L, void *stream) {
 
 int launch_list_reduce(const ListLaunch &L, const double *harm, void *stream) {
     if (L.ests <= 0 || L.max_chunks <= 0) return 0;
-    // One launch where a block per estimate is enough: a few chunks each, or
-    // estimates for a quarter of the chip.  Measured, both launches and one:
-    // N = 1000, 1 estimate 8.5 and 4.2 us; N = 1003, 101 estimates 10.4 and 5.8;
-    // N = 10^4, 201 estimates 20.1 and 14.0; but 1 estimate 9.6 and 11.5.
-    if (L.max_chunks <= kSumFew || (L.max_chunks <= kSumChunks && L.ests >= kSumEsts)) {
+    if (sums_in_one(L.max_chunks, L.ests)) {
         hipLaunchKernelGGL(list_sum_kernel, dim3((unsigned)L.ests), dim3(kSumThreads), 0, (hipStream_t)stream, L, harm);
         return hipGetLastError() == hipSuccess ? 0 : -1;
     }

@@ -1092,16 +1092,17 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     for (int t = 0; t < n_sets; ++t)
         if (geo[t].job >= 0) set_of[geo[t].job] = t;
     auto swapped = [&](int j) { return set_of[j] != rset_of[j]; };
-    std::vector<int64_t> lane_off(n_ljobs_ + 1, 0), est_off(n_ljobs_ + 1, 0), blk_off(n_ljobs_ + 1, 0),
+    std::vector<int64_t> fail_off(n_ljobs_ + 1, 0), est_off(n_ljobs_ + 1, 0), blk_off(n_ljobs_ + 1, 0),
         row_off(n_sets + 1, 0), build_off(n_sets + 1, 0), item_off(n_ljobs_ + 1, 0);
     lperm_rows_ = 0;
     int kmax = 0, dxm = 0;
     int64_t n_keys = 0;
-    int64_t total_est = 0;
+    int64_t total_est = 0, pairs_all = 0;
     for (const JobSpec &sp : specs) total_est += sp.n_est();
     for (int j = 0; j < n_ljobs_; ++j) {
         const JobSpec &sp = specs[j];
-        lane_off[j + 1] = lane_off[j] + (int64_t)sp.n * sp.n_est();
+        fail_off[j + 1] = fail_off[j] + (geo[rset_of[j]].walk ? 0 : (int64_t)sp.n * sp.n_est());
+        pairs_all += (int64_t)sp.n * sp.n_est();
         est_off[j + 1] = est_off[j] + sp.n_est();
         // many short permutations run as swaps of a table in LDS; few of them
         // beside a build, which is bound by its LDS atomics, row by row (one
@@ -1207,7 +1208,7 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     // scratch layout: per set its lists and Y,Z copy; per job xt, xp, the
     // packed counts and the chunk sums; then the queue
     size_t bytes = 0;
-    std::vector<size_t> o_l1(n_sets), o_l2(n_sets), o_len(n_sets), o_bound(n_sets), o_zy(n_sets),
+    std::vector<size_t> o_l1(n_sets), o_l2(n_sets), o_len(n_sets), o_zy(n_sets),
         o_order(n_sets, 0), o_rank(n_sets, 0);
     int max_rank_n = 0;
     for (int t = 0; t < n_sets; ++t) {
@@ -1220,18 +1221,16 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
         S.dz = sp.dz;
         S.theiler = sp.theiler;
         // rank arrays: zs, zord, zrank, for swapped jobs ys and yrank (n words
-        // each), and each ranked column's partial counts
+        // each), of a walk yord, yrank and the padded sorted column
         if (sp.walk) {
-            // yord, yrank, the partial counts and the padded sorted column
             max_rank_n = std::max(max_rank_n, sp.n);
             o_rank[t] = bytes;
-            bytes = align_up(bytes + ((3 + kRankParts) * (size_t)sp.n + 2 * kWalkPad) * sizeof(float), 256);
+            bytes = align_up(bytes + (3 * (size_t)sp.n + 2 * kWalkPad) * sizeof(float), 256);
         }
         if (sp.ranked) {
             max_rank_n = std::max(max_rank_n, sp.n);
             o_rank[t] = bytes;
-            bytes = align_up(bytes + (3 + kRankParts + (sp.rank_y ? 2 + kRankParts : 0)) * sizeof(float) * (size_t)sp.n,
-                             256);
+            bytes = align_up(bytes + (3 + (sp.rank_y ? 2 : 0)) * sizeof(float) * (size_t)sp.n, 256);
         }
         row_off[t + 1] = row_off[t];
         if (!sp.lists) continue;              // only its ranks are needed
@@ -1248,8 +1247,6 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
         bytes = align_up(bytes + sizeof(LEnt) * ((size_t)sp.n * S.s2 + kListPad), 256);
         o_len[t] = bytes;
         bytes = align_up(bytes + sizeof(int32_t) * 2 * (size_t)sp.n, 256);
-        o_bound[t] = bytes;
-        bytes = align_up(bytes + sizeof(float) * 2 * (size_t)sp.n, 256);
         o_zy[t] = bytes;
         bytes = align_up(bytes + sizeof(float) * (size_t)(sp.dy + sp.dz) * sp.n, 256);
         // a launch of several jobs scans rows grouped by Morton cell of their
@@ -1268,9 +1265,12 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
                                      width_of(cl) * scan_groups(cl.T) * (swapped(cl.job) ? 2 : sp.dx),
                          256);
     }
-    struct Off { size_t xp, pk, xs, chunk, xr, er, rad; bool wavelet; };
+    struct Off { size_t xp, pk, xs, chunk, xr, er; bool wavelet; };
     std::vector<Off> offs(n_ljobs_);
     std::vector<int64_t> rank_off(n_ljobs_ + 1, 0);
+    int max_chunks = 0;
+    for (const JobSpec &sp : specs) max_chunks = std::max(max_chunks, (sp.n + kChunk - 1) / kChunk);
+    const bool one_sum = sums_in_one(max_chunks, total_est);
     int64_t wavelet_est = 0;      // estimates that wavelet blocks could count
     for (int j = 0; j < n_ljobs_; ++j)
         if (geo[rset_of[j]].ranked && (specs[j].dx == 1 || swapped(j)) && specs[j].theiler == 0)
@@ -1306,23 +1306,41 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
         if (walks(j)) {
             offs[j].xr = bytes;
             bytes = align_up(bytes + sizeof(float) * pairs, 256);
-            offs[j].rad = bytes;
-            bytes = align_up(bytes + sizeof(float) * pairs, 256);
         }
-        // sorted X, its ranks, and the partial counts
+        // sorted X and, for the wavelets, its ranks
         offs[j].xs = bytes;
         if (sp.dz == 0 || (wl && !swapped(j))) {
-            bytes = align_up(bytes + (2 + kRankParts) * sizeof(float) * (size_t)sp.n, 256);
+            bytes = align_up(bytes + (wl ? 2 : 1) * sizeof(float) * (size_t)sp.n, 256);
             max_rank_n = std::max(max_rank_n, sp.n);
             ++n_rank_cols;
         }
-        offs[j].pk = bytes;
-        bytes = align_up(bytes + sizeof(uint64_t) * pairs, 256);
         offs[j].chunk = bytes;
-        bytes = align_up(bytes + sizeof(double) * (size_t)sp.n_est() * ((sp.n + kChunk - 1) / kChunk), 256);
+        if (!one_sum)
+            bytes = align_up(bytes + sizeof(double) * (size_t)sp.n_est() * ((sp.n + kChunk - 1) / kChunk), 256);
     }
+    // the count words, and among them first the ranked columns' partial counts
+    const size_t o_pk = bytes;
+    size_t o_parts = o_pk;
+    auto next_part = [&](int n) {
+        const size_t at = o_parts;
+        o_parts = align_up(o_parts + kRankParts * sizeof(int32_t) * (size_t)n, 256);
+        return at;
+    };
+    std::vector<size_t> o_zpart(n_sets, 0), o_ypart(n_sets, 0), o_xpart(n_ljobs_, 0);
+    for (int t = 0; t < n_sets; ++t) {
+        if (geo[t].ranked) o_zpart[t] = next_part(geo[t].n);
+        if (geo[t].rank_y) o_ypart[t] = next_part(geo[t].n);
+    }
+    for (int j = 0; j < n_ljobs_; ++j) {
+        const JobSpec &sp = specs[j];
+        if (sp.dz == 0 || (offs[j].wavelet && !swapped(j))) o_xpart[j] = next_part(sp.n);
+        offs[j].pk = bytes;
+        bytes = align_up(bytes + sizeof(uint64_t) * (size_t)sp.n * sp.n_est(), 256);
+    }
+    bytes = std::max(bytes, o_parts);
     const size_t o_failq = bytes;
-    bytes = align_up(bytes + sizeof(uint64_t) * (size_t)lane_off[n_ljobs_], 256);
+    const bool fail_wide = fail_off[n_ljobs_] > (int64_t)UINT32_MAX;
+    bytes = align_up(bytes + (fail_wide ? sizeof(uint64_t) : sizeof(uint32_t)) * (size_t)fail_off[n_ljobs_], 256);
     // tables: jobs, sets, keys, offsets
     const size_t t_jobs = align_up(sizeof(Job) * n_ljobs_, 256);
     const size_t t_sets = align_up(sizeof(ListSet) * n_sets, 256);
@@ -1350,7 +1368,6 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
             S.l1 = reinterpret_cast<LEnt *>(sb + o_l1[t]);
             S.l2 = reinterpret_cast<LEnt *>(sb + o_l2[t]);
             S.len = reinterpret_cast<int32_t *>(sb + o_len[t]);
-            S.bound = reinterpret_cast<float *>(sb + o_bound[t]);
             S.zy = reinterpret_cast<float *>(sb + o_zy[t]);
             S.order = o_order[t] ? reinterpret_cast<int32_t *>(sb + o_order[t]) : nullptr;
         }
@@ -1359,9 +1376,9 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
             uint8_t *r = sb + o_rank[t];
             S.yord = reinterpret_cast<int32_t *>(r);
             S.yrank = reinterpret_cast<int32_t *>(r + nb);
-            S.ys = reinterpret_cast<float *>(r + (2 + kRankParts) * nb) + kWalkPad;
-            rank_cols.push_back(RankCol{S.cols[0], S.n, reinterpret_cast<int32_t *>(r + 2 * nb), S.yrank, S.yord, S.ys,
-                                        kWalkPad});
+            S.ys = reinterpret_cast<float *>(r + 2 * nb) + kWalkPad;
+            rank_cols.push_back(RankCol{S.cols[0], S.n, reinterpret_cast<int32_t *>(sb + o_ypart[t]), S.yrank, S.yord,
+                                        S.ys, kWalkPad});
         }
         if (sp.ranked) {
             const size_t nb = sizeof(float) * (size_t)S.n;
@@ -1370,13 +1387,13 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
             S.zord = reinterpret_cast<int32_t *>(r + nb);
             S.zrank = reinterpret_cast<int32_t *>(r + 2 * nb);
             rank_cols.push_back(
-                RankCol{S.cols[S.dy], S.n, reinterpret_cast<int32_t *>(r + 3 * nb), S.zrank, S.zord, S.zs, 0});
+                RankCol{S.cols[S.dy], S.n, reinterpret_cast<int32_t *>(sb + o_zpart[t]), S.zrank, S.zord, S.zs, 0});
             if (sp.rank_y) {
-                r += (3 + kRankParts) * nb;
+                r += 3 * nb;
                 S.ys = reinterpret_cast<float *>(r);
                 S.yrank = reinterpret_cast<int32_t *>(r + nb);
                 rank_cols.push_back(
-                    RankCol{S.cols[0], S.n, reinterpret_cast<int32_t *>(r + 2 * nb), S.yrank, nullptr, S.ys, 0});
+                    RankCol{S.cols[0], S.n, reinterpret_cast<int32_t *>(sb + o_ypart[t]), S.yrank, nullptr, S.ys, 0});
             }
         }
     }
@@ -1432,7 +1449,6 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
         if (J.walk) {
             J.zrank = sets[rset_of[j]].yrank;
             J.xr = reinterpret_cast<float *>(sb + offs[j].xr);
-            J.rad = reinterpret_cast<float *>(sb + offs[j].rad);
         }
         J.sdx = swapped(j) ? 2 : sp.dx;
         J.theiler = sp.theiler;
@@ -1449,7 +1465,7 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
             int32_t *rank = offs[j].wavelet ? reinterpret_cast<int32_t *>(sb + offs[j].xs + nb) : nullptr;
             J.xrank = rank;
             rank_cols.push_back(
-                RankCol{J.cols[0], sp.n, reinterpret_cast<int32_t *>(sb + offs[j].xs + 2 * nb), rank, nullptr, J.xs, 0});
+                RankCol{J.cols[0], sp.n, reinterpret_cast<int32_t *>(sb + o_xpart[j]), rank, nullptr, J.xs, 0});
         }
         J.eps = sp.diag_eps;
         J.cnt = sp.diag_cnt;
@@ -1460,7 +1476,7 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
             else J.xr = reinterpret_cast<float *>(sb + offs[j].xr);
             J.er = reinterpret_cast<uint64_t *>(sb + offs[j].er);
         }
-        J.chunk = reinterpret_cast<double *>(sb + offs[j].chunk);
+        J.chunk = one_sum ? nullptr : reinterpret_cast<double *>(sb + offs[j].chunk);
         J.out = sp.out;
         J.keys = keys_dev + kpos;
         std::memcpy(keys_host + kpos, sp.keys.data(), sizeof(EstKey) * J.n_est);
@@ -1471,7 +1487,7 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     int64_t *oh = reinterpret_cast<int64_t *>(hs + t_jobs + t_sets + t_keys);
     int64_t *od = reinterpret_cast<int64_t *>(tb + t_jobs + t_sets + t_keys);
     const size_t nj1 = (size_t)n_ljobs_ + 1;
-    std::memcpy(oh, lane_off.data(), sizeof(int64_t) * nj1);
+    std::memcpy(oh, fail_off.data(), sizeof(int64_t) * nj1);
     std::memcpy(oh + nj1, est_off.data(), sizeof(int64_t) * nj1);
     std::memcpy(oh + 2 * nj1, blk_off.data(), sizeof(int64_t) * nj1);
     std::memcpy(oh + 3 * nj1, row_off.data(), sizeof(int64_t) * (n_sets + 1));
@@ -1497,7 +1513,7 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     ListLaunch &L = ll_;
     L.jobs = ljobs_dev_;
     L.sets = reinterpret_cast<const ListSet *>(tb + t_jobs);
-    L.lane_off = od;
+    L.fail_off = od;
     L.est_off = od + nj1;
     L.row_off = od + 3 * nj1;
     L.build_off = od + 3 * nj1 + (n_sets + 1);
@@ -1505,17 +1521,17 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     L.stats = 0;
     L.n_jobs = n_ljobs_;
     L.n_sets = n_sets;
-    L.lanes = lane_off[n_ljobs_];
+    L.lanes = pairs_all;
     L.rows = row_off[n_sets];
     L.ests = est_off[n_ljobs_];
-    L.failq = reinterpret_cast<uint64_t *>(sb + o_failq);
+    L.failq = sb + o_failq;
+    L.fail_wide = fail_wide ? 1 : 0;
     L.counters = lcounters_.as<uint32_t>();
     L.kmax = kmax <= 4 ? 4 : (kmax <= 8 ? 8 : 16);
     L.dxm = dxm <= 2 ? dxm : kMaxDx;
     L.rank_dxm = rdxm;
     L.fb_grid = std::max(1, 2 * c.n_cu);
-    L.max_chunks = 0;
-    for (const JobSpec &sp : specs) L.max_chunks = std::max(L.max_chunks, (sp.n + kChunk - 1) / kChunk);
+    L.max_chunks = max_chunks;
     L.coop_lanes = env_int("MTE_COOP_LANES", tc.coop_lanes > 0 ? tc.coop_lanes : kCoopLanes);
     L.xcd_off = od + o_units;
     L.units = reinterpret_cast<const ScanUnit *>(tb + units_at);
