@@ -984,6 +984,7 @@ struct SetSpec {
 // 2, 3 and 4 columns (N = 9995, autoregressive series), 1802, 1248 and 772 at
 // the 99.9th percentile.
 constexpr int kSwapListCap = 2048;
+constexpr int kSwapShared = 24;
 
 // The sets of a launch: the jobs' (Y, Z) samples (rset_of), and one per
 // swapped job.  A sample with one Z column and one Y column is counted by
@@ -997,14 +998,19 @@ constexpr int kSwapListCap = 2048;
 // A job of fewer than kListMinEstimates estimates does not pay for lists of
 // its own, 16 KB a row (200 requests of one estimate on one sample, N = 5000,
 // 2 X columns: 15.3 ms and 16.6 GB exchanged, 3.9 ms and 0.65 GB on the
-// sample's lists).
+// sample's lists).  Nor do jobs that share the sample's lists with others, with
+// 2 X columns and fewer than kSwapShared estimates: bursts of 24 requests,
+// N = 10^4, on the sample's lists and exchanged, 6.0 and 7.4 ms with 8
+// estimates each, 9.0 and 9.0 with 16, 12.2 and 10.1 with 24; with 3 columns
+// 15.1 and 6.0 ms with 8.
 // Sets of the same number of Z columns follow one another (the build's parts).
 static std::vector<SetSpec> plan_sets(const std::vector<JobSpec> &specs, int n_rsets, std::vector<int> *rset_io) {
     const std::vector<int> rset_of = *rset_io;
     const char *rk_env = std::getenv("MTE_RANK_COUNTS");
     const bool rank_on = !(rk_env && *rk_env == '0');
     std::vector<SetSpec> sets((size_t)n_rsets);
-    std::vector<int> dxmax((size_t)n_rsets, 0);
+    std::vector<int> dxmax((size_t)n_rsets, 0), n_of((size_t)n_rsets, 0);   // of a sample's jobs
+    for (int r : rset_of) ++n_of[(size_t)r];
     for (size_t j = 0; j < specs.size(); ++j) {
         const JobSpec &sp = specs[j];
         SetSpec &S = sets[(size_t)rset_of[j]];
@@ -1022,7 +1028,8 @@ static std::vector<SetSpec> plan_sets(const std::vector<JobSpec> &specs, int n_r
             S.rank_y = S.walk;
         }
         if (S.walk) continue;
-        const bool swap = S.ranked && sp.dx >= 2 && sp.theiler == 0 && sp.n_est() >= kListMinEstimates &&
+        const int least = n_of[(size_t)rset_of[j]] > 1 && sp.dx == 2 ? kSwapShared : kListMinEstimates;
+        const bool swap = S.ranked && sp.dx >= 2 && sp.theiler == 0 && sp.n_est() >= least &&
                           list_wavelet_lds(sp.n) > 0;
         if (!swap) {
             S.lists = 1;

@@ -52,3 +52,13 @@ def test_bytes_of_a_burst(n, dz, jobs, S):
     want = n * (jobs * (S + 1) * pair_bytes(1, dz) + 3 * (512 if dz == 0 else row_bytes(n, 1, dz)))
     say("bytes of a burst", n, dz, jobs, S, got, want, got / want)
     assert got <= want + 3 * SLOP
+
+
+def test_bytes_of_shared_two_column_jobs():
+    """Jobs of 8 estimates and 2 X columns on one sample use its lists: none of 16 KB a row each."""
+    n, jobs, S = 3000, 24, 7
+    _, _, got = burst(series_of(60, n, 3), jobs, n, 2, 1, 4, S)
+    # a job that arrives first may go alone, and then has lists of its own
+    want = n * (jobs * (S + 1) * pair_bytes(2, 1) + 3 * (row_bytes(n, 2, 1) + 8 * (2048 + 16)))
+    say("two-column jobs", n, jobs, S, got, want, got / want)
+    assert got <= want + 3 * SLOP
