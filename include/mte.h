@@ -508,6 +508,9 @@ int mte_tile_configs(int32_t *cfg_out, int capacity, int *count_out);
  *     several), tuned by the device calls on the batch itself and by the host
  *     calls and greedy rounds on one job of the shape when the batch holds at
  *     least 2^20 (row, estimate) pairs; the request loop only looks them up.
+ *     A shape's first call times only the knobs that its kernels read (without
+ *     Z, with one X and one Y column, the lane order alone; with one Z column
+ *     not the permutation's blocks); the others keep their defaults.
  * Choices persist in a text file, MTE_TUNE_FILE or else
  * $XDG_CACHE_HOME/mte/tune.txt or $HOME/.cache/mte/tune.txt ("off": none),
  * keyed by the GPU architecture and the library build; MTE_TUNE=0 turns

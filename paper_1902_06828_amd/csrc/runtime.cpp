@@ -754,9 +754,26 @@ static int tune_pairs(const std::vector<JobSpec> &specs, hipStream_t s, int mode
     return MTE_OK;
 }
 
+// The forms of a list-path job that need ranks instead of lists or beside them:
+// without Z (with one Y column) its rows walk the ranks of y (MTE_LIST_CAP keeps
+// the lists); with one Z and one Y column it is counted by ranks of z
+// (MTE_RANK_COUNTS=0 keeps the Z list, for comparison).
+static bool walk_form(const JobSpec &sp) {
+    const char *cap = std::getenv("MTE_LIST_CAP");
+    return sp.dz == 0 && sp.dy == 1 && !(cap && *cap);
+}
+
+static bool ranked_form(const JobSpec &sp) {
+    const char *on = std::getenv("MTE_RANK_COUNTS");
+    return sp.dz == 1 && sp.dy == 1 && sp.n <= kRankMaxN && !(on && *on == '0');
+}
+
 // List knobs: the compiled-dimension build's rows per block (2, 4), the
-// scan's cooperative-finish threshold (2, 4, 8), its entries per step (8, 4)
-// and, for launches of one job, the estimate-group lane order (on, off).
+// scan's cooperative-finish threshold (2, 4, 8), its entries per step (8, 4),
+// the permutation's blocks per CU beside the build (2, 3) and, for launches of
+// one job, the estimate-group lane order (on, off); of these only the ones
+// that the launch's kernels read (a walk builds and scans no lists, and a
+// permutation that waits for ranks is not held back).
 static int tune_lists(const std::vector<JobSpec> &lists, hipStream_t s, int mode, TileChoice *out) {
     Ctx &c = ctx();
     const bool several = lists.size() > 1;
@@ -784,15 +801,21 @@ static int tune_lists(const std::vector<JobSpec> &lists, hipStream_t s, int mode
     // write the same values to the same outputs)
     const std::vector<JobSpec> probe =
         mode == kTuneBatch ? lists : (several ? std::vector<JobSpec>{rep, rep} : std::vector<JobSpec>{rep});
+    bool scans = false, ranks = false;
+    for (const auto &sp : probe) {
+        scans |= !walk_form(sp);
+        ranks |= walk_form(sp) || ranked_form(sp);
+    }
     const bool lean = rep.dy == 1 && rep.dz >= 1 && rep.dz <= kBuildFixedDz && rep.n < 65536;
     std::vector<TileChoice> cand;
     std::vector<int> away;   // knobs that differ from the default
     const int step0 = several ? 4 : 8, qb0 = lean ? 2 : 0, grp0 = several ? 0 : 1;
     for (int qb : lean ? std::vector<int>{2, 4} : std::vector<int>{0})
-        for (int coop : {4, 2, 8})
+        for (int coop : scans ? std::vector<int>{4, 2, 8} : std::vector<int>{4})
             for (int grp : several ? std::vector<int>{0} : std::vector<int>{1, 0})
-                for (int step : {step0, 12 - step0})
-                    for (int pcu : {kPermuteBlocksPerCu, kPermuteBlocksPerCu + 1}) {
+                for (int step : scans ? std::vector<int>{step0, 12 - step0} : std::vector<int>{step0})
+                    for (int pcu : ranks ? std::vector<int>{kPermuteBlocksPerCu}
+                                         : std::vector<int>{kPermuteBlocksPerCu, kPermuteBlocksPerCu + 1}) {
                         TileChoice tc = *out;
                         tc.build_qb = qb;
                         tc.coop_lanes = coop;
@@ -988,13 +1011,13 @@ constexpr int kSwapShared = 24;
 
 // The sets of a launch: the jobs' (Y, Z) samples (rset_of), and one per
 // swapped job.  A sample with one Z column and one Y column is counted by
-// ranks of z (MTE_RANK_COUNTS=0 keeps it on the Z list, for comparison).  Its
-// jobs with several X columns and no Theiler window are swapped: the estimate
-// is the same with the roles of the two sides exchanged (X in place, Y and Z
-// permuted by the inverse), and lists over the dx X columns hold far fewer
-// rows below a radius than lists over (Y, Z): at N = 9995, 201 estimates and 4
-// X columns a pair reads 70 entries of 2 permuted columns instead of 1139 of
-// 4, and then 70 instead of about 2900 rows for n_xz: 26.9 -> 1.05 ms a test.
+// ranks of z.  Its jobs with several X columns and no Theiler window are
+// swapped: the estimate is the same with the roles of the two sides exchanged
+// (X in place, Y and Z permuted by the inverse), and lists over the dx X
+// columns hold far fewer rows below a radius than lists over (Y, Z): at
+// N = 9995, 201 estimates and 4 X columns a pair reads 70 entries of 2 permuted
+// columns instead of 1139 of 4, and then 70 instead of about 2900 rows for
+// n_xz: 30.3 -> 1.05 ms a test.
 // A job of fewer than kListMinEstimates estimates does not pay for lists of
 // its own, 16 KB a row (200 requests of one estimate on one sample, N = 5000,
 // 2 X columns: 15.3 ms and 16.6 GB exchanged, 3.9 ms and 0.65 GB on the
@@ -1006,8 +1029,6 @@ constexpr int kSwapShared = 24;
 // Sets of the same number of Z columns follow one another (the build's parts).
 static std::vector<SetSpec> plan_sets(const std::vector<JobSpec> &specs, int n_rsets, std::vector<int> *rset_io) {
     const std::vector<int> rset_of = *rset_io;
-    const char *rk_env = std::getenv("MTE_RANK_COUNTS");
-    const bool rank_on = !(rk_env && *rk_env == '0');
     std::vector<SetSpec> sets((size_t)n_rsets);
     std::vector<int> dxmax((size_t)n_rsets, 0), n_of((size_t)n_rsets, 0);   // of a sample's jobs
     for (int r : rset_of) ++n_of[(size_t)r];
@@ -1020,11 +1041,9 @@ static std::vector<SetSpec> plan_sets(const std::vector<JobSpec> &specs, int n_r
             S.dy = sp.dy;
             S.dz = sp.dz;
             S.theiler = sp.theiler;
-            S.ranked = rank_on && sp.dz == 1 && sp.dy == 1 && sp.n <= kRankMaxN;
+            S.ranked = ranked_form(sp);
             S.lists = 0;
-            // without Z, with one Y column: no lists (MTE_LIST_CAP keeps them)
-            const char *cap = std::getenv("MTE_LIST_CAP");
-            S.walk = sp.dz == 0 && sp.dy == 1 && !(cap && *cap);
+            S.walk = walk_form(sp);
             S.rank_y = S.walk;
         }
         if (S.walk) continue;
