@@ -111,18 +111,21 @@ __device__ __forceinline__ void store_row(const Job &J, int e, int64_t i, int64_
         // row x of the swapped scan stands for row i: its Z and Y
         for (int c = 0; c < 2; ++c) xg[c * gc + row(x)] = J.cols[J.dx + 1 - c][i];
     }
-    if (J.walk && i < kWalkPad) {
-        // the rows past either end, which a step may load (with fewer rows than
-        // pads the last row's thread writes the rest)
-        const int end = i == J.n - 1 ? kWalkPad : (int)i + 1;
-        for (int q = (int)i; q < end; ++q) xg[(-1 - q) * gw] = xg[row(J.n + q)] = 0.f;
-    }
     for (int c = 0; c < J.dx; ++c) {
         const float v = J.cols[c][x];
         if (J.xt && !J.swap) xg[c * gc + row(J.walk ? ri : i)] = v;
         J.xp[((int64_t)e * J.dx + c) * J.n + i] = v;
         if (J.xr) J.xr[((int64_t)e * J.dx + c) * J.n + ri] = v;
     }
+}
+
+// The rows past either end of a walk job's groups, which a step may load: one
+// block of estimate e writes them, a thread each.
+__device__ __forceinline__ void store_pads(const Job &J, int e, int tid) {
+    if (!J.walk || tid >= 2 * kWalkPad) return;
+    const int t = J.t0 + e, gg = scan_group_of(t, J.T);
+    const int64_t at = (int64_t)gg * (J.n + 2 * kWalkPad) + (tid < kWalkPad ? tid : J.n + tid);
+    J.xt[at * J.xtw + (t - scan_group_first(gg, J.T))] = 0.f;
 }
 
 __global__ __launch_bounds__(kPermThreads) void permute_kernel(const Job *__restrict__ jobs, int n_jobs,
@@ -148,6 +151,7 @@ __global__ __launch_bounds__(kPermThreads) void permute_kernel(const Job *__rest
         const int rem = (int)(local % ((int64_t)reps * cpr));
         const int rep = rem / cpr;
         const int c0 = (rem % cpr) * kPermRows;
+        if (rem == 0) store_pads(J, e, tid);
         const EstKey key = J.keys[e];
         // key schedule: domain dn, hash hh
         const uint32_t dn = J.rep_shuffle ? (uint32_t)reps : (uint32_t)nr;
@@ -255,6 +259,7 @@ __global__ __launch_bounds__(kPermTabThreads) void permute_table_kernel(const Jo
         }
         __syncthreads();
     }
+    if (rep == 0) store_pads(J, e, tid);
     const int64_t base = (int64_t)rep * n;
     for (int t = tid; t < n; t += kPermTabThreads) store_row(J, e, base + t, base + tab[t]);
 }
