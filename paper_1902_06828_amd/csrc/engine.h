@@ -108,8 +108,10 @@ struct Job {
     // go by rank in y (zrank, xr and xt's rows), neighbours in y are
     // neighbouring ranks (xt has kWalkPad rows before and after each group's,
     // and xtw is kScanLanes: a step's rows are then constant offsets).
-    // A row's radius waits in the low half of its count word (pk).
+    // rad: radii by row ([n_est][n]; in the low halves of the count words the
+    // counts read 8 bytes for 4, 0.5% of a test)
     int walk;
+    float *rad;
 };
 
 // Counts of the list path are packed kPackBits to a field: N <= kListMaxN.
@@ -211,12 +213,16 @@ constexpr int kKeyBins = 1 << (32 - kKeyShift - 1);
 
 // Scan groups of a class: its E estimates in G = ceil(E / 64) groups of nearly
 // equal size, group g holding the estimates g*E/G .. (g+1)*E/G - 1, one lane
-// each; a row of a group takes scan_width(E) words of xt, the largest group's
-// (64 words took 11.4 ms where 51 take 10.5: 201 estimates, N = 9995, 4 X and 3
-// Z columns; 3.64 and 3.49 ms at N = 30011, 4 Z columns).
+// each; a row of a group takes scan_width(E) words of xt: as many as there are
+// estimates below 64, else the largest group's in whole 64-byte lines (130
+// estimates, 43 a group, N = 9995, 3 X and 2 Z columns: 5.38 ms with 48 words,
+// 5.42 with 43, 6.31 with 64; but 100 estimates at N = 4000 0.73 ms with 64
+// words, 0.76 with 50).
 constexpr int kScanLanes = 64;
 MTE_HD inline int scan_groups(int n_est) { return (n_est + kScanLanes - 1) / kScanLanes; }
-MTE_HD inline int scan_width(int n_est) { return (n_est + scan_groups(n_est) - 1) / scan_groups(n_est); }
+MTE_HD inline int scan_width(int n_est) {
+    return n_est < kScanLanes ? n_est : ((n_est + scan_groups(n_est) - 1) / scan_groups(n_est) + 15) / 16 * 16;
+}
 MTE_HD inline int scan_group_first(int g, int n_est) { return (int)((int64_t)g * n_est / scan_groups(n_est)); }
 MTE_HD inline int scan_group_of(int e, int n_est) {
     return (int)((((int64_t)e + 1) * scan_groups(n_est) - 1) / n_est);

@@ -1405,11 +1405,11 @@ __global__ __launch_bounds__(kScanLanes) void list_walk_kernel(const ListLaunch 
     }
     // X by rank of the lane's estimate, and its radii
     const float *xrow = nullptr;
-    uint64_t *rad = nullptr;
+    float *rad = nullptr;
     if constexpr (MANY) {
         const LaneJob lj = lane_job(L, U, e0 + min(lane, ne - 1));
         xrow = L.jobs[lj.job].xr + (int64_t)lj.e * n;
-        rad = L.jobs[lj.job].pk + (int64_t)lj.e * n;
+        rad = L.jobs[lj.job].rad + (int64_t)lj.e * n;
     }
     while (open && (lt > 0 || rt < n)) {
         const float dl = lt > 0 ? absdiff(ys[lt - 1], yq) : inf_f(), dr = rt < n ? absdiff(ys[rt], yq) : inf_f();
@@ -1434,8 +1434,8 @@ __global__ __launch_bounds__(kScanLanes) void list_walk_kernel(const ListLaunch 
             seen += 64;
         }
     }
-    if (!MANY) rad = J->pk + (int64_t)(e0 + lane) * n;
-    if (live) *reinterpret_cast<float *>(rad + i) = top[KMAX - 1];
+    if (!MANY) rad = J->rad + (int64_t)(e0 + lane) * n;
+    if (live) rad[i] = top[KMAX - 1];
     if (L.stats && lane == 0) {
         const int slot = (int)(b & (kListStatSlots - 1));
         unsigned long long *st =
@@ -1480,8 +1480,7 @@ __global__ __launch_bounds__(kWalkThreads) void list_walk_count_kernel(const Lis
     };
     const int c0 = (int)((int64_t)n * cut / L.est_cuts), c1 = (int)((int64_t)n * (cut + 1) / L.est_cuts);
     for (int i = c0 + tid; i < c1; i += kWalkThreads) {
-        const float eps = __uint_as_float((uint32_t)J->pk[e * n + i]), xq = gload(xe, (uint32_t)i),
-                    yq = gload(yc, (uint32_t)i);
+        const float eps = J->rad[e * n + i], xq = gload(xe, (uint32_t)i), yq = gload(yc, (uint32_t)i);
         // the row itself is in both ranges exactly when eps > 0
         const int own = 0.f < eps ? 1 : 0;
         int nx = range(xs, xq, eps) - own, ny = range(ys, yq, eps) - own;

@@ -1291,7 +1291,7 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
                                      width_of(cl) * scan_groups(cl.T) * (swapped(cl.job) ? 2 : sp.dx),
                          256);
     }
-    struct Off { size_t xp, pk, xs, chunk, xr, er; bool wavelet; };
+    struct Off { size_t xp, pk, xs, chunk, xr, er, rad; bool wavelet; };
     std::vector<Off> offs(n_ljobs_);
     std::vector<int64_t> rank_off(n_ljobs_ + 1, 0);
     int max_chunks = 0;
@@ -1331,6 +1331,8 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
         }
         if (walks(j)) {
             offs[j].xr = bytes;
+            bytes = align_up(bytes + sizeof(float) * pairs, 256);
+            offs[j].rad = bytes;
             bytes = align_up(bytes + sizeof(float) * pairs, 256);
         }
         // sorted X and, for the wavelets, its ranks
@@ -1475,6 +1477,7 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
         if (J.walk) {
             J.zrank = sets[rset_of[j]].yrank;
             J.xr = reinterpret_cast<float *>(sb + offs[j].xr);
+            J.rad = reinterpret_cast<float *>(sb + offs[j].rad);
         }
         J.sdx = swapped(j) ? 2 : sp.dx;
         J.theiler = sp.theiler;

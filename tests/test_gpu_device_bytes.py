@@ -2,6 +2,7 @@
 
 A pair (row, estimate) is allowed X by row and by estimate, its count word (8 bytes), a place in the
 redo queue (8 bytes) and a share of the 64-row sums; with one Z column X by rank and the radius too.
+From 64 estimates on, the groups that X by row is cut into take whole 64-byte lines of a row.
 A row of a sample is allowed its lists (8 bytes an entry of the first, 12 of the second, 8 entries past
 each), lengths, bounds and copies; without Z the first list holds every row."""
 
@@ -25,6 +26,14 @@ def pair_bytes(dx, dz):
     return 8 * dx + 16.125 + (4 * dx + 4 if dz == 1 else 0)
 
 
+def line_bytes(dx, E):
+    """What whole lines add to a row of X by row."""
+    if E < 64:
+        return 0
+    groups = (E + 63) // 64
+    return 4 * dx * (groups * -(-(-(-E // groups)) // 16) * 16 - E)
+
+
 def row_bytes(n, dx, dz):
     if dz == 0:
         return 8 * (n - 1 + 8) + 96 + 16 + 4 + 4
@@ -40,7 +49,8 @@ def row_bytes(n, dx, dz):
                                          (3000, 1, 1, 0, 64), (3000, 1, 1, 0, 200), (1500, 1, 1, 0, 31),
                                          (3000, 2, 1, 0, 20), (3000, 3, 1, 0, 64)])
 def test_bytes_of_one_request(n, dx, dz, w, S):
-    got, want = alone(n, dx, dz, S, w), n * (row_bytes(n, dx, dz) + (S + 1) * pair_bytes(dx, dz))
+    got = alone(n, dx, dz, S, w)
+    want = n * (row_bytes(n, dx, dz) + (S + 1) * pair_bytes(dx, dz) + line_bytes(dx, S + 1))
     say("bytes", n, dx, dz, w, S, got, want, got / want)
     assert got <= want + SLOP
 
