@@ -264,6 +264,8 @@ struct ListLaunch {
     const int64_t *est_off;       // [n_jobs+1] prefix sums of n_est
     int n_jobs, n_sets;
     int64_t lanes, rows, ests;
+    int64_t fail_pairs;           // pairs that may be redone (fail_off[n_jobs]); none: no redo launch
+    int ordered;                  // some set has a row order
     void *failq;                  // undecided pairs, fail_off[job] + i * n_est + e each, in
     int fail_wide;                // uint64 words if the launch has 2^32 pairs or more, else uint32
     uint32_t *counters;           // [0] undecided pairs; from word kListStatWord,

@@ -2173,7 +2173,7 @@ int launch_list_zy(const ListLaunch &L, void *stream) {
 }
 
 int launch_list_order(const ListLaunch &L, void *stream) {
-    if (L.n_jobs <= 1) return 0;
+    if (!L.ordered) return 0;
     hipLaunchKernelGGL(list_order_kernel, dim3((unsigned)L.n_sets), dim3(kSortThreads), 0, (hipStream_t)stream, L);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
@@ -2293,7 +2293,7 @@ int launch_list_rank_count(const ListLaunch &L, void *stream) {
 }
 
 int launch_list_fallback(const ListLaunch &L, void *stream) {
-    if (L.lanes <= 0) return 0;
+    if (L.fail_pairs <= 0) return 0;
     const dim3 grid((unsigned)L.fb_grid), block(kFbThreads);
     if (L.kmax == 4) hipLaunchKernelGGL(list_fallback_kernel<4>, grid, block, 0, (hipStream_t)stream, L);
     else if (L.kmax == 8) hipLaunchKernelGGL(list_fallback_kernel<8>, grid, block, 0, (hipStream_t)stream, L);

@@ -1576,6 +1576,8 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     L.ests = est_off[n_ljobs_];
     L.failq = sb + o_failq;
     L.fail_wide = fail_wide ? 1 : 0;
+    L.fail_pairs = fail_off[n_ljobs_];
+    L.ordered = std::any_of(o_order.begin(), o_order.end(), [](size_t o) { return o != 0; }) ? 1 : 0;
     L.counters = lcounters_.as<uint32_t>();
     L.kmax = kmax <= 4 ? 4 : (kmax <= 8 ? 8 : 16);
     L.dxm = dxm <= 2 ? dxm : kMaxDx;
@@ -1971,9 +1973,9 @@ int Batch::launch_all(hipStream_t s, bool timed) {
         // the scan's row order (launches of several jobs) is needed by the
         // scan only, so it waits on the side stream too
         if (launch_list_order(ll_, side)) return hip_fail(hipGetLastError(), "row order launch");
-        // timed with no row-order kernel (one job), the permutation's end
-        // event is the join
-        const bool join_at_end = timed && ll_.n_jobs <= 1;
+        // timed with no row-order kernel, the permutation's end event is the
+        // join
+        const bool join_at_end = timed && !ll_.ordered;
         if (!join_at_end) MTE_HIP(hipEventRecord(join_, side));
         MTE_HIP(hipStreamWaitEvent(s, join_at_end ? ev[1] : join_, 0));
         if ((rc = begin(s))) return rc;
