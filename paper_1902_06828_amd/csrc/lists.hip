@@ -1603,18 +1603,19 @@ __global__ __launch_bounds__(kRankThreads) void list_rank_count_kernel(const Lis
             const int own = pe > 0.f ? 1 : 0;
             cz -= own;
             cx -= own;
-        } else
-        for (int j = w0 + lane; j - lane <= w1; j += 64) {
-            const bool inw = j <= w1;
-            const int rj = min(max(S.zrank[inw ? j : w1], 0), n - 1);
-            const bool inr = inw && rj >= plo && rj < phi;
-            float d = absdiff(xr[rj], px[0]);
-            Unroll<1, DXM>::upto(dx, [&](auto cc) {
-                constexpr int c = decltype(cc)::value;
-                d = fmax_(d, absdiff(xr[(int64_t)c * n + rj], px[c]));
-            });
-            cz -= __builtin_popcountll(ballot(inr));
-            cx -= __builtin_popcountll(ballot(inr && d < pe));
+        } else {
+            for (int j = w0 + lane; j - lane <= w1; j += 64) {
+                const bool inw = j <= w1;
+                const int rj = min(max(S.zrank[inw ? j : w1], 0), n - 1);
+                const bool inr = inw && rj >= plo && rj < phi;
+                float d = absdiff(xr[rj], px[0]);
+                Unroll<1, DXM>::upto(dx, [&](auto cc) {
+                    constexpr int c = decltype(cc)::value;
+                    d = fmax_(d, absdiff(xr[(int64_t)c * n + rj], px[c]));
+                });
+                cz -= __builtin_popcountll(ballot(inr));
+                cx -= __builtin_popcountll(ballot(inr && d < pe));
+            }
         }
         ent += phi - plo;
         if (lane == o) {
@@ -2274,10 +2275,8 @@ int launch_list_walk(const ListLaunch &L, void *stream) {
     if (L.walk_lds > 65536 - 1024 &&
         hipFuncSetAttribute(cf, hipFuncAttributeMaxDynamicSharedMemorySize, 163840 - 1024) != hipSuccess)
         return -1;
-    return hipLaunchKernel(cf, dim3((unsigned)L.ests, (unsigned)L.est_cuts), dim3(kWalkThreads), args, L.walk_lds, (hipStream_t)stream) ==
-                   hipSuccess
-               ? 0
-               : -1;
+    const dim3 cuts((unsigned)L.ests, (unsigned)L.est_cuts);
+    return hipLaunchKernel(cf, cuts, dim3(kWalkThreads), args, L.walk_lds, (hipStream_t)stream) == hipSuccess ? 0 : -1;
 }
 
 int launch_list_rank_count(const ListLaunch &L, void *stream) {

@@ -1395,7 +1395,8 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     const size_t t_sets = align_up(sizeof(ListSet) * n_sets, 256);
     const size_t t_keys = align_up(sizeof(EstKey) * (size_t)n_keys, 256);
     const size_t t_offs = align_up(
-        sizeof(int64_t) * (6 * (size_t)(n_ljobs_ + 1) + 2 * ((size_t)n_sets + 1) + su.xcd_off.size() + wu.xcd_off.size()),
+        sizeof(int64_t) * (6 * (size_t)(n_ljobs_ + 1) + 2 * ((size_t)n_sets + 1) + su.xcd_off.size() +
+                           wu.xcd_off.size()),
         256);
     const size_t t_units = align_up(
         sizeof(ScanUnit) * (su.u.size() + wu.u.size()) + sizeof(ClassJob) * class_jobs.size(), 256);
