@@ -85,11 +85,12 @@ def build_ops(n, dy, dz):
 
 
 def scan_bytes(dx, entries):
-    """Neighbour-list scan, from the list entries it reads: an entry is
-    8 bytes (distance, row) and also reads the row's dx permuted X values (4
-    bytes each)."""
+    """Neighbour-list scan, what its lanes request: the row's dx permuted X
+    values (4 bytes each) for every list entry that a pair reads.  The entries
+    themselves reach the estimates of a wave by one scalar load each, and the
+    pass over list 1 that counts n_yz gathers nothing."""
     knn, zl = entries
-    return (knn + zl) * (8 + 4 * dx)
+    return (knn + zl) * 4 * dx
 
 
 def counter_record(kernel):
@@ -647,7 +648,7 @@ def main():
         k_ms = stage_ms[stage]["ms_per_launch"]
         if stage == "scan":
             # a gather kernel: HBM bytes from the counter record; the bytes
-            # its lanes request (list entries and permuted X values as issued,
+            # its lanes request (permuted X values as issued,
             # most served by L2) are reported beside them, not as the roof
             bound, unit, peak = "hbm", "GB/s", PEAK_HBM_GBS
             work = measured_traffic(stage)
