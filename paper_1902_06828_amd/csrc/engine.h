@@ -137,7 +137,7 @@ MTE_HD inline Counts unpack_counts(uint64_t w, int n) {
     return Counts{xz < m ? xz : m, yz < m ? yz : m, z < m ? z : m};
 }
 
-// Largest N of a list-path job without Z (its X column is sorted in LDS).
+// Largest N of a list-path job without Z (its two sorted columns lie in LDS).
 constexpr int kNoZSortMax = 16384;
 
 // Neighbour lists of one (Y, Z) sample, shared by every job of a launch whose
@@ -154,7 +154,7 @@ struct LEnt {
     int32_t j;                    // row
 };
 
-constexpr int kListPad = 16;                  // sentinel entries after each row's list
+constexpr int kListPad = 16;                  // sentinel entries after each row's list: two steps
 
 struct ListSet {
     const float *cols[kMaxDy + kMaxDz];   // Y columns, then Z columns
@@ -251,7 +251,7 @@ struct RankCol {
     int pad;                      // words of -inf before and +inf after `sorted`
 };
 
-// One launch of the list path over `n_jobs` jobs (all with dz > 0).
+// One launch of the list path over `n_jobs` jobs.
 struct ListLaunch {
     const Job *jobs;              // device
     const ListSet *sets;          // device
@@ -380,7 +380,7 @@ int launch_list_fallback(const ListLaunch &L, void *stream);
 int launch_list_reduce(const ListLaunch &L, const double *harm, void *stream);
 // The digamma sums take one launch where a block per estimate is enough, and
 // then no Job::chunk: a few chunks each, or estimates for a quarter of the
-// chip.  Measured, both launches and one: N = 1000, 1 estimate 8.5 and 4.2 us;
+// chip.  Kernel times, both launches and one: N = 1000, 1 estimate 8.5 and 4.2 us;
 // N = 1003, 101 estimates 10.4 and 5.8; N = 10^4, 201 estimates 20.1 and 14.0;
 // but 1 estimate 9.6 and 11.5.
 constexpr int kSumFew = 64, kSumEsts = 64;

@@ -9,9 +9,9 @@
 //   build    for each row i, the other rows bucketed by d_yz(i,j) and by
 //            d_z(i,j) (12-bit keys of the float encoding), keeping the
 //            smallest buckets that fit the list capacity, in bucket order,
-//            with a lower bound of every distance left out;
+//            then sentinels with a lower bound of every distance left out;
 //
-// and then, for every (row, estimate) pair, one lane:
+// and then, a wave per row and group of estimates, a lane per estimate:
 //
 //   scan     k-NN over list 1 in bucket order, max(d_x, d_yz) with the
 //            estimate's permuted X; it stops at the first bucket whose floor
@@ -19,9 +19,15 @@
 //            radius is exact when it stopped that way or when the k-th
 //            distance is at most the list's bound.  n_yz counts the entries of
 //            list 1 below eps, n_z and n_xz scan list 2 until its bucket floor
-//            reaches eps, exact when it stopped that way or eps <= its bound.
-//            Without Z (one X column) there is no list 2: n_x comes from range
-//            counts on the sorted X column;
+//            reaches eps, exact when it stopped that way or eps <= its bound;
+//   counts   with one Z column and one Y column n_z and n_xz are ranges of
+//            ranks of z instead: rows of a range counted one by one (rank
+//            counts), or, with one X column and no window, two-dimensional
+//            ranges in a wavelet matrix per estimate.  Such jobs with several
+//            X columns and no window exchange the sides: lists over X, the
+//            permuted columns are Y and Z;
+//   walk     without Z, with one X and one Y column, no lists: radii from the
+//            neighbouring ranks of y, counts from the sorted columns;
 //   fallback the pairs the lists cannot decide (rare) are queued and redone
 //            over all rows (a block per pair, or a wave when they are many);
 //   reduce   the digamma sum per estimate in the same fixed order as the
@@ -875,7 +881,8 @@ __global__ __launch_bounds__(kSortThreads) void list_order_kernel(const ListLaun
 // or only rows at +inf).
 // A step of kU entries that starts at or before the list's end, and the step
 // after it, whose X values are loaded ahead, then need no bounds checks, and
-// the last step of a list always ends on a sentinel, whose bucket-floor test (floor = bound >= radius) is exactly the
+// the last step of a list always ends on a sentinel, whose bucket-floor test
+// (floor = bound >= radius) is exactly the
 // condition under which the list decides the pair.  A sentinel that enters
 // the k-NN list (bound + 1 ulp < k-th distance) leaves a radius above the
 // bound, i.e. an undecided pair, as it should.
@@ -949,10 +956,12 @@ __device__ __forceinline__ const float *bcast(const float *v, int o) {
 // A wave takes one row and one scan group of a class, a lane per estimate, so
 // that a step's list entries are the same for all lanes: they come through
 // the scalar cache into scalar registers, and the only vector loads are the
-// X gathers, 256 aligned bytes per entry (xt holds a group's estimates of one
-// row in adjacent words) at a uniform base.  With the entries loaded per lane
-// the broadcast loads (64 or 96 bytes a lane and step) took two thirds of the
-// vector memory path's cycles; the kernel held 79 registers (20 now).  Whole
+// X gathers, up to 256 adjacent bytes per entry (xt holds a group's estimates
+// of one row in adjacent words) at a uniform base.  With the entries loaded per
+// lane the broadcast loads (64 or 96 bytes a lane and step) took two thirds of
+// the vector memory path's cycles, and the kernel held 79 vector registers
+// instead of 36 (one X column, k <= 4, 8 entries a step; its 106 scalar
+// registers are all there are, so the forms for many columns spill some).  Whole
 // tests, before and after: N = 10^4, dz = 5, 201 estimates 662 -> 560 us;
 // N = 30011, dz = 4, 101 estimates 3.00 -> 2.75 ms; 32 served requests
 // 11.4 -> 9.8 ms; network of 8 targets, T = 3000 101 -> 86 ms; without Z
@@ -971,7 +980,8 @@ __device__ __forceinline__ const float *bcast(const float *v, int o) {
 // more than `coop` of them still need entries (a lane past its own stop reads
 // on without effect: no later entry is below its radius), then finishes the
 // remaining lanes together, 64 list entries per step, one per lane, for each
-// of them in turn.  Entries, distances and tests are the same, so the results are too.
+// of them in turn.  Entries, distances and tests are the same, so the results
+// are too.
 //
 // Phases: the k-NN radius over list 1; n_yz, the entries of list 1 below the
 // radius (every such entry precedes the stop, so no X is gathered); n_z and
@@ -1301,7 +1311,7 @@ __global__ __launch_bounds__(kScanLanes) void list_scan_kernel(const ListLaunch 
 // so a step's X values are adjacent rows, and neighbouring waves read the same
 // ones; for the last lanes xr holds an estimate's X by rank.  Every pair is
 // decided.  n_x and n_y are two binary searches each, on the sorted columns in
-// LDS (a block per estimate).  At N = 9995, 201 estimates the lists of every
+// LDS (one or two blocks per estimate).  At N = 9995, 201 estimates the lists of every
 // row (800 MB) took 0.53 ms to build and 0.62 ms to scan (1.22 ms for
 // the whole test, 0.51 this way): the walk takes 0.33 ms, bound by the waves'
 // chains of dependent loads, the counts 43 us.

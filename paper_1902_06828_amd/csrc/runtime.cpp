@@ -396,11 +396,12 @@ int assign_paths(const std::vector<JobSpec> &specs, std::vector<int> *set_of, in
     std::vector<int> gid(specs.size(), -1);
     for (size_t j = 0; j < specs.size(); ++j) {
         const JobSpec &sp = specs[j];
-        // the list kernels index the transposed X columns with 32-bit
-        // element offsets and a column of the build's copy of Y and Z with
-        // 32-bit byte offsets, and pack a row's counts kPackBits to a field;
-        // without Z the list path needs one X column (its range counts use
-        // the sorted column) and N within the in-LDS sort
+        // the list kernels address a column of the build's copy of Y and Z and
+        // a group's rows of the transposed X with 32-bit byte offsets and pack
+        // a row's counts kPackBits to a field (N <= kListMaxN); without Z the
+        // list path needs one X column (its range counts use the sorted column)
+        // and two sorted columns in LDS.  A job of 2^31 permuted X values or
+        // more, 60 GB of list scratch, stays on the all-pairs kernel
         if (force == 0 || (int64_t)sp.dx * sp.n * sp.n_est() >= ((int64_t)1 << 31)) continue;
         if (sp.n > kListMaxN) continue;
         if (sp.dz == 0 && (sp.dx != 1 || sp.n > kNoZSortMax)) continue;
