@@ -1454,9 +1454,7 @@ __global__ __launch_bounds__(kScanLanes) void list_walk_kernel(const ListLaunch 
     }
 }
 
-constexpr int kWalkThreads = 1024;
-
-__global__ __launch_bounds__(kWalkThreads) void list_walk_count_kernel(const ListLaunch L) {
+__global__ __launch_bounds__(kRowThreads) void list_walk_count_kernel(const ListLaunch L) {
     extern __shared__ uint64_t wv_lds[];
     const int64_t g = bid_x();
     const int cut = (int)__builtin_amdgcn_workgroup_id_y();
@@ -1468,7 +1466,7 @@ __global__ __launch_bounds__(kWalkThreads) void list_walk_count_kernel(const Lis
     const int64_t e = g - as_const(L.est_off)[jb];
     float *xs = reinterpret_cast<float *>(wv_lds), *ys = xs + n;
     const float *xsg = J->xs, *ysg = S->ys, *yc = J->cols[1], *xe = J->xp + e * n;
-    for (int q = tid; q < n; q += kWalkThreads) {
+    for (int q = tid; q < n; q += L.walk_threads) {
         xs[q] = gload(xsg, (uint32_t)q);
         ys[q] = gload(ysg, (uint32_t)q);
     }
@@ -1489,7 +1487,7 @@ __global__ __launch_bounds__(kWalkThreads) void list_walk_count_kernel(const Lis
         return p - first;
     };
     const int c0 = (int)((int64_t)n * cut / L.est_cuts), c1 = (int)((int64_t)n * (cut + 1) / L.est_cuts);
-    for (int i = c0 + tid; i < c1; i += kWalkThreads) {
+    for (int i = c0 + tid; i < c1; i += L.walk_threads) {
         const float eps = J->rad[e * n + i], xq = gload(xe, (uint32_t)i), yq = gload(yc, (uint32_t)i);
         // the row itself is in both ranges exactly when eps > 0
         const int own = 0.f < eps ? 1 : 0;
@@ -1664,8 +1662,7 @@ __global__ __launch_bounds__(kRankThreads) void list_rank_count_kernel(const Lis
 // for a and one for b, a lane per pair, instead of reading the hi - lo rows
 // (on average 740 at N = 10^4) with all lanes over one pair after another:
 // 423 -> 160 us at N = 9995, 201 estimates (the whole test 1.06 -> 0.71 ms).
-constexpr int kWvThreads = 1024;
-constexpr int kWvWaves = kWvThreads / 64;
+constexpr int kWvWaves = kRowThreads / 64;
 constexpr int kWvBits = 16;
 
 struct WvNode {
@@ -1674,7 +1671,7 @@ struct WvNode {
 
 __device__ __forceinline__ int wv_bits(int n) { return 32 - __builtin_clz((unsigned)n); }   // n < 2^bits
 
-__global__ __launch_bounds__(kWvThreads) void list_wavelet_kernel(const ListLaunch L) {
+__global__ __launch_bounds__(kRowThreads) void list_wavelet_kernel(const ListLaunch L) {
     extern __shared__ uint64_t wv_lds[];
     __shared__ int wtot[kWvWaves];
     __shared__ int zeros[kWvBits];
@@ -1685,9 +1682,10 @@ __global__ __launch_bounds__(kWvThreads) void list_wavelet_kernel(const ListLaun
     Const<ListSet> *S = as_const(L.sets) + J->rset;
     const bool swap = J->swap;
     const int n = J->n, e = (int)(g - as_const(L.est_off)[jb]);
-    const int tid = tid_x(), lane = tid & 63;
+    const int tid = tid_x(), lane = tid & 63, nt = L.wavelet_threads, waves = nt / 64;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int nblk = (n + 63) / 64, per = (nblk + kWvWaves - 1) / kWvWaves;
+    const int nblk = (n + 63) / 64, per = (nblk + waves - 1) / waves;
+    if (tid < kWvWaves) wtot[tid] = 0;        // (of the waves that a small block lacks)
     const int nb = wv_bits(n), stride = 2 * nblk + 1;
     WvNode *node = reinterpret_cast<WvNode *>(wv_lds);
     // the sequence, from one buffer into the other level by level
@@ -1697,7 +1695,7 @@ __global__ __launch_bounds__(kWvThreads) void list_wavelet_kernel(const ListLaun
     const uint16_t *src = J->xw + (int64_t)e * n;
     uint16_t *xw = J->xw + (int64_t)(J->n_est + e) * n;
     const int32_t *xrank = swap ? S->yrank : J->xrank;
-    for (int q = tid; q < n; q += kWvThreads) {
+    for (int q = tid; q < n; q += nt) {
         sa[q] = src[q];
         sb[q] = (uint16_t)xrank[q];
     }
@@ -1759,7 +1757,7 @@ __global__ __launch_bounds__(kWvThreads) void list_wavelet_kernel(const ListLaun
     }
     // the sorted X column takes the sequence's place
     const float *xsg = swap ? S->ys : J->xs;
-    for (int q = tid; q < n; q += kWvThreads) xs[q] = gload(xsg, (uint32_t)q);
+    for (int q = tid; q < n; q += nt) xs[q] = gload(xsg, (uint32_t)q);
     __syncthreads();
 
     const float *zs = S->zs;
@@ -1768,7 +1766,7 @@ __global__ __launch_bounds__(kWvThreads) void list_wavelet_kernel(const ListLaun
         const WvNode w = nd[p >> 5];
         return (int)w.ones + __builtin_popcount(w.bits & ((1u << (p & 31)) - 1u));
     };
-    for (int r = tid; r < n; r += kWvThreads) {
+    for (int r = tid; r < n; r += nt) {
         const int i = min(max(zord[r], 0), n - 1);
         const int m0 = swap ? min((int)src[i], n - 1) : r;
         const uint64_t word = er[m0];
@@ -2106,11 +2104,10 @@ __global__ __launch_bounds__(kBlock) void list_reduce_kernel(const ListLaunch L,
 // CU 64 cycles, so their first kSumHead (the neighbour counts of most rows) are
 // read from LDS.  Bound by latency (a launch, two dependent loads, the last
 // additions); the figures stand with the choice (sums_in_one).
-constexpr int kSumThreads = 1024, kSumWaves = kSumThreads / 64;
 constexpr int kSumHead = 2048;
 constexpr int kSumU = 4;          // chunks of a wave in flight
 
-__global__ __launch_bounds__(kSumThreads) void list_sum_kernel(const ListLaunch L, const double *__restrict__ harm) {
+__global__ __launch_bounds__(kRowThreads) void list_sum_kernel(const ListLaunch L, const double *__restrict__ harm) {
     __shared__ double head[kSumHead];
     __shared__ double part[kSumChunks];
     const int64_t g = bid_x();
@@ -2120,18 +2117,19 @@ __global__ __launch_bounds__(kSumThreads) void list_sum_kernel(const ListLaunch 
     const int n = J.n, tid = tid_x(), lane = tid & 63;
     const int wave = (int)__builtin_amdgcn_readfirstlane((uint32_t)tid >> 6);
     const int nch = (n + kChunk - 1) / kChunk, nh = min(n, kSumHead);
+    const int nt = row_threads(L.max_chunks * kChunk), waves = nt / 64;
     const uint64_t *pk = J.pk + (int64_t)e * n;
-    for (int q = tid; q < nh; q += kSumThreads) head[q] = harm[q];
+    for (int q = tid; q < nh; q += nt) head[q] = harm[q];
     __syncthreads();
     auto h = [&](uint32_t c) { return c < (uint32_t)kSumHead ? head[c] : harm[c]; };
-    for (int c0 = wave; c0 < nch; c0 += kSumWaves * kSumU) {
+    for (int c0 = wave; c0 < nch; c0 += waves * kSumU) {
         uint64_t w[kSumU];
         double v[kSumU];
 #pragma unroll
-        for (int u = 0; u < kSumU; ++u) w[u] = pk[min((c0 + u * kSumWaves) * kChunk + lane, n - 1)];
+        for (int u = 0; u < kSumU; ++u) w[u] = pk[min((c0 + u * waves) * kChunk + lane, n - 1)];
 #pragma unroll
         for (int u = 0; u < kSumU; ++u) {
-            const bool in = (c0 + u * kSumWaves) * kChunk + lane < n;
+            const bool in = (c0 + u * waves) * kChunk + lane < n;
             const Counts c3 = unpack_counts(w[u], n);
             v[u] = in ? (h(c3.xz) + h(c3.yz)) - h(c3.z) : 0.0;
         }
@@ -2141,7 +2139,7 @@ __global__ __launch_bounds__(kSumThreads) void list_sum_kernel(const ListLaunch 
             for (int u = 0; u < kSumU; ++u) v[u] = v[u] + __shfl_xor(v[u], off, 64);
 #pragma unroll
         for (int u = 0; u < kSumU; ++u)
-            if (lane == 0 && c0 + u * kSumWaves < nch) part[c0 + u * kSumWaves] = v[u];
+            if (lane == 0 && c0 + u * waves < nch) part[c0 + u * waves] = v[u];
     }
     __syncthreads();
     if (tid) return;
@@ -2264,10 +2262,8 @@ int launch_list_wavelet(const ListLaunch &L, void *stream) {
         return -1;
     ListLaunch arg = L;
     void *args[] = {(void *)&arg};
-    return hipLaunchKernel(fn, dim3((unsigned)L.ests), dim3(kWvThreads), args, L.wavelet_lds, (hipStream_t)stream) ==
-                   hipSuccess
-               ? 0
-               : -1;
+    const dim3 grid((unsigned)L.ests), block((unsigned)L.wavelet_threads);
+    return hipLaunchKernel(fn, grid, block, args, L.wavelet_lds, (hipStream_t)stream) == hipSuccess ? 0 : -1;
 }
 
 int launch_list_walk(const ListLaunch &L, void *stream) {
@@ -2286,7 +2282,7 @@ int launch_list_walk(const ListLaunch &L, void *stream) {
         hipFuncSetAttribute(cf, hipFuncAttributeMaxDynamicSharedMemorySize, 163840 - 1024) != hipSuccess)
         return -1;
     const dim3 cuts((unsigned)L.ests, (unsigned)L.est_cuts);
-    return hipLaunchKernel(cf, cuts, dim3(kWalkThreads), args, L.walk_lds, (hipStream_t)stream) == hipSuccess ? 0 : -1;
+    return hipLaunchKernel(cf, cuts, dim3((unsigned)L.walk_threads), args, L.walk_lds, (hipStream_t)stream) == hipSuccess ? 0 : -1;
 }
 
 int launch_list_rank_count(const ListLaunch &L, void *stream) {
@@ -2314,7 +2310,8 @@ int launch_list_fallback(const ListLaunch &L, void *stream) {
 int launch_list_reduce(const ListLaunch &L, const double *harm, void *stream) {
     if (L.ests <= 0 || L.max_chunks <= 0) return 0;
     if (sums_in_one(L.max_chunks, L.ests)) {
-        hipLaunchKernelGGL(list_sum_kernel, dim3((unsigned)L.ests), dim3(kSumThreads), 0, (hipStream_t)stream, L, harm);
+        hipLaunchKernelGGL(list_sum_kernel, dim3((unsigned)L.ests), dim3((unsigned)row_threads(L.max_chunks * kChunk)),
+                           0, (hipStream_t)stream, L, harm);
         return hipGetLastError() == hipSuccess ? 0 : -1;
     }
     const dim3 grid1((unsigned)L.ests, (unsigned)((L.max_chunks + kWaves - 1) / kWaves));

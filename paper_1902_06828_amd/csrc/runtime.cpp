@@ -1597,12 +1597,16 @@ int Batch::prepare_lists(const std::vector<JobSpec> &specs, const std::vector<in
     L.walk_unit_t = wu.t;
     L.walk_blocks = wu.blocks;
     L.walk_lds = 0;
+    L.walk_threads = L.wavelet_threads = 64;
     L.walk_window = L.walk_many = 0;
     for (const ScanUnit &u : wu.u) L.walk_many |= u.n_jobs > 1;
     for (int j = 0; j < n_ljobs_; ++j)
         if (walks(j)) {
             L.walk_lds = std::max(L.walk_lds, 2 * sizeof(float) * (size_t)specs[j].n);
+            L.walk_threads = std::max(L.walk_threads, row_threads(specs[j].n));
             L.walk_window |= specs[j].theiler > 0;
+        } else if (offs[j].wavelet) {
+            L.wavelet_threads = std::max(L.wavelet_threads, row_threads(specs[j].n));
         }
     L.scan_step = env_int("MTE_SCAN_STEP", tc.scan_step > 0 ? tc.scan_step : (n_ljobs_ == 1 ? 8 : 4)) == 4 ? 4 : 8;
     perm_cu_ = std::max(0, env_int("MTE_PERMUTE_BLOCKS_PER_CU", tc.perm_cu > 0 ? tc.perm_cu : kPermuteBlocksPerCu));
