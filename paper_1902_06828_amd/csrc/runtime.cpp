@@ -628,6 +628,11 @@ constexpr int kPermuteBlocksPerCu = 2;
 
 // ---------------------------------------------------------------- tuning
 constexpr double kTuneMargin = 0.97;   // a candidate must be 3% faster to replace the best
+// The same for list knobs, which are timed on a busy GPU and, the default and
+// the winner, in turn at the end.  With 3% a warm default kept off gains of
+// 1.5 to 3%: N = 20000, dz = 4, window 7, 201 estimates 1.70 ms against 1.65,
+// N = 9995, dz = 3 0.650 against 0.639.
+constexpr double kListTuneMargin = 0.99;
 // Wall time one shape's tuning may take (MTE_TUNE_BUDGET_MS overrides): the
 // candidates are timed in order of how far they are from the default, and
 // the search stops when the budget is spent.  A shape whose launch takes
@@ -837,35 +842,40 @@ static int tune_lists(const std::vector<JobSpec> &lists, hipStream_t s, int mode
     MTE_HIP(hipEventCreate(&e1));
     // the first candidate is the default (2 build rows, 4 lanes, the grouped
     // order and 8-entry steps for one job, 4-entry steps for several);
-    // another replaces the best so far only when it is kTuneMargin faster
+    // another replaces the best so far only when it is kListTuneMargin faster
     double best_ms = 1e30, dflt_ms = 1e30;
     const TileChoice dflt = cand[order.front()];
     TileChoice best = dflt;
     const double t_end = wall_s() + tune_budget_s();
-    auto time_default = [&] {
-        const double ms = time_launch(probe, dflt, s, e0, e1);
-        if (ms >= 0.0) dflt_ms = std::min(dflt_ms, ms);
+    auto timed = [&](const TileChoice &tc) {
+        const double ms = time_launch(probe, tc, s, e0, e1);
+        return ms >= 0.0 ? ms : 1e30;
     };
     // the first launches of a shape run on a GPU that has been idle: the
-    // default is timed until it has run for a while, and once more against the
-    // winner (timed once, cold, it lost to knobs that a test of 201 estimates
+    // default is timed until it has run for a while, and the last of these
+    // counts (timed once, cold, it lost to knobs that a test of 201 estimates
     // with one Z column runs 3% slower with)
     const double t_warm = std::min(t_end, wall_s() + kTuneWarmMs * 1e-3);
-    do time_default();
+    do dflt_ms = timed(dflt);
     while (wall_s() < t_warm);
     best_ms = dflt_ms;
     for (size_t oi = 1; oi < order.size(); ++oi) {
         if (wall_s() > t_end) break;
         const TileChoice &tc = cand[order[oi]];
-        const double ms = time_launch(probe, tc, s, e0, e1);
-        if (ms >= 0.0 && ms < best_ms * (best_ms < 1e30 ? kTuneMargin : 1.0)) {
+        const double ms = timed(tc);
+        if (ms < best_ms * (best_ms < 1e30 ? kListTuneMargin : 1.0)) {
             best_ms = ms;
             best = tc;
         }
     }
+    // one timing can be off by more than the margin: both again, in turn
     if (best_ms < dflt_ms) {
-        time_default();
-        if (!(best_ms < dflt_ms * kTuneMargin)) {
+        best_ms = dflt_ms = 1e30;
+        for (int i = 0; i < 2 && (i == 0 || wall_s() < t_end); ++i) {
+            dflt_ms = std::min(dflt_ms, timed(dflt));
+            best_ms = std::min(best_ms, timed(best));
+        }
+        if (!(best_ms < dflt_ms * kListTuneMargin)) {
             best_ms = dflt_ms;
             best = dflt;
         }
